@@ -84,21 +84,14 @@ __global__ __launch_bounds__(256) void router_logits_f32_kernel(const float* __r
   if (lane == 0) logits[pair] = acc;
 }
 
-// bf16 layers, more than 8 tokens: see router_logits_tokens.
-template <int NF>
-__global__ __launch_bounds__(256) void router_logits_bf16_kernel(const bf16_t* __restrict__ x,
-                                                                 const bf16_t* __restrict__ w_g, int n_tokens,
-                                                                 int n_experts, int hidden, float* __restrict__ logits,
-                                                                 int tokens_per_block) {
-  router_logits_tokens<NF>(x, w_g, n_tokens, n_experts, hidden, logits, tokens_per_block, nullptr);
-}
-
-// decode batches (T <= 8): one block, loads kept in flight (router_body.h)
-template <int NF>
-__global__ __launch_bounds__(256) void router_logits_small_kernel(const bf16_t* __restrict__ x,
-                                                                  const bf16_t* __restrict__ w_g, int n_tokens,
-                                                                  int n_experts, int hidden, float* __restrict__ logits) {
-  router_logits_small<NF>(x, w_g, n_tokens, n_experts, hidden, logits, nullptr);
+// bf16 layers: see router_body.h
+template <class SHAPE>
+__global__ __launch_bounds__(SHAPE::THREADS, SHAPE::NW == 8 ? 4 : 1) void router_logits_bf16_kernel(const bf16_t* __restrict__ x,
+                                                                            const bf16_t* __restrict__ w_g, int n_tokens,
+                                                                            int n_experts, int hidden,
+                                                                            float* __restrict__ logits, int tokens_per_block) {
+  __shared__ float red[SHAPE::RED];
+  router_logits_block<SHAPE>(x, w_g, n_tokens, n_experts, hidden, logits, tokens_per_block, red, nullptr);
 }
 
 }  // namespace hmoe
@@ -138,20 +131,13 @@ extern "C" int32_t hmoe_router_logits(const hmoe_layer_desc* desc, const void* x
   if (desc->dtype != HMOE_F32) {
     if (H % 16 != 0) return HMOE_ERR_UNSUPPORTED;
     if (!aligned16(x) || !aligned16(w_g)) return HMOE_ERR_INVALID_ARG;
-    int tpb = 32;  // tokens per block: fewer while the grid would leave more than half of the CUs without a block
-    while (tpb > 4 && (T + tpb - 1) / tpb < 128) tpb /= 2;
-    const dim3 grid((unsigned)((T + tpb - 1) / tpb)), block(256);
-    const bf16_t* xb = (const bf16_t*)x;
-    const bf16_t* wb = (const bf16_t*)w_g;
-    if (T <= ROUTER_SMALL_T) {
-      if (E <= 32) hipLaunchKernelGGL((router_logits_small_kernel<1>), dim3(1), block, 0, s, xb, wb, T, E, H, logits);
-      else if (E <= 64) hipLaunchKernelGGL((router_logits_small_kernel<2>), dim3(1), block, 0, s, xb, wb, T, E, H, logits);
-      else if (E <= 128) hipLaunchKernelGGL((router_logits_small_kernel<4>), dim3(1), block, 0, s, xb, wb, T, E, H, logits);
-      else hipLaunchKernelGGL((router_logits_small_kernel<8>), dim3(1), block, 0, s, xb, wb, T, E, H, logits);
-    } else if (E <= 32) hipLaunchKernelGGL((router_logits_bf16_kernel<1>), grid, block, 0, s, xb, wb, T, E, H, logits, tpb);
-    else if (E <= 64) hipLaunchKernelGGL((router_logits_bf16_kernel<2>), grid, block, 0, s, xb, wb, T, E, H, logits, tpb);
-    else if (E <= 128) hipLaunchKernelGGL((router_logits_bf16_kernel<4>), grid, block, 0, s, xb, wb, T, E, H, logits, tpb);
-    else hipLaunchKernelGGL((router_logits_bf16_kernel<8>), grid, block, 0, s, xb, wb, T, E, H, logits, tpb);
+    const int tpb = router_tokens_per_block(T, E);
+    const dim3 grid((unsigned)((T + tpb - 1) / tpb));
+#define HMOE_LAUNCH_LOGITS(G, VPL, MA, NF, KS, NW)                                                                 \
+  hipLaunchKernelGGL((router_logits_bf16_kernel<RouterShape<MA, NF, KS, NW>>), grid, dim3(64 * NW), 0, s, (const bf16_t*)x, \
+                     (const bf16_t*)w_g, T, E, H, logits, tpb)
+    HMOE_ROUTER_SHAPES(E, tpb, HMOE_LAUNCH_LOGITS);
+#undef HMOE_LAUNCH_LOGITS
   } else {
     const long pairs = (long)T * E;
     hipLaunchKernelGGL(router_logits_f32_kernel, dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, s, (const float*)x,

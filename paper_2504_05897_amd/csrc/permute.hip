@@ -2,14 +2,20 @@
 //
 // Per-expert load is the quantity everything downstream consumes (Section IV-B uses it to order
 // the queues); here it becomes expert_offsets.  The sort is stable and uses no order-dependent
-// atomics, so the result is the same on every run:
-//   1. histogram   every block counts its 1024-assignment chunk per expert in LDS
-//   2. scan        one block turns the per-block counts into per-(block, expert) bases and the
-//                  per-expert totals into expert_offsets
-//   3. rank        every block re-reads its chunk; a wave ranks 64 assignments at a time with
-//                  ballots (same-key mask), waves and steps are ordered by per-wave LDS bases
-// For A <= 1024 (every decode shape) one block does all three in one launch.
-//   4. gather      x_perm[p] = x[perm[p] / K], 16 bytes per lane
+// atomics, so the result is the same on every run.  A block ranks one assignment per thread: a wave finds the lanes of
+// equal key with ballots, and waves are ordered by per-wave LDS counts.  What a block needs besides its own
+// assignments is, per expert, how many lie in front of them and how many there are in all:
+//   A <= 1024 (every decode shape)  one block of 16 waves, nothing lies elsewhere
+//   A <= 16384                      blocks of 16 waves, each counts all A keys itself (64 KB from L2 at most): one launch
+//   A <= 262144                     a histogram launch over chunks of 1024 first; every block adds up the counts
+//   beyond                          histogram, one-block scan, rank
+// The launches are latency, not bandwidth (a few KB each), so what counts is how many follow one another.  T = 1003,
+// K = 6, 64 experts: histogram, scan and rank took 5.6 + 6.0 + 6.8 us, the one launch 8.3 us; T = 16384, next to the shared
+// experts' FFN: 6.4 + 31 + 9.9 us, now 6.3 + 20 us.
+// The last two have blocks of four waves and 6 KB of LDS: batches of that size run next to prefill FFN blocks (of the
+// shared experts) that leave a CU 56 registers per lane and 9 KB of LDS, and what does not fit beside them waits for
+// their end (16-wave blocks there: the 16384-token layer 1.3 % slower).
+//   then: gather    x_perm[p] = x[perm[p] / K], 16 bytes per lane
 #include <mutex>
 
 #include "route_body.h"
@@ -17,10 +23,11 @@
 
 namespace hmoe {
 
-constexpr int PB_THREADS = 256;
-constexpr int PB_WAVES = PB_THREADS / 64;
+constexpr int PB_THREADS = 256;              // histogram, scan, decode front end's routing
 constexpr int PB_CHUNK = 1024;               // assignments per block
-constexpr int PB_STEPS = PB_CHUNK / PB_THREADS;  // 64-wide steps per wave
+constexpr int PR_THREADS = PB_CHUNK;         // one-launch permutation: one assignment of a chunk per thread
+constexpr int PR_SELF_COUNT_CHUNKS = 16;     // up to here every rank block counts all keys itself
+constexpr int PR_SELF_SCAN_CHUNKS = 256;     // up to here every rank block adds up the histogram's counts itself
 
 __device__ __forceinline__ int clamp_key(int key, int n_experts) {
   return key < 0 ? 0 : (key >= n_experts ? n_experts - 1 : key);
@@ -59,7 +66,7 @@ __global__ __launch_bounds__(PB_THREADS) void permute_scan_kernel(int32_t* __res
   __shared__ int total[HMOE_MAX_EXPERTS];
   __shared__ int start[HMOE_MAX_EXPERTS];
   // (the counts are read 16 blocks at a time: one after the other, a read could not start before the store in
-  // front of it, and 96 blocks of the largest workload cost 96 memory round trips)
+  // front of it)
   constexpr int AHEAD = 16;
   const int e = threadIdx.x;
   if (e < n_experts) {
@@ -100,13 +107,13 @@ __global__ __launch_bounds__(PB_THREADS) void permute_scan_kernel(int32_t* __res
 // The whole permutation of at most 64 assignments (every decode batch) by one wavefront, without LDS and
 // without barriers: lane a holds assignment a, learns every other key through readlane, and counts the
 // keys that sort before its own (smaller key, or equal key in a lower lane: the stable order); lane l
-// does the same counting for experts l, 64 + l, ... to produce the offsets.  Same integers as the general
+// does the same counting for experts l, 64 + l, ... (CH of them) to produce the offsets.  Same integers as the general
 // path.  Call with the first wavefront of a block.
+template <int CH>
 __device__ __forceinline__ void permute_rank_one_wave(const int32_t* topk_idx, int n_assign, int n_experts,
                                                       int32_t* __restrict__ expert_offsets,
                                                       int32_t* __restrict__ counts_out, int32_t* __restrict__ perm,
                                                       int32_t* __restrict__ inv_perm) {
-  constexpr int CH = HMOE_MAX_EXPERTS / 64;
   const int lane = threadIdx.x % 64;
   const bool valid = lane < n_assign;
   const int key = valid ? clamp_key(topk_idx[lane], n_experts) : n_experts;
@@ -137,129 +144,203 @@ __device__ __forceinline__ void permute_rank_one_wave(const int32_t* topk_idx, i
   if (lane == 0) expert_offsets[n_experts] = n_assign;
 }
 
-// Ranks one chunk.  SINGLE: the chunk is the whole input and this block also builds the offsets.
-template <bool SINGLE>
+// Where a rank block learns what lies outside its chunk.
+enum RankSource {
+  RANK_SINGLE,     // nothing does: the chunk is the whole input
+  RANK_COUNT_ALL,  // it counts every key of the input
+  RANK_ADD_UP,     // counts [chunks][E] of the histogram launch
+  RANK_BASES       // exclusive bases [chunks][E] of the scan launch (which also wrote the offsets)
+};
+
+// Ranks assignments [64 NW b, 64 NW (b + 1)) in block b of NW waves.  expert_offsets and counts_out are written by block 0.
+template <RankSource SRC, int NW>
 __device__ __forceinline__ void permute_rank_body(const int32_t* topk_idx, int n_assign, int n_experts, int key_bits,
-                                                  const int32_t* __restrict__ block_bases,
+                                                  const int32_t* __restrict__ from_before,
                                                   int32_t* __restrict__ expert_offsets,
                                                   int32_t* __restrict__ counts_out, int32_t* __restrict__ perm,
                                                   int32_t* __restrict__ inv_perm) {
-  __shared__ int wave_base[PB_WAVES][HMOE_MAX_EXPERTS];  // first counts, then running bases
-  __shared__ int scan_tmp[HMOE_MAX_EXPERTS];
+  constexpr int THREADS = 64 * NW;
+  constexpr int PER_CHUNK = PB_CHUNK / THREADS;    // blocks that share one chunk of the histogram
+  static_assert(NW >= HMOE_MAX_EXPERTS / 64, "one thread per expert");
+  __shared__ int wave_base[NW][HMOE_MAX_EXPERTS];  // first counts, then bases
+  __shared__ int outside[2][HMOE_MAX_EXPERTS];     // per expert: in front of the block's assignments, and the rest of the others
+  __shared__ int wave_total[4];
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  if (SINGLE && n_assign <= 64) {  // uniform over the block: nothing below runs, so no barrier is left unmatched
-    if (wave == 0) permute_rank_one_wave(topk_idx, n_assign, n_experts, expert_offsets, counts_out, perm, inv_perm);
+  if (SRC == RANK_SINGLE && n_assign <= 64) {  // uniform over the block: nothing below runs, so no barrier is left unmatched
+    if (wave == 0) {
+      if (n_experts <= 64) permute_rank_one_wave<1>(topk_idx, n_assign, n_experts, expert_offsets, counts_out, perm, inv_perm);
+      else permute_rank_one_wave<HMOE_MAX_EXPERTS / 64>(topk_idx, n_assign, n_experts, expert_offsets, counts_out, perm, inv_perm);
+    }
     return;
   }
-  for (int i = threadIdx.x; i < PB_WAVES * HMOE_MAX_EXPERTS; i += PB_THREADS) (&wave_base[0][0])[i] = 0;
+  const int block = SRC == RANK_SINGLE ? 0 : (int)blockIdx.x;
+  const int chunk = block / PER_CHUNK;
+  const long a = (long)block * THREADS + threadIdx.x;
+  const bool valid = a < n_assign;
+  const int key = valid ? clamp_key(topk_idx[a], n_experts) : -1;
+  for (int i = threadIdx.x; i < NW * HMOE_MAX_EXPERTS; i += THREADS) (&wave_base[0][0])[i] = 0;
+  for (int i = threadIdx.x; i < 2 * HMOE_MAX_EXPERTS; i += THREADS) (&outside[0][0])[i] = 0;
+  const uint64_t same = same_key_mask(key, valid, key_bits);
   __syncthreads();
-
-  // each wave owns a contiguous quarter of the chunk, in PB_STEPS steps of 64
-  const long wave_first = (long)blockIdx.x * PB_CHUNK + (long)wave * (PB_STEPS * 64);
-  int keys[PB_STEPS];
+  if (valid && (same >> lane) >> 1 == 0) wave_base[wave][key] = __popcll(same);  // highest lane of the group
+  if constexpr (SRC == RANK_COUNT_ALL) {
+    static_assert(PER_CHUNK == 1, "");
+    const int n_chunks = (n_assign + PB_CHUNK - 1) / PB_CHUNK;
+    int others[PR_SELF_COUNT_CHUNKS];
 #pragma unroll
-  for (int s = 0; s < PB_STEPS; ++s) {
-    const long a = wave_first + s * 64 + lane;
-    keys[s] = a < n_assign ? clamp_key(topk_idx[a], n_experts) : -1;
-    if (keys[s] >= 0) atomicAdd(&wave_base[wave][keys[s]], 1);
+    for (int c = 0; c < PR_SELF_COUNT_CHUNKS; ++c) {
+      const long i = (long)c * PB_CHUNK + threadIdx.x;
+      others[c] = c < n_chunks && c != chunk && i < n_assign ? clamp_key(topk_idx[i], n_experts) : -1;
+    }
+#pragma unroll
+    for (int c = 0; c < PR_SELF_COUNT_CHUNKS; ++c)
+      if (others[c] >= 0) atomicAdd(&outside[c < chunk ? 0 : 1][others[c]], 1);
+  }
+  if constexpr (SRC == RANK_ADD_UP || SRC == RANK_BASES) {
+    // the rest of the block's own chunk
+    for (int q = 0; q < PER_CHUNK; ++q) {
+      const long i = (long)chunk * PB_CHUNK + q * THREADS + threadIdx.x;
+      if (q != block % PER_CHUNK && i < n_assign) atomicAdd(&outside[q < block % PER_CHUNK ? 0 : 1][clamp_key(topk_idx[i], n_experts)], 1);
+    }
+  }
+  if constexpr (SRC == RANK_ADD_UP) {
+    // THREADS / slice chunks at a time, one thread per expert of each
+    const int slice = n_experts <= 64 ? 64 : n_experts <= 128 ? 128 : 256;
+    const int e = threadIdx.x % slice, n_chunks = (n_assign + PB_CHUNK - 1) / PB_CHUNK, step = THREADS / slice;
+    int before = 0, after = 0;
+    if (e < n_experts) {
+#pragma unroll 8
+      for (int c = threadIdx.x / slice; c < n_chunks; c += step) {
+        const int n = from_before[(long)c * n_experts + e];
+        before += c < chunk ? n : 0;
+        after += c > chunk ? n : 0;
+      }
+      if (before) atomicAdd(&outside[0][e], before);
+      if (after) atomicAdd(&outside[1][e], after);
+    }
   }
   __syncthreads();
 
   // counts -> exclusive bases over (expert, wave)
   const int e = threadIdx.x;
-  int cnt[PB_WAVES], tot = 0;
-  if (e < n_experts) {
-#pragma unroll
-    for (int w = 0; w < PB_WAVES; ++w) { cnt[w] = wave_base[w][e]; tot += cnt[w]; }
-  }
-  int first;
-  if (SINGLE) {
-    // inclusive Hillis-Steele scan of the per-expert totals over the 256 threads
-    scan_tmp[threadIdx.x] = e < n_experts ? tot : 0;
-    __syncthreads();
-    for (int off = 1; off < HMOE_MAX_EXPERTS; off <<= 1) {
-      const int add = threadIdx.x >= off ? scan_tmp[threadIdx.x - off] : 0;
-      __syncthreads();
-      scan_tmp[threadIdx.x] += add;
-      __syncthreads();
-    }
-    first = scan_tmp[threadIdx.x] - tot;
-    if (e < n_experts) {
-      expert_offsets[e] = first;
-      if (counts_out) counts_out[e] = tot;
-      if (e == n_experts - 1) expert_offsets[n_experts] = first + tot;
-    }
+  int first = 0, mine = 0;
+  if (SRC == RANK_BASES) {
+    if (e < n_experts) first = from_before[(long)chunk * n_experts + e] + outside[0][e];
   } else {
-    first = e < n_experts ? block_bases[(long)blockIdx.x * n_experts + e] : 0;
+    int tot = 0, incl = 0;
+    if (e < HMOE_MAX_EXPERTS) {  // the first four waves
+      if (e < n_experts) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mine += wave_base[w][e];
+        tot = mine + outside[0][e] + outside[1][e];
+      }
+      incl = tot;
+#pragma unroll
+      for (int d = 1; d < 64; d *= 2) {
+        const int below = __shfl_up(incl, d);
+        if (lane >= d) incl += below;
+      }
+      if (lane == 63) wave_total[wave] = incl;
+    }
+    __syncthreads();
+    if (e < n_experts) {
+      for (int w = 0; w < wave; ++w) incl += wave_total[w];
+      const int start = incl - tot;
+      first = start + outside[0][e];
+      if (block == 0) {
+        expert_offsets[e] = start;
+        if (counts_out) counts_out[e] = tot;
+        if (e == n_experts - 1) expert_offsets[n_experts] = incl;
+      }
+    }
   }
   if (e < n_experts) {
     int run = first;
 #pragma unroll
-    for (int w = 0; w < PB_WAVES; ++w) { wave_base[w][e] = run; run += cnt[w]; }
+    for (int w = 0; w < NW; ++w) {
+      const int n = wave_base[w][e];
+      wave_base[w][e] = run;
+      run += n;
+    }
   }
   __syncthreads();
-
-#pragma unroll
-  for (int s = 0; s < PB_STEPS; ++s) {
-    const int key = keys[s];
-    const bool valid = key >= 0;
-    const uint64_t same = same_key_mask(key, valid, key_bits);
-    if (valid) {
-      const uint64_t below = same & ((1ull << lane) - 1ull);
-      const int pos = wave_base[wave][key] + __popcll(below);
-      const int a = (int)(wave_first + s * 64 + lane);
-      perm[pos] = a;
-      inv_perm[a] = pos;
-    }
-    __syncthreads();  // everyone has read the bases of this step
-    if (valid && (same >> lane) >> 1 == 0) wave_base[wave][key] += __popcll(same);  // highest lane of the group
-    __syncthreads();
+  if (valid) {
+    const int pos = wave_base[wave][key] + __popcll(same & ((1ull << lane) - 1ull));
+    perm[pos] = (int)a;
+    inv_perm[a] = pos;
   }
 }
 
-template <bool SINGLE>
-__global__ __launch_bounds__(PB_THREADS) void permute_rank_kernel(const int32_t* __restrict__ topk_idx, int n_assign,
+template <RankSource SRC, int NW>
+__global__ __launch_bounds__(64 * NW) void permute_rank_kernel(const int32_t* __restrict__ topk_idx, int n_assign,
                                                                   int n_experts, int key_bits,
-                                                                  const int32_t* __restrict__ block_bases,
+                                                                  const int32_t* __restrict__ from_before,
                                                                   int32_t* __restrict__ expert_offsets,
                                                                   int32_t* __restrict__ counts_out,
                                                                   int32_t* __restrict__ perm,
                                                                   int32_t* __restrict__ inv_perm) {
-  permute_rank_body<SINGLE>(topk_idx, n_assign, n_experts, key_bits, block_bases, expert_offsets, counts_out, perm,
-                            inv_perm);
+  permute_rank_body<SRC, NW>(topk_idx, n_assign, n_experts, key_bits, from_before, expert_offsets, counts_out, perm, inv_perm);
 }
 
-// One block routes its tokens one lane group at a time, so beyond a few dozen tokens the many-block
+// One block routes its tokens a few at a time, so beyond a few dozen tokens the many-block
 // route kernel plus the one-block rank kernel are faster than the single launch (measured at 512
 // tokens: 10 us against 25 us).
 constexpr int ROUTE_PERMUTE_SMALL_T = 64;
 
 // Small batches (T <= 64 and A <= 1024, every decode shape): routing and permutation in ONE block and one launch.
-// The block first routes all tokens (lane groups as in hmoe_route), then ranks the assignments it has
-// just written.
+// The block first routes all tokens (lane groups as in hmoe_route; the next group's logits are on their way while one
+// is routed), then ranks the assignments it has just made (kept in LDS).  Sixteen waves: 21 tokens of 64 experts, K = 8 were
+// routed in six rounds by four waves.
 template <int G, int VPL>
-__global__ __launch_bounds__(PB_THREADS) void route_permute_small_kernel(const float* __restrict__ logits, int n_tokens,
+__global__ __launch_bounds__(PR_THREADS) void route_permute_small_kernel(const float* __restrict__ logits, int n_tokens,
                                                                          int n_experts, int top_k, int key_bits,
                                                                          int32_t* topk_idx, float* __restrict__ topk_w,
                                                                          int32_t* __restrict__ expert_offsets,
                                                                          int32_t* __restrict__ counts_out,
                                                                          int32_t* __restrict__ perm,
                                                                          int32_t* __restrict__ inv_perm) {
-  constexpr int TOKENS_PER_PASS = PB_THREADS / G;
+  constexpr int TOKENS_PER_PASS = PR_THREADS / G;
+  __shared__ int32_t chosen[PB_CHUNK];  // the ids once more, for the ranking below
+  const int gl = threadIdx.x % G;
+  uint32_t next[VPL];
+  load_keys<G, VPL>(logits, n_experts, threadIdx.x / G, (int)threadIdx.x / G < n_tokens, gl, next);
   for (int t0 = 0; t0 < n_tokens; t0 += TOKENS_PER_PASS) {
     const long token = t0 + threadIdx.x / G;
-    route_token<G, VPL>(logits, n_experts, top_k, token, token < n_tokens, threadIdx.x % G, topk_idx, topk_w);
+    uint32_t key[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) key[i] = next[i];
+    load_keys<G, VPL>(logits, n_experts, token + TOKENS_PER_PASS, token + TOKENS_PER_PASS < n_tokens, gl, next);
+    route_keys<G, VPL>(key, n_experts, top_k, token, token < n_tokens, gl, topk_idx, topk_w, chosen);
   }
-  __threadfence_block();
-  __syncthreads();  // the ids written above are read back below by other lanes of this block
-  permute_rank_body<true>(topk_idx, n_tokens * top_k, n_experts, key_bits, nullptr, expert_offsets, counts_out, perm,
-                          inv_perm);
+  __syncthreads();
+  permute_rank_body<RANK_SINGLE, PR_THREADS / 64>(chosen, n_tokens * top_k, n_experts, key_bits, nullptr, expert_offsets, counts_out, perm,
+                                 inv_perm);
 }
 
-// Decode batches (T <= 8, bf16): router logits, routing and permutation in ONE block and one launch.
-// The logits go to global memory (they are an output) and to LDS, from where the lane groups route.
-template <int G, int VPL, int NF>
-__global__ __launch_bounds__(PB_THREADS) void front_small_kernel(const bf16_t* __restrict__ x,
+// bf16 batches: router logits and routing in one launch.  A block computes the logits of its tokens (global memory,
+// they are an output, and LDS) and routes them from LDS, lane groups as in hmoe_route.
+template <int G, int VPL, class SHAPE>
+__device__ __forceinline__ void front_tokens_body(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_g, int hidden,
+                                                  float* __restrict__ logits, int n_tokens, int n_experts, int top_k,
+                                                  int tokens_per_block, int32_t* __restrict__ topk_idx,
+                                                  float* __restrict__ topk_w, int32_t* lds_idx) {
+  constexpr int MAX_EXPERTS = SHAPE::EXPERT_FRAGS * 16;
+  __shared__ float red[SHAPE::RED];
+  __shared__ float lds_logits[SHAPE::MA * 16 * MAX_EXPERTS];
+  router_logits_block<SHAPE>(x, w_g, n_tokens, n_experts, hidden, logits, tokens_per_block, red, lds_logits);  // ends with a barrier
+  constexpr int TOKENS_PER_PASS = SHAPE::THREADS / G;
+  const long t0 = (long)blockIdx.x * tokens_per_block;
+  for (int l0 = 0; l0 < tokens_per_block; l0 += TOKENS_PER_PASS) {
+    const int local = l0 + threadIdx.x / G;
+    const bool valid = local < tokens_per_block && t0 + local < n_tokens;
+    route_token<G, VPL>(lds_logits, n_experts, top_k, local, valid, threadIdx.x % G, topk_idx + t0 * top_k,
+                        topk_w + t0 * top_k, lds_idx);
+  }
+}
+
+// ... of up to ROUTER_SMALL_T tokens: one block, which permutes as well.
+template <int G, int VPL, class SHAPE>
+__global__ __launch_bounds__(PR_THREADS) void front_small_kernel(const bf16_t* __restrict__ x,
                                                                  const bf16_t* __restrict__ w_g, int hidden,
                                                                  float* __restrict__ logits, int n_tokens, int n_experts,
                                                                  int top_k, int key_bits, int32_t* topk_idx,
@@ -268,38 +349,22 @@ __global__ __launch_bounds__(PB_THREADS) void front_small_kernel(const bf16_t* _
                                                                  int32_t* __restrict__ counts_out,
                                                                  int32_t* __restrict__ perm,
                                                                  int32_t* __restrict__ inv_perm) {
-  __shared__ float lds_logits[ROUTER_SMALL_T * HMOE_MAX_EXPERTS];
-  router_logits_small<NF>(x, w_g, n_tokens, n_experts, hidden, logits, lds_logits);  // ends with a barrier
-  constexpr int TOKENS_PER_PASS = PB_THREADS / G;
-  for (int t0 = 0; t0 < n_tokens; t0 += TOKENS_PER_PASS) {
-    const long token = t0 + threadIdx.x / G;
-    route_token<G, VPL>(lds_logits, n_experts, top_k, token, token < n_tokens, threadIdx.x % G, topk_idx, topk_w);
-  }
-  __threadfence_block();
+  static_assert(PR_THREADS == SHAPE::THREADS, "");
+  __shared__ int32_t chosen[PB_CHUNK];
+  front_tokens_body<G, VPL, SHAPE>(x, w_g, hidden, logits, n_tokens, n_experts, top_k, 16, topk_idx, topk_w, chosen);
   __syncthreads();
-  permute_rank_body<true>(topk_idx, n_tokens * top_k, n_experts, key_bits, nullptr, expert_offsets, counts_out, perm,
-                          inv_perm);
+  permute_rank_body<RANK_SINGLE, PR_THREADS / 64>(chosen, n_tokens * top_k, n_experts, key_bits, nullptr, expert_offsets, counts_out, perm,
+                                 inv_perm);
 }
 
-// Larger bf16 batches: router logits and routing in one launch.  A block computes the logits of its tokens (global
-// memory, they are an output, and LDS) and routes them from LDS, lane groups as in hmoe_route; the permutation,
-// which needs every token's choice, stays a launch of its own.
-template <int G, int VPL, int NF>
-__global__ __launch_bounds__(PB_THREADS) void front_tokens_kernel(const bf16_t* __restrict__ x,
-                                                                  const bf16_t* __restrict__ w_g, int hidden,
-                                                                  float* __restrict__ logits, int n_tokens, int n_experts,
-                                                                  int top_k, int tokens_per_block, int32_t* topk_idx,
-                                                                  float* __restrict__ topk_w) {
-  __shared__ float lds_logits[32 * NF * 32];
-  router_logits_tokens<NF>(x, w_g, n_tokens, n_experts, hidden, logits, tokens_per_block, lds_logits);  // ends with a barrier
-  constexpr int TOKENS_PER_PASS = PB_THREADS / G;
-  const long t0 = (long)blockIdx.x * tokens_per_block;
-  for (int l0 = 0; l0 < tokens_per_block; l0 += TOKENS_PER_PASS) {
-    const int local = l0 + threadIdx.x / G;
-    const bool valid = local < tokens_per_block && t0 + local < n_tokens;
-    route_token<G, VPL>(lds_logits, n_experts, top_k, local, valid, threadIdx.x % G, topk_idx + t0 * top_k,
-                        topk_w + t0 * top_k);
-  }
+// ... of more: the permutation, which needs every token's choice, stays a launch of its own.
+template <int G, int VPL, class SHAPE>
+__global__ __launch_bounds__(SHAPE::THREADS, SHAPE::NW == 8 ? 4 : 1) void front_tokens_kernel(const bf16_t* __restrict__ x,
+                                                                      const bf16_t* __restrict__ w_g, int hidden,
+                                                                      float* __restrict__ logits, int n_tokens, int n_experts,
+                                                                      int top_k, int tokens_per_block, int32_t* topk_idx,
+                                                                      float* __restrict__ topk_w) {
+  front_tokens_body<G, VPL, SHAPE>(x, w_g, hidden, logits, n_tokens, n_experts, top_k, tokens_per_block, topk_idx, topk_w, nullptr);
 }
 
 // x_perm[p, :] = x[perm[p] / K, :], rows of row_bytes (multiple of 16)
@@ -349,16 +414,24 @@ static int32_t permute_with_workspace(const hmoe_layer_desc* desc, const int32_t
   int32_t* block_counts = (int32_t*)workspace;
   int32_t* counts_dev = block_counts + (size_t)(nblk > 0 ? nblk : 0) * E;
 
+#define HMOE_LAUNCH_RANK(SRC, NW, FROM, OFFSETS, COUNTS)                                                              \
+  hipLaunchKernelGGL((permute_rank_kernel<SRC, NW>), dim3(A > 0 ? (unsigned)((A + 64 * NW - 1) / (64 * NW)) : 1), dim3(64 * NW), 0, s, \
+                     topk_idx, (int)A, E, key_bits, (const int32_t*)(FROM), OFFSETS, COUNTS, perm, inv_perm)
   if (nblk <= 1) {
-    hipLaunchKernelGGL((permute_rank_kernel<true>), dim3(1), dim3(PB_THREADS), 0, s, topk_idx, (int)A, E, key_bits,
-                       (const int32_t*)nullptr, expert_offsets, counts_dev, perm, inv_perm);
+    HMOE_LAUNCH_RANK(RANK_SINGLE, 16, nullptr, expert_offsets, counts_dev);
+  } else if (nblk <= PR_SELF_COUNT_CHUNKS) {
+    HMOE_LAUNCH_RANK(RANK_COUNT_ALL, 16, nullptr, expert_offsets, counts_dev);
   } else {
     hipLaunchKernelGGL(permute_hist_kernel, dim3(nblk), dim3(PB_THREADS), 0, s, topk_idx, (int)A, E, block_counts);
-    hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(PB_THREADS), 0, s, block_counts, nblk, E, (int)A,
-                       expert_offsets, counts_dev);
-    hipLaunchKernelGGL((permute_rank_kernel<false>), dim3(nblk), dim3(PB_THREADS), 0, s, topk_idx, (int)A, E, key_bits,
-                       (const int32_t*)block_counts, expert_offsets, (int32_t*)nullptr, perm, inv_perm);
+    if (nblk <= PR_SELF_SCAN_CHUNKS) {
+      HMOE_LAUNCH_RANK(RANK_ADD_UP, 4, block_counts, expert_offsets, counts_dev);
+    } else {
+      hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(PB_THREADS), 0, s, block_counts, nblk, E, (int)A,
+                         expert_offsets, counts_dev);
+      HMOE_LAUNCH_RANK(RANK_BASES, 4, block_counts, (int32_t*)nullptr, (int32_t*)nullptr);
+    }
   }
+#undef HMOE_LAUNCH_RANK
   HMOE_HIP(hipGetLastError());
   if (h_counts_pinned)
     HMOE_HIP(hipMemcpyAsync(h_counts_pinned, counts_dev, (size_t)E * sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -448,7 +521,7 @@ extern "C" int32_t hmoe_route_permute(const hmoe_layer_desc* desc, const float* 
   while ((1 << key_bits) < E) ++key_bits;
   int32_t* counts_dev = (int32_t*)workspace + (size_t)n_chunks(A) * E;
 #define HMOE_LAUNCH_SMALL(G, VPL)                                                                                   \
-  hipLaunchKernelGGL((route_permute_small_kernel<G, VPL>), dim3(1), dim3(PB_THREADS), 0, s, logits, (int)T, E, K, key_bits, \
+  hipLaunchKernelGGL((route_permute_small_kernel<G, VPL>), dim3(1), dim3(PR_THREADS), 0, s, logits, (int)T, E, K, key_bits, \
                      topk_idx, topk_w, expert_offsets, counts_dev, perm, inv_perm)
   if (E <= 8) HMOE_LAUNCH_SMALL(8, 1);
   else if (E <= 16) HMOE_LAUNCH_SMALL(16, 1);
@@ -472,23 +545,16 @@ extern "C" int32_t hmoe_router_route_permute(const hmoe_layer_desc* desc, const 
   if (rc != HMOE_OK) return rc;
   if (T < 0 || !expert_offsets) return HMOE_ERR_INVALID_ARG;
   const long A = (long)T * desc->top_k;
-  if (T > ROUTER_SMALL_T && T <= 2048 && desc->dtype != HMOE_F32 && desc->hidden % 16 == 0 && x && w_g && logits &&
-      topk_idx && topk_w && aligned16(x) && aligned16(w_g)) {
-    // logits and routing in one launch, then the permutation (a launch saved; beyond a few thousand tokens the
-    // separate routing kernel, with a block per few tokens, is the faster one)
+  if ((T > ROUTER_SMALL_T || A > PB_CHUNK) && desc->dtype != HMOE_F32 && desc->hidden % 16 == 0 && x && w_g && logits && topk_idx &&
+      topk_w && aligned16(x) && aligned16(w_g)) {
+    // logits and routing in one launch, then the permutation
     const int E = desc->n_experts, K = desc->top_k;
-    int tpb = 32;  // tokens per block: fewer while the grid would leave more than half of the CUs without a block
-    while (tpb > 4 && (T + tpb - 1) / tpb < 128) tpb /= 2;
+    const int tpb = router_tokens_per_block(T, E);
     const dim3 grid((unsigned)((T + tpb - 1) / tpb));
-#define HMOE_LAUNCH_FRONT_TOKENS(G, VPL, NF)                                                                        \
-  hipLaunchKernelGGL((front_tokens_kernel<G, VPL, NF>), grid, dim3(PB_THREADS), 0, (hipStream_t)stream,             \
+#define HMOE_LAUNCH_FRONT_TOKENS(G, VPL, MA, NF, KS, NW)                                                                    \
+  hipLaunchKernelGGL((front_tokens_kernel<G, VPL, RouterShape<MA, NF, KS, NW>>), grid, dim3(64 * NW), 0, (hipStream_t)stream, \
                      (const bf16_t*)x, (const bf16_t*)w_g, desc->hidden, logits, (int)T, E, K, tpb, topk_idx, topk_w)
-    if (E <= 8) HMOE_LAUNCH_FRONT_TOKENS(8, 1, 1);
-    else if (E <= 16) HMOE_LAUNCH_FRONT_TOKENS(16, 1, 1);
-    else if (E <= 32) HMOE_LAUNCH_FRONT_TOKENS(32, 1, 1);
-    else if (E <= 64) HMOE_LAUNCH_FRONT_TOKENS(64, 1, 2);
-    else if (E <= 128) HMOE_LAUNCH_FRONT_TOKENS(64, 2, 4);
-    else HMOE_LAUNCH_FRONT_TOKENS(64, 4, 8);
+    HMOE_ROUTER_SHAPES(E, tpb, HMOE_LAUNCH_FRONT_TOKENS);
 #undef HMOE_LAUNCH_FRONT_TOKENS
     HMOE_HIP(hipGetLastError());
     return hmoe_permute(desc, topk_idx, T, nullptr, nullptr, expert_offsets, perm, inv_perm, h_counts_pinned, workspace,
@@ -510,16 +576,11 @@ extern "C" int32_t hmoe_router_route_permute(const hmoe_layer_desc* desc, const 
   int key_bits = 0;
   while ((1 << key_bits) < E) ++key_bits;
   int32_t* counts_dev = (int32_t*)workspace + (size_t)n_chunks(A) * E;
-#define HMOE_LAUNCH_FRONT(G, VPL, NF)                                                                              \
-  hipLaunchKernelGGL((front_small_kernel<G, VPL, NF>), dim3(1), dim3(PB_THREADS), 0, s, (const bf16_t*)x,          \
-                     (const bf16_t*)w_g, desc->hidden, logits, (int)T, E, K, key_bits, topk_idx, topk_w, expert_offsets, \
+#define HMOE_LAUNCH_FRONT(G, VPL, MA, NF, KS, NW)                                                                            \
+  hipLaunchKernelGGL((front_small_kernel<G, VPL, RouterShape<MA, NF, KS, NW>>), dim3(1), dim3(PR_THREADS), 0, s, (const bf16_t*)x, \
+                     (const bf16_t*)w_g, desc->hidden, logits, (int)T, E, K, key_bits, topk_idx, topk_w, expert_offsets,   \
                      counts_dev, perm, inv_perm)
-  if (E <= 8) HMOE_LAUNCH_FRONT(8, 1, 1);
-  else if (E <= 16) HMOE_LAUNCH_FRONT(16, 1, 1);
-  else if (E <= 32) HMOE_LAUNCH_FRONT(32, 1, 1);
-  else if (E <= 64) HMOE_LAUNCH_FRONT(64, 1, 2);
-  else if (E <= 128) HMOE_LAUNCH_FRONT(64, 2, 4);
-  else HMOE_LAUNCH_FRONT(64, 4, 8);
+  HMOE_ROUTER_SHAPES_16(E, HMOE_LAUNCH_FRONT);
 #undef HMOE_LAUNCH_FRONT
   HMOE_HIP(hipGetLastError());
   if (h_counts_pinned)

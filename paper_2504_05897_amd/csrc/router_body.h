@@ -1,171 +1,177 @@
-// Router logits x . W_g (Eq. (1), Section II-A) of a decode batch by ONE block; shared by
-// hmoe_router_logits (T <= 8) and the fused decode front end.
+// Router logits x . W_g (Eq. (1), Section II-A) of the tokens of a block; shared by hmoe_router_logits and the fused
+// front ends.
 #pragma once
 
 #include "common.h"
 
 namespace hmoe {
 
-constexpr int ROUTER_SMALL_T = 8;  // tokens the one-block body handles
+constexpr int ROUTER_SMALL_T = 16;      // tokens up to which a single block computes the logits (and the fused front end
+                                        // routes and permutes in the same launch)
 
-// 256 threads.  bf16 operands, K-contiguous rows: lanes load 32x32x16 MFMA fragments straight from
-// global memory (token or expert row = lane % 32, 8 k values at 8 * (lane / 32)); the 4 waves split K
-// into 4 contiguous ranges and add their partial sums in wave order, which is the summation order of
-// the many-token kernel, so both produce the same bits.  With at most 8 tokens only accumulator
-// registers 0..3 hold rows (register r of lane (half, col) is token 4 * half + r, expert col).
-// Two register sets of U k-tiles alternate so that loads stay in flight while the other set is
-// multiplied: a decode router is a chain of dependent memory round trips, not a bandwidth problem.
-//   logits [T, E] global out; lds_logits [T * E] the same values in LDS, or NULL.
-// Ends with a block barrier.
-template <int NF>
-__device__ __forceinline__ void router_logits_small(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_g,
-                                                    int n_tokens, int n_experts, int hidden,
-                                                    float* __restrict__ logits, float* lds_logits) {
-  constexpr int U = NF == 1 ? 8 : NF == 2 ? 4 : NF == 4 ? 2 : 1;
-  __shared__ float red[3 * NF * 4 * 64];
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, half = lane / 32, col = lane % 32;
-  const int kt = hidden / 16, per_wave = (kt + 3) / 4;
-  const int kb0 = min(wave * per_wave, kt), kb1 = min(kb0 + per_wave, kt);
-  const bool has_tok = col < n_tokens;
-  const u32x4* xp = (const u32x4*)(x + (long)(has_tok ? col : 0) * hidden) + half;
-  const u32x4* wp[NF];
-  bool has_exp[NF];
-#pragma unroll
-  for (int j = 0; j < NF; ++j) {
-    has_exp[j] = j * 32 + col < n_experts;
-    wp[j] = (const u32x4*)(w_g + (long)(has_exp[j] ? j * 32 + col : 0) * hidden) + half;
-  }
-  f32x16_t acc[NF];
-#pragma unroll
-  for (int j = 0; j < NF; ++j) acc[j] = f32x16_t{0};
-  u32x4 xa[2][U], wb[2][U][NF];
-  auto load = [&](int set, int kb) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool in_range = kb + u < kb1;
-      xa[set][u] = (in_range && has_tok) ? xp[(long)(kb + u) * 2] : u32x4{0, 0, 0, 0};
-#pragma unroll
-      for (int j = 0; j < NF; ++j)
-        wb[set][u][j] = (in_range && has_exp[j]) ? wp[j][(long)(kb + u) * 2] : u32x4{0, 0, 0, 0};
-    }
-  };
-  auto multiply = [&](int set) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int j = 0; j < NF; ++j) acc[j] = mfma_32x32x16_bf16(xa[set][u], wb[set][u][j], acc[j]);
-  };
-  load(0, kb0);
-  for (int kb = kb0; kb < kb1; kb += 2 * U) {
-    load(1, kb + U);
-    multiply(0);
-    load(0, kb + 2 * U);
-    multiply(1);
-  }
-  if (wave > 0) {
-#pragma unroll
-    for (int j = 0; j < NF; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) red[(((wave - 1) * NF + j) * 4 + r) * 64 + lane] = acc[j][r];
-  }
-  __syncthreads();
-  if (wave == 0) {
-#pragma unroll
-    for (int j = 0; j < NF; ++j) {
-      const int e = j * 32 + col;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float v = acc[j][r];
-        for (int w = 0; w < 3; ++w) v += red[((w * NF + j) * 4 + r) * 64 + lane];
-        const int t = half * 4 + r;
-        if (t < n_tokens && e < n_experts) {
-          logits[(long)t * n_experts + e] = v;
-          if (lds_logits) lds_logits[t * n_experts + e] = v;
-        }
-      }
-    }
-  }
-  __syncthreads();
-}
+// How a block of NW waves divides its work: MA fragments of 16 tokens; the waves split K KS ways, and NW / KS groups of
+// them own NF fragments of 16 experts each.
+template <int MA_, int NF_, int KS_, int NW_>
+struct RouterShape {
+  static constexpr int MA = MA_, NF = NF_, KS = KS_, NW = NW_, THREADS = 64 * NW_;
+  static constexpr int EXPERT_FRAGS = NW / KS * NF;            // of the block
+  static constexpr int RED = KS * EXPERT_FRAGS * MA * 4 * 64;  // floats of partial sums in LDS
+};
 
-// bf16 layers: a block takes tokens_per_block (at most 32) tokens and all experts; both operands are K-contiguous
-// rows, so lanes load MFMA fragments straight from global memory (token or expert row = lane%32, 8 k values
-// at 8*(lane/32)).  The 4 waves split K and meet in LDS.  NF = ceil(E/32) expert fragments.  The launch gives a
-// block fewer than 32 tokens when that is what it takes to have blocks for half of the CUs (the rows of the MFMA
-// that stay empty cost nothing; a token's sum runs in the same order whatever the block holds).
-template <int NF>
-__device__ __forceinline__ void router_logits_tokens(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_g,
-                                                     int n_tokens, int n_experts, int hidden,
-                                                     float* __restrict__ logits, int tokens_per_block,
-                                                     float* lds_logits) {
-  __shared__ float red[3 * NF * 16 * 64];
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, half = lane / 32, col = lane % 32;
+// bf16 operands, K-contiguous rows: lanes load 16x16x32 MFMA fragments straight from global memory (token or expert
+// row = lane % 16, 8 k values at 8 * (lane / 16)).  K is cut into 16 contiguous pieces s0..s15, each summed in
+// ascending k, and a logit is ((W0 + W1) + W2) + W3 with Wi = (s4i + s4i+1) + (s4i+2 + s4i+3).  That order is the
+// same for every block shape, so a token's logits do not depend on the batch it is part of: with KS = 16 a wave owns
+// one piece; with KS = 8 or 4 it works through two or four pieces and adds them up itself.
+//
+// What bounds it: a decode router is a chain of memory round trips, not bandwidth, so what counts is how few loads a
+// wave has to wait for one after the other.  Four waves with contiguous quarters of K took 9.6 us for one token, 8
+// experts, K = 4096 (eight dependent batches of loads), 12-14 us for 8 to 512 tokens; sixteen waves have all of
+// their loads in flight at once.  The 16x16x32 shape costs half the matrix-core time per k of the 32x32x16 one.
+// Large batches take blocks of eight waves and 32 tokens, two to a CU, so that one loads while the other routes.
+// Loads are unconditional, from clamped addresses, so that the compiler's count of outstanding loads stays exact;
+// steps past a piece's end are skipped by a wave-uniform branch around the matrix instructions only.
+//
+// tokens_per_block <= 16 MA.  logits [T, E] global out; lds_logits [tokens_per_block * E] the same values in LDS, or
+// NULL.  Ends with a block barrier.
+template <class SHAPE>
+__device__ __forceinline__ void router_logits_block(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_g,
+                                                    int n_tokens, int n_experts, int hidden, float* __restrict__ logits,
+                                                    int tokens_per_block, float* red, float* lds_logits) {
+  constexpr int MA = SHAPE::MA, NF = SHAPE::NF, KS = SHAPE::KS, EF = SHAPE::EXPERT_FRAGS;
+  constexpr int U = MA + NF <= 2 ? 4 : MA + NF <= (KS == 4 ? 4 : 5) ? 2 : 1;  // steps of 32 k per register set (128 registers)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int row = lane % 16, kblk = lane / 16;
+  const int part = wave % KS, egroup = wave / KS;
   const long t0 = (long)blockIdx.x * tokens_per_block;
-  const int kt = hidden / 16, per_wave = (kt + 3) / 4;
-  const int kb0 = min(wave * per_wave, kt), kb1 = min(kb0 + per_wave, kt);
-  const bool has_tok = col < tokens_per_block && t0 + col < n_tokens;
-  const u32x4* xp = (const u32x4*)(x + (t0 + (has_tok ? col : 0)) * hidden) + half;
-  const u32x4* wp[NF];
-  bool has_exp[NF];
+  const int kt = (hidden + 31) / 32, quarter = (kt + 3) / 4, piece = (quarter + 3) / 4;
+  // (32-bit lane offsets from wave-uniform bases: half the registers of pointers)
+  const u32x4* const x_block = (const u32x4*)(x + t0 * hidden);
+  const u32x4* const w_all = (const u32x4*)w_g;
+  uint32_t xo[MA], wo[NF];
+#pragma unroll
+  for (int m = 0; m < MA; ++m) {
+    const int t = m * 16 + row;
+    xo[m] = (uint32_t)(t0 + t < n_tokens ? t : (int)(n_tokens - 1 - t0)) * (uint32_t)(hidden / 8);
+  }
 #pragma unroll
   for (int j = 0; j < NF; ++j) {
-    has_exp[j] = j * 32 + col < n_experts;
-    wp[j] = (const u32x4*)(w_g + (long)(has_exp[j] ? j * 32 + col : 0) * hidden) + half;
+    const int e = (egroup * NF + j) * 16 + row;
+    wo[j] = (uint32_t)(e < n_experts ? e : n_experts - 1) * (uint32_t)(hidden / 8);
   }
-  f32x16_t acc[NF];
-#pragma unroll
-  for (int j = 0; j < NF; ++j) acc[j] = f32x16_t{0};
-  // two register sets of U k-tiles alternate: the loads of one are in flight while the other is multiplied
-  constexpr int U = NF == 1 ? 8 : NF == 2 ? 4 : NF == 4 ? 2 : 1;
-  u32x4 xa[2][U], wb[2][U][NF];
+  const int last_chunk = hidden / 8 - 1;  // 16-byte pieces of a row; hidden is a multiple of 16, so a step may be half full
+  u32x4 xa[2][U][MA], wb[2][U][NF];
   auto load = [&](int set, int kb) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool in_range = kb + u < kb1;
-      xa[set][u] = (in_range && has_tok) ? xp[(long)(kb + u) * 2] : u32x4{0, 0, 0, 0};
+      const int c = (kb + u) * 4 + kblk, cc = c < last_chunk ? c : last_chunk;
 #pragma unroll
-      for (int j = 0; j < NF; ++j)
-        wb[set][u][j] = (in_range && has_exp[j]) ? wp[j][(long)(kb + u) * 2] : u32x4{0, 0, 0, 0};
+      for (int m = 0; m < MA; ++m) xa[set][u][m] = x_block[xo[m] + cc];
+#pragma unroll
+      for (int j = 0; j < NF; ++j) wb[set][u][j] = w_all[wo[j] + cc];
     }
   };
-  auto multiply = [&](int set) {
+  f32x4_t acc[MA][NF], pair[MA][NF], sum[MA][NF];
+  auto multiply = [&](int set, int kb, int kb1) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) {
+      if (kb + u < kb1) {  // uniform over the wave
+        if ((kb + u) * 32 + 32 > hidden) {  // the half step at the end of K: its upper half counts nothing
 #pragma unroll
-      for (int j = 0; j < NF; ++j) acc[j] = mfma_32x32x16_bf16(xa[set][u], wb[set][u][j], acc[j]);
-  };
-  load(0, kb0);
-  for (int kb = kb0; kb < kb1; kb += 2 * U) {
-    load(1, kb + U);
-    multiply(0);
-    load(0, kb + 2 * U);
-    multiply(1);
-  }
-  if (wave > 0) {
+          for (int m = 0; m < MA; ++m) xa[set][u][m] = kblk < 2 ? xa[set][u][m] : u32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int j = 0; j < NF; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) red[(((wave - 1) * NF + j) * 16 + r) * 64 + lane] = acc[j][r];
-  }
-  __syncthreads();
-  if (wave == 0) {
-#pragma unroll
-    for (int j = 0; j < NF; ++j) {
-      const int e = j * 32 + col;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float v = acc[j][r];
-        for (int w = 0; w < 3; ++w) v += red[((w * NF + j) * 16 + r) * 64 + lane];
-        const int row = (r / 4) * 8 + half * 4 + (r % 4);
-        const long t = t0 + row;
-        if (row < tokens_per_block && t < n_tokens && e < n_experts) {
-          logits[t * n_experts + e] = v;
-          if (lds_logits) lds_logits[row * n_experts + e] = v;
+          for (int j = 0; j < NF; ++j) wb[set][u][j] = kblk < 2 ? wb[set][u][j] : u32x4{0, 0, 0, 0};
         }
+#pragma unroll
+        for (int m = 0; m < MA; ++m)
+#pragma unroll
+          for (int j = 0; j < NF; ++j) acc[m][j] = mfma_16x16x32_bf16(xa[set][u][m], wb[set][u][j], acc[m][j]);
       }
     }
+  };
+#pragma unroll 1
+  for (int q = 0; q < 16 / KS; ++q) {
+    const int s = part * (16 / KS) + q;  // piece
+    const int end = min((s / 4 + 1) * quarter, kt);
+    const int kb0 = min((s / 4) * quarter + (s % 4) * piece, end), kb1 = min(kb0 + piece, end);
+#pragma unroll
+    for (int m = 0; m < MA; ++m)
+#pragma unroll
+      for (int j = 0; j < NF; ++j) acc[m][j] = f32x4_t{0, 0, 0, 0};
+    if (kb0 < kb1) {
+      load(0, kb0);
+      for (int kb = kb0; kb < kb1; kb += 2 * U) {
+        load(1, kb + U);
+        multiply(0, kb, kb1);
+        load(0, kb + 2 * U);
+        multiply(1, kb + U, kb1);
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < MA; ++m)
+#pragma unroll
+      for (int j = 0; j < NF; ++j) {
+        pair[m][j] = q % 2 == 0 ? acc[m][j] : pair[m][j] + acc[m][j];
+        if (q <= 1) sum[m][j] = pair[m][j];
+        else if (q == 3) sum[m][j] = sum[m][j] + pair[m][j];
+      }
   }
-  __syncthreads();  // the LDS copy of the logits is complete
+  // partial sums [part][expert fragment][token fragment][register][lane]
+#pragma unroll
+  for (int j = 0; j < NF; ++j)
+#pragma unroll
+    for (int m = 0; m < MA; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[(((part * EF + egroup * NF + j) * MA + m) * 4 + r) * 64 + lane] = sum[m][j][r];
+  __syncthreads();
+  for (int i = threadIdx.x; i < EF * MA * 4 * 64; i += SHAPE::THREADS) {
+    // register r of lane l is token 4 (l / 16) + r, expert l % 16 of the fragment
+    const int l = i % 64, r = i / 64 % 4, m = i / 256 % MA, f = i / (256 * MA);
+    const int tok = m * 16 + 4 * (l / 16) + r, e = f * 16 + l % 16;
+    float v = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      float q[KS / 4];
+#pragma unroll
+      for (int p = 0; p < KS / 4; ++p) q[p] = red[(w * (KS / 4) + p) * (EF * MA * 256) + i];
+      const float quarter_sum = KS == 16 ? (q[0] + q[1 % (KS / 4)]) + (q[2 % (KS / 4)] + q[3 % (KS / 4)]) : KS == 8 ? q[0] + q[1 % (KS / 4)] : q[0];
+      v = w == 0 ? quarter_sum : v + quarter_sum;
+    }
+    if (tok < tokens_per_block && t0 + tok < n_tokens && e < n_experts) {
+      logits[(t0 + tok) * n_experts + e] = v;
+      if (lds_logits) lds_logits[tok * n_experts + e] = v;
+    }
+  }
+  __syncthreads();
 }
+
+// Tokens per block: 16, or fewer while the grid would leave more than half of the CUs without a block; beyond 4096 tokens
+// (a block per CU) 32, of up to 64 experts.
+static inline int router_tokens_per_block(int n_tokens, int n_experts) {
+  if (n_tokens <= ROUTER_SMALL_T) return 16;
+  if (n_tokens > 4096 && n_experts <= 64) return 32;
+  int tpb = 16;
+  while (tpb > 4 && (n_tokens + tpb - 1) / tpb < 128) tpb /= 2;
+  return tpb;
+}
+// CALL(lanes per token when routing, values per lane, the four RouterShape parameters) for a number of experts, blocks of
+// up to 16 tokens and larger ones.
+#define HMOE_ROUTER_SHAPES_16(E, CALL)                   \
+  do {                                                   \
+    if ((E) <= 8) { CALL(8, 1, 1, 1, 16, 16); }          \
+    else if ((E) <= 16) { CALL(16, 1, 1, 1, 16, 16); }   \
+    else if ((E) <= 32) { CALL(32, 1, 1, 2, 16, 16); }   \
+    else if ((E) <= 64) { CALL(64, 1, 1, 4, 16, 16); }   \
+    else if ((E) <= 128) { CALL(64, 2, 1, 2, 4, 16); }   \
+    else { CALL(64, 4, 1, 4, 4, 16); }                   \
+  } while (0)
+#define HMOE_ROUTER_SHAPES(E, TPB, CALL)                 \
+  do {                                                   \
+    if ((TPB) <= 16) { HMOE_ROUTER_SHAPES_16(E, CALL); } \
+    else if ((E) <= 8) { CALL(8, 1, 2, 1, 8, 8); }       \
+    else if ((E) <= 16) { CALL(16, 1, 2, 1, 8, 8); }     \
+    else if ((E) <= 32) { CALL(32, 1, 2, 2, 8, 8); }     \
+    else { CALL(64, 1, 2, 4, 8, 8); }                    \
+  } while (0)
 
 }  // namespace hmoe

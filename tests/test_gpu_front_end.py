@@ -1,0 +1,98 @@
+"""Front end at the sizes where its dispatch changes: block shapes of the router, ways of the permutation."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from hmoe_testlib import to_device
+from oracle import moe_oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def hm():
+    import paper_2504_05897_amd as module
+    return module
+
+
+@pytest.mark.parametrize("T,E,K", [(16384, 5, 1), (16385, 5, 1), (8192, 256, 2), (5462, 64, 3), (262144, 3, 1), (262145, 3, 1),
+                                   (87383, 130, 3)])
+def test_permute_at_the_edges_of_its_ways(hm, T, E, K):
+    """16 and 256 chunks of 1024 assignments are the last of the one- and two-launch ways."""
+    print("permute edges", T, E, K, flush=True)
+    rng = np.random.default_rng(T + E)
+    idx = np.minimum(rng.geometric(0.2, (T, K)) - 1, E - 1).astype(np.int32)
+    d = hm.make_desc(64, 64, E, K, E, hm.HMOE_BF16)
+    A = T * K
+    offs = torch.full((E + 1,), -7, dtype=torch.int32, device=DEV)
+    perm, inv = (torch.full((A,), -7, dtype=torch.int32, device=DEV) for _ in range(2))
+    counts = torch.zeros(E, dtype=torch.int32, pin_memory=True)
+    ws_bytes = hm.hmoe_permute_workspace_bytes(d, T)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+    hm.hmoe_permute(d, to_device(idx), T, None, None, offs, perm, inv, counts, ws, ws_bytes)
+    torch.cuda.synchronize()
+    ro, rp, ri = orc.permute(idx, E)
+    assert np.array_equal(offs.cpu().numpy(), ro) and np.array_equal(counts.numpy(), np.diff(ro))
+    assert np.array_equal(perm.cpu().numpy(), rp) and np.array_equal(inv.cpu().numpy(), ri)
+
+
+@pytest.mark.parametrize("T,E,K,H", [(16, 8, 2, 48), (17, 8, 2, 48), (16, 64, 6, 2048), (16, 256, 32, 80), (64, 100, 8, 48), (4096, 16, 2, 64),
+                                     (4097, 8, 2, 48), (4097, 33, 4, 80), (8192, 64, 6, 48), (8193, 64, 6, 48), (8193, 100, 6, 64),
+                                     (8193, 200, 2, 16)])
+def test_router_block_shapes(hm, T, E, K, H):
+    """Logits within fp32 summation error (|error| <= 2 H 2^-24 sum |x w|), the same bits for a token whatever its batch,
+    and the fused call's integers equal to the oracle's for the logits it wrote."""
+    print("router block shapes", T, E, K, H, flush=True)
+    rng = np.random.default_rng(T + E + H)
+    x = wl.store(rng.standard_normal((T, H)).astype(np.float32), wl.BF16)
+    wg = wl.store(rng.standard_normal((E, H)).astype(np.float32) * 0.05, wl.BF16)
+    d = hm.make_desc(H, 64, E, K, E, hm.HMOE_BF16)
+    xd, wd = to_device(x), to_device(wg)
+    lg = torch.full((T, E), 9.0, dtype=torch.float32, device=DEV)
+    idx = torch.full((T, K), -5, dtype=torch.int32, device=DEV)
+    w = torch.zeros(T, K, dtype=torch.float32, device=DEV)
+    offs = torch.full((E + 1,), -7, dtype=torch.int32, device=DEV)
+    perm, inv = (torch.full((T * K,), -7, dtype=torch.int32, device=DEV) for _ in range(2))
+    ws_bytes = hm.hmoe_permute_workspace_bytes(d, T)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+    hm.hmoe_router_route_permute(d, xd, wd, T, lg, idx, w, offs, perm, inv, None, ws, ws_bytes)
+    alone, single = torch.empty_like(lg), torch.empty(1, E, dtype=torch.float32, device=DEV)
+    hm.hmoe_router_logits(d, xd, wd, T, alone)
+    hm.hmoe_router_logits(d, xd[T - 1:].contiguous(), wd, 1, single)
+    torch.cuda.synchronize()
+    got = lg.cpu().numpy()
+    assert np.array_equal(got, alone.cpu().numpy()) and np.array_equal(got[T - 1:], single.cpu().numpy())
+    xf, wf = wl.as_f64(x), wl.as_f64(wg)
+    assert (np.abs(got - xf @ wf.T) <= 2 * H * 2.0 ** -24 * (np.abs(xf) @ np.abs(wf).T)).all()
+    ridx, rw = orc.route(got, K)
+    ro, rp, ri = orc.permute(ridx, E)
+    assert np.array_equal(idx.cpu().numpy(), ridx) and np.abs(w.cpu().numpy() - rw).max() < 1e-6
+    assert np.array_equal(offs.cpu().numpy(), ro) and np.array_equal(perm.cpu().numpy(), rp) and np.array_equal(inv.cpu().numpy(), ri)
+
+
+@pytest.mark.parametrize("T,E,K", [(1, 8, 8), (21, 64, 8), (64, 16, 3), (5, 30, 30), (40, 100, 9), (33, 256, 31)])
+def test_equal_logits_go_to_the_smaller_id(hm, T, E, K):
+    """Few distinct values (both zeros, both signs among them), so that most choices are ties within and across lanes."""
+    print("ties", T, E, K, flush=True)
+    rng = np.random.default_rng(T * E + K)
+    lg = rng.choice(np.array([0.0, -0.0, 1.5, -2.0, 1e-38], np.float32), (T, E)).astype(np.float32)
+    d = hm.make_desc(64, 64, E, K, E, hm.HMOE_BF16)
+    ridx, rw = orc.route(lg, K)
+    ro, rp, ri = orc.permute(ridx, E)
+    for fused in (False, True):
+        idx = torch.full((T, K), -5, dtype=torch.int32, device=DEV)
+        w = torch.zeros(T, K, dtype=torch.float32, device=DEV)
+        offs = torch.full((E + 1,), -7, dtype=torch.int32, device=DEV)
+        perm, inv = (torch.full((T * K,), -7, dtype=torch.int32, device=DEV) for _ in range(2))
+        ws_bytes = hm.hmoe_permute_workspace_bytes(d, T)
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+        if fused:
+            hm.hmoe_route_permute(d, to_device(lg), T, idx, w, offs, perm, inv, None, ws, ws_bytes)
+        else:
+            hm.hmoe_route(d, to_device(lg), T, idx, w)
+            hm.hmoe_permute(d, idx, T, None, None, offs, perm, inv, None, ws, ws_bytes)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy(), ridx) and np.abs(w.cpu().numpy() - rw).max() < 1e-6
+        assert np.array_equal(offs.cpu().numpy(), ro) and np.array_equal(perm.cpu().numpy(), rp) and np.array_equal(inv.cpu().numpy(), ri)
