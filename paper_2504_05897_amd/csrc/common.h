@@ -154,6 +154,8 @@ struct CombineArgs {
   int32_t n_tokens = 0;
 };
 int launch_ffn_reference(const FfnArgs& a);
+bool ffn_f32_takes(const hmoe_layer_desc& d, int n_rows);
+int launch_ffn_f32(const FfnArgs& a);
 int launch_ffn_skinny(const FfnArgs& a, const FfnArgs* dense = nullptr, const CombineArgs* combine = nullptr);
 int launch_ffn_tiled(const FfnArgs& a);
 int launch_ffn_skinny_w4(const FfnArgs& a);

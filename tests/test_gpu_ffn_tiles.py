@@ -1,0 +1,60 @@
+"""Tile heights and ragged edges of the fp32 matrix kernels, against the oracle in 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from oracle import moe_oracle as orc
+from hmoe_testlib import desc_of, max_rel_err, to_device, to_host_f32
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def grouped_ffn(hm, d, experts, x_bits, offsets, path):
+    A = int(offsets[-1])
+    layer = hm.MoELayer(d, experts, (), None, max_tokens=A)
+    o = torch.full((A, d.hidden), float("nan"), dtype=layer.dt, device=DEV)
+    ws_bytes = hm.hmoe_ffn_workspace_bytes(d, A)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+    hm.hmoe_expert_ffn_grouped(d, layer.cache, to_device(x_bits), to_device(offsets), A, None, o, ws, ws_bytes, path)
+    torch.cuda.synchronize()
+    got = to_host_f32(o)
+    layer.close()
+    return got
+
+
+def case(dtype, hidden, ffn, counts):
+    shape = wl.small_shape(dtype=dtype, hidden=hidden, ffn=ffn, n_experts=len(counts), top_k=2)
+    lay = wl.make_layer(shape, hidden + ffn, n_tokens=1)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    x = wl.store(np.random.default_rng(7).standard_normal((int(offsets[-1]), hidden)).astype(np.float32), dtype)
+    return shape, lay, offsets, x
+
+
+def reference(x, offsets, experts, hidden, to_f64):
+    ref = np.zeros((int(offsets[-1]), hidden))
+    for e, (lo, hi) in enumerate(zip(offsets[:-1], offsets[1:])):
+        if hi > lo:
+            ref[lo:hi] = orc.expert_ffn(wl.as_f64(x[lo:hi]), *(to_f64(m) for m in experts[e]))
+    return ref
+
+
+# one 16-row fragment per tile and two; K of one and several rounds of 256 with remainders; widths that are no multiple of 16
+@pytest.mark.parametrize("hidden,ffn,counts", [
+    (256, 512, [1, 0, 16, 5]), (4, 8, [3, 1]), (260, 36, [17, 2, 0, 1]), (516, 772, [2, 9]),
+    (256, 512, [31, 0, 33, 64, 1]), (100, 44, [40, 15]), (1028, 20, [65, 32]),
+])
+def test_ffn_f32_tiles(hm, hidden, ffn, counts):
+    shape, lay, offsets, x = case(wl.F32, hidden, ffn, counts)
+    d = desc_of(hm, shape, n_slots=len(counts))
+    got = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_AUTO)
+    # sums of K / 64 products each in fp32, then 64 bits: at most 24 roundings of 2^-24 per GEMM at these sizes, and a
+    # handful in silu: 2e-6 of the largest value leaves the margin of cancellation
+    assert max_rel_err(got, reference(x, offsets, lay.experts, hidden, wl.as_f64)) < 4e-6
+
+
+@pytest.fixture(scope="module")
+def hm():
+    import paper_2504_05897_amd as hm
+    return hm
