@@ -1,11 +1,12 @@
-"""Tile heights and ragged edges of the fp32 matrix kernels, against the oracle in 64 bits."""
+"""Tile heights and ragged edges of the fp32 matrix kernels and the 4-bit prefill kernel, against the oracle in 64 bits."""
 import numpy as np
 import pytest
 import torch
 
 import workloads as wl
 from oracle import moe_oracle as orc
-from hmoe_testlib import desc_of, max_rel_err, to_device, to_host_f32
+from oracle import w4_oracle as w4
+from hmoe_testlib import TOL, desc_of, max_rel_err, to_device, to_host_f32
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -52,6 +53,23 @@ def test_ffn_f32_tiles(hm, hidden, ffn, counts):
     # sums of K / 64 products each in fp32, then 64 bits: at most 24 roundings of 2^-24 per GEMM at these sizes, and a
     # handful in silu: 2e-6 of the largest value leaves the margin of cancellation
     assert max_rel_err(got, reference(x, offsets, lay.experts, hidden, wl.as_f64)) < 4e-6
+
+
+# every height of one tile (1 to 6 fragments), experts of several tiles with uneven heights, ragged last fragments, a
+# column tile that is not full, and one, two, three and more scale groups (the ring holds three).  The last three have more
+# than 256 tiles in one projection, which then takes the blocks of one set of waves; fewer take those of two sets.
+@pytest.mark.parametrize("hidden,ffn,counts", [
+    (256, 128, [1, 16, 17, 33, 49, 80, 81, 96]), (128, 256, [97, 0, 112, 113]), (384, 640, [193, 96, 290]),
+    (512, 384, [64, 65]), (1152, 128, [95, 3]),
+    (384, 16768, [100]), (4096, 128, [97, 33, 16, 50, 81, 1, 2, 64, 96]), (4096, 640, [96, 34, 17, 51, 80, 2, 3, 64, 65]),
+])
+def test_ffn_w4_tile_heights(hm, hidden, ffn, counts):
+    shape, lay, offsets, x = case(wl.BF16, hidden, ffn, counts)
+    E = len(counts)
+    d = hm.make_desc(hidden, ffn, E, 2 if E > 1 else 1, E, hm.HMOE_BF16_W4)
+    got = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_TILED)
+    ref = reference(x, offsets, lay.experts, hidden, lambda m: w4.dequantize_w4(*w4.quantize_w4(wl.as_f32(m))))
+    assert max_rel_err(got, ref) < TOL[wl.BF16]
 
 
 @pytest.fixture(scope="module")
