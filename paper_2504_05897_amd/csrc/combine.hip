@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void router_logits_f32_kernel(const float* __r
 
 // bf16 layers: see router_body.h
 template <class SHAPE>
-__global__ __launch_bounds__(SHAPE::THREADS, SHAPE::NW == 8 ? 4 : 1) void router_logits_bf16_kernel(const bf16_t* __restrict__ x,
+__global__ __launch_bounds__(SHAPE::THREADS, SHAPE::WAVES_PER_SIMD) void router_logits_bf16_kernel(const bf16_t* __restrict__ x,
                                                                             const bf16_t* __restrict__ w_g, int n_tokens,
                                                                             int n_experts, int hidden,
                                                                             float* __restrict__ logits, int tokens_per_block) {
@@ -131,7 +131,7 @@ extern "C" int32_t hmoe_router_logits(const hmoe_layer_desc* desc, const void* x
   if (desc->dtype != HMOE_F32) {
     if (H % 16 != 0) return HMOE_ERR_UNSUPPORTED;
     if (!aligned16(x) || !aligned16(w_g)) return HMOE_ERR_INVALID_ARG;
-    const int tpb = router_tokens_per_block(T, E);
+    const int tpb = router_tokens_per_block(T);
     const dim3 grid((unsigned)((T + tpb - 1) / tpb));
 #define HMOE_LAUNCH_LOGITS(G, VPL, MA, NF, KS, NW)                                                                 \
   hipLaunchKernelGGL((router_logits_bf16_kernel<RouterShape<MA, NF, KS, NW>>), grid, dim3(64 * NW), 0, s, (const bf16_t*)x, \

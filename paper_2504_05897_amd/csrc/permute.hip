@@ -359,7 +359,7 @@ __global__ __launch_bounds__(PR_THREADS) void front_small_kernel(const bf16_t* _
 
 // ... of more: the permutation, which needs every token's choice, stays a launch of its own.
 template <int G, int VPL, class SHAPE>
-__global__ __launch_bounds__(SHAPE::THREADS, SHAPE::NW == 8 ? 4 : 1) void front_tokens_kernel(const bf16_t* __restrict__ x,
+__global__ __launch_bounds__(SHAPE::THREADS, SHAPE::WAVES_PER_SIMD) void front_tokens_kernel(const bf16_t* __restrict__ x,
                                                                       const bf16_t* __restrict__ w_g, int hidden,
                                                                       float* __restrict__ logits, int n_tokens, int n_experts,
                                                                       int top_k, int tokens_per_block, int32_t* topk_idx,
@@ -549,7 +549,7 @@ extern "C" int32_t hmoe_router_route_permute(const hmoe_layer_desc* desc, const 
       topk_w && aligned16(x) && aligned16(w_g)) {
     // logits and routing in one launch, then the permutation
     const int E = desc->n_experts, K = desc->top_k;
-    const int tpb = router_tokens_per_block(T, E);
+    const int tpb = router_tokens_per_block(T);
     const dim3 grid((unsigned)((T + tpb - 1) / tpb));
 #define HMOE_LAUNCH_FRONT_TOKENS(G, VPL, MA, NF, KS, NW)                                                                    \
   hipLaunchKernelGGL((front_tokens_kernel<G, VPL, RouterShape<MA, NF, KS, NW>>), grid, dim3(64 * NW), 0, (hipStream_t)stream, \

@@ -40,7 +40,10 @@ def test_permute_at_the_edges_of_its_ways(hm, T, E, K):
 
 @pytest.mark.parametrize("T,E,K,H", [(16, 8, 2, 48), (17, 8, 2, 48), (16, 64, 6, 2048), (16, 256, 32, 80), (64, 100, 8, 48), (4096, 16, 2, 64),
                                      (4097, 8, 2, 48), (4097, 33, 4, 80), (8192, 64, 6, 48), (8193, 64, 6, 48), (8193, 100, 6, 64),
-                                     (8193, 200, 2, 16)])
+                                     (8193, 200, 2, 16),
+                                     # pieces of K with a remainder in every shape of the block, and pieces that are empty
+                                     (20, 12, 2, 7184), (33, 30, 4, 2080), (5, 64, 8, 1104), (9, 96, 8, 1536), (20, 256, 8, 2064),
+                                     (4097, 64, 6, 1104), (4097, 128, 4, 1104), (4100, 256, 8, 592)])
 def test_router_block_shapes(hm, T, E, K, H):
     """Logits within fp32 summation error (|error| <= 2 H 2^-24 sum |x w|), the same bits for a token whatever its batch,
     and the fused call's integers equal to the oracle's for the logits it wrote."""
