@@ -136,7 +136,8 @@ extern "C" int32_t hmoe_router_logits(const hmoe_layer_desc* desc, const void* x
 #define HMOE_LAUNCH_LOGITS(G, VPL, MA, NF, KS, NW)                                                                 \
   hipLaunchKernelGGL((router_logits_bf16_kernel<RouterShape<MA, NF, KS, NW>>), grid, dim3(64 * NW), 0, s, (const bf16_t*)x, \
                      (const bf16_t*)w_g, T, E, H, logits, tpb)
-    HMOE_ROUTER_SHAPES(E, tpb, HMOE_LAUNCH_LOGITS);
+    if (T <= ROUTER_SMALL_T) HMOE_ROUTER_SHAPES_ONE_BLOCK(E, HMOE_LAUNCH_LOGITS);
+    else HMOE_ROUTER_SHAPES_MANY(E, tpb, HMOE_LAUNCH_LOGITS);
 #undef HMOE_LAUNCH_LOGITS
   } else {
     const long pairs = (long)T * E;

@@ -554,7 +554,7 @@ extern "C" int32_t hmoe_router_route_permute(const hmoe_layer_desc* desc, const 
 #define HMOE_LAUNCH_FRONT_TOKENS(G, VPL, MA, NF, KS, NW)                                                                    \
   hipLaunchKernelGGL((front_tokens_kernel<G, VPL, RouterShape<MA, NF, KS, NW>>), grid, dim3(64 * NW), 0, (hipStream_t)stream, \
                      (const bf16_t*)x, (const bf16_t*)w_g, desc->hidden, logits, (int)T, E, K, tpb, topk_idx, topk_w)
-    HMOE_ROUTER_SHAPES(E, tpb, HMOE_LAUNCH_FRONT_TOKENS);
+    HMOE_ROUTER_SHAPES_MANY(E, tpb, HMOE_LAUNCH_FRONT_TOKENS);
 #undef HMOE_LAUNCH_FRONT_TOKENS
     HMOE_HIP(hipGetLastError());
     return hmoe_permute(desc, topk_idx, T, nullptr, nullptr, expert_offsets, perm, inv_perm, h_counts_pinned, workspace,
@@ -580,7 +580,7 @@ extern "C" int32_t hmoe_router_route_permute(const hmoe_layer_desc* desc, const 
   hipLaunchKernelGGL((front_small_kernel<G, VPL, RouterShape<MA, NF, KS, NW>>), dim3(1), dim3(PR_THREADS), 0, s, (const bf16_t*)x, \
                      (const bf16_t*)w_g, desc->hidden, logits, (int)T, E, K, key_bits, topk_idx, topk_w, expert_offsets,   \
                      counts_dev, perm, inv_perm)
-  HMOE_ROUTER_SHAPES_16(E, HMOE_LAUNCH_FRONT);
+  HMOE_ROUTER_SHAPES_ONE_BLOCK(E, HMOE_LAUNCH_FRONT);
 #undef HMOE_LAUNCH_FRONT
   HMOE_HIP(hipGetLastError());
   if (h_counts_pinned)

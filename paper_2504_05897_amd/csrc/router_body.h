@@ -39,8 +39,9 @@ struct RouterShape {
 // branch): with a second register set loaded ahead from clamped addresses, a piece of four steps cost twelve steps of
 // loads: 16 experts, K = 2048, 12.1 us for 17 to 2048 tokens, now 5.8 (four waves: 6.7).  Of more than 64 experts every
 // wave takes as many as its registers hold, so that x is read once or twice and not by four groups of waves: 128 experts,
-// K = 4096, 17 to 2048 tokens 54 -> 34 us (four waves: 35); 16384 tokens 214 -> 79 us (92).  Beyond 4096 tokens, a
-// block per CU, blocks of 32 tokens and eight waves halve the reads of w_g.
+// K = 4096, 17 to 2048 tokens 54 -> 34 us (four waves: 35); 16384 tokens 214 -> 79 us (92).  Blocks of up to 32 tokens
+// halve the reads of w_g of large batches.
+//
 // tokens_per_block <= 16 MA.  logits [T, E] global out; lds_logits [tokens_per_block * E] the same values in LDS, or
 // NULL.  Ends with a block barrier.
 template <class SHAPE>
@@ -155,18 +156,22 @@ __device__ __forceinline__ void router_logits_block(const bf16_t* __restrict__ x
   }
 }
 
-// Tokens per block: 16, or fewer while the grid would leave more than half of the CUs without a block; beyond 4096 tokens
-// (a block per CU) 32.
+// Tokens per block: 16, or fewer while the grid would leave more than half of the CUs without a block; beyond 2048 tokens
+// up to 32, so that the grid stays at half of the CUs until they are full (the other half is left to what runs beside it).
 static inline int router_tokens_per_block(int n_tokens) {
   if (n_tokens <= ROUTER_SMALL_T) return 16;
-  if (n_tokens > 4096) return 32;
+  if (n_tokens > 2048) return n_tokens < 4096 ? (n_tokens + 127) / 128 : 32;
   int tpb = 16;
   while (tpb > 4 && (n_tokens + tpb - 1) / tpb < 128) tpb /= 2;
   return tpb;
 }
-// CALL(lanes per token when routing, values per lane, the four RouterShape parameters) for a number of experts, blocks of
-// up to 16 tokens and larger ones.
-#define HMOE_ROUTER_SHAPES_16(E, CALL)                   \
+// CALL(lanes per token when routing, values per lane, the four RouterShape parameters) for a number of experts: batches
+// of one block, and larger ones.
+// The one block has the GPU to itself and takes sixteen waves.  The blocks of a larger batch run beside the shared
+// experts' FFN, whose gate/up launch they would keep off half of the CUs for their whole time: eight waves of up to 116
+// registers leave room for a block of it (of up to 128 experts).  Alone both take the same time (64 experts, K = 2048, 2048 tokens 14.2 us); the layer of 64
+// experts of 2048 x 1408, top 6, 1024 tokens 295 -> 288 us, 4096 tokens with half as many blocks 585 -> 575 us.
+#define HMOE_ROUTER_SHAPES_ONE_BLOCK(E, CALL)            \
   do {                                                   \
     if ((E) <= 8) { CALL(8, 1, 1, 1, 16, 16); }          \
     else if ((E) <= 16) { CALL(16, 1, 1, 1, 16, 16); }   \
@@ -175,15 +180,23 @@ static inline int router_tokens_per_block(int n_tokens) {
     else if ((E) <= 128) { CALL(64, 2, 1, 8, 16, 16); }  \
     else { CALL(64, 4, 1, 8, 8, 16); }                   \
   } while (0)
-#define HMOE_ROUTER_SHAPES(E, TPB, CALL)                 \
+#define HMOE_ROUTER_SHAPES_MANY(E, TPB, CALL)            \
   do {                                                   \
-    if ((TPB) <= 16) { HMOE_ROUTER_SHAPES_16(E, CALL); } \
-    else if ((E) <= 8) { CALL(8, 1, 2, 1, 8, 8); }       \
-    else if ((E) <= 16) { CALL(16, 1, 2, 1, 8, 8); }     \
-    else if ((E) <= 32) { CALL(32, 1, 2, 2, 8, 8); }     \
-    else if ((E) <= 64) { CALL(64, 1, 2, 4, 8, 8); }     \
-    else if ((E) <= 128) { CALL(64, 2, 2, 8, 8, 8); }    \
-    else { CALL(64, 4, 2, 8, 4, 8); }                    \
+    if ((TPB) <= 16) {                                   \
+      if ((E) <= 8) { CALL(8, 1, 1, 1, 8, 8); }          \
+      else if ((E) <= 16) { CALL(16, 1, 1, 1, 8, 8); }   \
+      else if ((E) <= 32) { CALL(32, 1, 1, 2, 8, 8); }   \
+      else if ((E) <= 64) { CALL(64, 1, 1, 4, 8, 8); }   \
+      else if ((E) <= 128) { CALL(64, 2, 1, 8, 8, 8); }  \
+      else { CALL(64, 4, 1, 8, 8, 16); }                 \
+    } else {                                             \
+      if ((E) <= 8) { CALL(8, 1, 2, 1, 8, 8); }          \
+      else if ((E) <= 16) { CALL(16, 1, 2, 1, 8, 8); }   \
+      else if ((E) <= 32) { CALL(32, 1, 2, 2, 8, 8); }   \
+      else if ((E) <= 64) { CALL(64, 1, 2, 4, 8, 8); }   \
+      else if ((E) <= 128) { CALL(64, 2, 2, 8, 8, 8); }  \
+      else { CALL(64, 4, 2, 8, 4, 8); }                  \
+    }                                                    \
   } while (0)
 
 }  // namespace hmoe

@@ -43,6 +43,7 @@ def test_permute_at_the_edges_of_its_ways(hm, T, E, K):
                                      (8193, 200, 2, 16),
                                      # pieces of K with a remainder in every shape of the block, and pieces that are empty
                                      (20, 12, 2, 7184), (33, 30, 4, 2080), (5, 64, 8, 1104), (9, 96, 8, 1536), (20, 256, 8, 2064),
+                                     (2049, 64, 6, 1104), (2100, 128, 4, 592), (3000, 33, 4, 80), (2200, 256, 8, 80), (4095, 12, 2, 48),
                                      (4097, 64, 6, 1104), (4097, 128, 4, 1104), (4100, 256, 8, 592)])
 def test_router_block_shapes(hm, T, E, K, H):
     """Logits within fp32 summation error (|error| <= 2 H 2^-24 sum |x w|), the same bits for a token whatever its batch,
