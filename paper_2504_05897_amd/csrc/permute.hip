@@ -6,12 +6,15 @@
 // equal key with ballots, and waves are ordered by per-wave LDS counts.  What a block needs besides its own
 // assignments is, per expert, how many lie in front of them and how many there are in all:
 //   A <= 1024 (every decode shape)  one block of 16 waves, nothing lies elsewhere
-//   A <= 16384                      blocks of 16 waves, each counts all A keys itself (64 KB from L2 at most): one launch
-//   A <= 262144                     a histogram launch over chunks of 1024 first; every block adds up the counts
+//   A <= 4096                       blocks of 8 waves, each counts all A keys itself (16 KB from L2 at most): one launch
+//   A <= 262144                     a histogram launch over chunks of 1024 first; every block of 4 waves adds up the counts
 //   beyond                          histogram, one-block scan, rank
-// The launches are latency, not bandwidth (a few KB each), so what counts is how many follow one another.  T = 1003,
-// K = 6, 64 experts: histogram, scan and rank took 5.6 + 6.0 + 6.8 us, the one launch 8.3 us; T = 16384, next to the shared
-// experts' FFN: 6.4 + 31 + 9.9 us, now 6.3 + 20 us.
+// The launches are latency, not bandwidth (a few KB each), so what counts is how many follow one another, and that no
+// block counts many keys that are alike: lanes of a wave that add to one LDS counter take turns (about 110 cycles for 64
+// of them, one wave at a time).  With blocks of 16 waves counting up to 16384 keys themselves, 16384 rows of one expert took
+// 20 us, of 8 experts that all rows name the same two of 12 us.  Now (histogram, scan and rank in three launches before
+// either): one expert, 4096 rows 4.5 us (8.1), 16384 rows 6.7 (8.9); 64 experts, top 6, 2288 assignments 4.3 (9.0), 4096
+// 4.9 (9.2), 16384 7.1 (9.9), 98304 7.9 (17.4).
 // The last two have blocks of four waves and 6 KB of LDS: batches of that size run next to prefill FFN blocks (of the
 // shared experts) that leave a CU 56 registers per lane and 9 KB of LDS, and what does not fit beside them waits for
 // their end (16-wave blocks there: the 16384-token layer 1.3 % slower).
@@ -25,8 +28,8 @@ namespace hmoe {
 
 constexpr int PB_THREADS = 256;              // histogram, scan, decode front end's routing
 constexpr int PB_CHUNK = 1024;               // assignments per block
-constexpr int PR_THREADS = PB_CHUNK;         // one-launch permutation: one assignment of a chunk per thread
-constexpr int PR_SELF_COUNT_CHUNKS = 16;     // up to here every rank block counts all keys itself
+constexpr int PR_THREADS = PB_CHUNK;         // one-block permutation: one assignment per thread
+constexpr int PR_SELF_COUNT_CHUNKS = 4;      // up to here every rank block counts all keys itself
 constexpr int PR_SELF_SCAN_CHUNKS = 256;     // up to here every rank block adds up the histogram's counts itself
 
 __device__ __forceinline__ int clamp_key(int key, int n_experts) {
@@ -184,17 +187,24 @@ __device__ __forceinline__ void permute_rank_body(const int32_t* topk_idx, int n
   __syncthreads();
   if (valid && (same >> lane) >> 1 == 0) wave_base[wave][key] = __popcll(same);  // highest lane of the group
   if constexpr (SRC == RANK_COUNT_ALL) {
-    static_assert(PER_CHUNK == 1, "");
-    const int n_chunks = (n_assign + PB_CHUNK - 1) / PB_CHUNK;
-    int others[PR_SELF_COUNT_CHUNKS];
+    constexpr int MOST = PR_SELF_COUNT_CHUNKS * PER_CHUNK;  // blocks
+    int others[MOST];
 #pragma unroll
-    for (int c = 0; c < PR_SELF_COUNT_CHUNKS; ++c) {
-      const long i = (long)c * PB_CHUNK + threadIdx.x;
-      others[c] = c < n_chunks && c != chunk && i < n_assign ? clamp_key(topk_idx[i], n_experts) : -1;
+    for (int b = 0; b < MOST; ++b) {
+      const long i = (long)b * THREADS + threadIdx.x;
+      others[b] = b != block && i < n_assign ? clamp_key(topk_idx[i], n_experts) : -1;
     }
 #pragma unroll
-    for (int c = 0; c < PR_SELF_COUNT_CHUNKS; ++c)
-      if (others[c] >= 0) atomicAdd(&outside[c < chunk ? 0 : 1][others[c]], 1);
+    for (int b = 0; b < MOST; ++b) {
+      // the lanes that hold the key of the first one are counted by that one alone: a popular expert, or one of few
+      const uint64_t in = __ballot(others[b] >= 0);
+      if (!in) continue;  // uniform over the wave
+      const int key0 = __builtin_amdgcn_readlane(others[b], __ffsll((long long)in) - 1);
+      const uint64_t alike = __ballot(others[b] == key0);
+      const bool counts_alike = lane == __ffsll((long long)alike) - 1;
+      if (others[b] >= 0 && (others[b] != key0 || counts_alike))
+        atomicAdd(&outside[b < block ? 0 : 1][others[b]], counts_alike ? __popcll(alike) : 1);
+    }
   }
   if constexpr (SRC == RANK_ADD_UP || SRC == RANK_BASES) {
     // the rest of the block's own chunk
@@ -420,7 +430,7 @@ static int32_t permute_with_workspace(const hmoe_layer_desc* desc, const int32_t
   if (nblk <= 1) {
     HMOE_LAUNCH_RANK(RANK_SINGLE, 16, nullptr, expert_offsets, counts_dev);
   } else if (nblk <= PR_SELF_COUNT_CHUNKS) {
-    HMOE_LAUNCH_RANK(RANK_COUNT_ALL, 16, nullptr, expert_offsets, counts_dev);
+    HMOE_LAUNCH_RANK(RANK_COUNT_ALL, 8, nullptr, expert_offsets, counts_dev);
   } else {
     hipLaunchKernelGGL(permute_hist_kernel, dim3(nblk), dim3(PB_THREADS), 0, s, topk_idx, (int)A, E, block_counts);
     if (nblk <= PR_SELF_SCAN_CHUNKS) {
@@ -493,7 +503,7 @@ extern "C" int32_t hmoe_permute_static(const hmoe_layer_desc* desc, const int32_
   rc = static_scratch(&ws);
   if (rc != HMOE_OK) return rc;
   // Nothing in the scratch memory has to start at zero: the histogram kernel writes every per-block count before
-  // the scan reads it, and the row of per-expert totals is written in full by the scan (or the one-block kernel).
+  // anything reads it, and the row of per-expert totals is written in full by the scan or by the first rank block.
   return permute_with_workspace(desc, topk_idx, T, x, x_perm, expert_offsets, perm, inv_perm, h_counts_pinned, ws,
                                 (size_t)HMOE_PERMUTE_STATIC_BYTES, stream);
 }

@@ -18,9 +18,11 @@ def hm():
 
 
 @pytest.mark.parametrize("T,E,K", [(16384, 5, 1), (16385, 5, 1), (8192, 256, 2), (5462, 64, 3), (262144, 3, 1), (262145, 3, 1),
-                                   (87383, 130, 3)])
+                                   (87383, 130, 3), (1025, 1, 1), (1536, 2, 2), (513, 64, 2), (4096, 1, 1), (4096, 5, 1),
+                                   (2048, 2, 2), (586, 256, 7), (4097, 1, 1), (4097, 200, 1)])
 def test_permute_at_the_edges_of_its_ways(hm, T, E, K):
-    """16 and 256 chunks of 1024 assignments are the last of the one- and two-launch ways."""
+    """4 and 256 chunks of 1024 assignments are the last of the one- and two-launch ways; few experts, or most rows at one
+    of them, are keys that lanes of a wave share."""
     print("permute edges", T, E, K, flush=True)
     rng = np.random.default_rng(T + E)
     idx = np.minimum(rng.geometric(0.2, (T, K)) - 1, E - 1).astype(np.int32)
