@@ -1142,6 +1142,15 @@ int launch_ffn_tiled(const FfnArgs& a) {
   if (shared_panels) {
     v_gate_up = V_FIT4_PLAIN;
     v_down = tiles_down < 256 || d.ffn >= 4096 ? V_FIT4_PLAIN : V_FIT_PLAIN;
+    // A dense expert with a very long K range: a few tiles of the down projection, each a chain of 192 K steps or more,
+    // are what the layer's last launch waits for, the more so when the routed experts' launches got the CUs before
+    // them.  Tiles of 256x128 halve the reads of weights per row and so the chain.  Shared expert of 3584 x 20480 beside 64
+    // experts, top 8 (layer): 286 tokens 750 -> 716 us, 400 tokens 848 -> 770 us, 1003 tokens 1234 -> 1108 us; 4096 x
+    // 14336 beside 16, top 2, 300 tokens 344 -> 306 us.  Up to 256 rows they are no more tiles than 128x256, but twice as
+    // high (5 % slower at 220 rows), with 192 and more of them the many smaller ones are as fast, and for shorter K
+    // (shared experts of 4096 to 8192) the layer is 25 % faster to 7 % slower, by how the two FFNs' blocks happen to meet.
+    const long tiles_256 = ((long)a.n_rows + 255) / 256 * ((d.hidden + 127) / 128);
+    if (d.n_experts == 1 && d.ffn >= 12288 && a.n_rows > 256 && tiles_256 <= 192) v_down = V_FIT256_PLAIN;
     // A layer whose routed experts make at least seven rounds of 224x256 tiles (a large batch) takes that tile with
     // one wave per SIMD, in blocks that walk through their tiles -- for both projections, and for the layer's shared
     // experts too (hmoe_cache_set_layer tells their launches which layer they run beside): stress shape -3.5 % per

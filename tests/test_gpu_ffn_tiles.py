@@ -26,7 +26,7 @@ def grouped_ffn(hm, d, experts, x_bits, offsets, path):
 
 
 def case(dtype, hidden, ffn, counts):
-    shape = wl.small_shape(dtype=dtype, hidden=hidden, ffn=ffn, n_experts=len(counts), top_k=2)
+    shape = wl.small_shape(dtype=dtype, hidden=hidden, ffn=ffn, n_experts=len(counts), top_k=min(2, len(counts)))
     lay = wl.make_layer(shape, hidden + ffn, n_tokens=1)
     offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     x = wl.store(np.random.default_rng(7).standard_normal((int(offsets[-1]), hidden)).astype(np.float32), dtype)
@@ -70,6 +70,23 @@ def test_ffn_w4_tile_heights(hm, hidden, ffn, counts):
     got = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_TILED)
     ref = reference(x, offsets, lay.experts, hidden, lambda m: w4.dequantize_w4(*w4.quantize_w4(wl.as_f32(m))))
     assert max_rel_err(got, ref) < TOL[wl.BF16]
+
+
+# the edges of the rule that gives a dense expert's down projection 256x128 tiles (more than 256 rows, K of 12288 or more,
+# at most 192 tiles), widths that are no multiple of 128
+@pytest.mark.parametrize("rows,hidden,ffn", [(256, 192, 12288), (257, 192, 12288), (300, 320, 12352), (513, 64, 12288),
+                                             (300, 192, 12224), (12300, 448, 12288)])
+def test_dense_down_tiles(hm, monkeypatch, rows, hidden, ffn):
+    """Same bits as with the 128x256 tiles (a tile sums all of K in order), sampled rows against the oracle."""
+    print("dense down", rows, hidden, ffn, flush=True)
+    shape, lay, offsets, x = case(wl.BF16, hidden, ffn, [rows])
+    d = hm.make_desc(hidden, ffn, 1, 1, 1, hm.HMOE_BF16)
+    got = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_TILED)
+    monkeypatch.setenv("HMOE_TILED_VARIANT", "3")
+    assert np.array_equal(got, grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_TILED))
+    some = np.unique(np.r_[0:min(rows, 260):37, rows - 3:rows])
+    ref = orc.expert_ffn(wl.as_f64(x[some]), *(wl.as_f64(m) for m in lay.experts[0]))
+    assert max_rel_err(got[some], ref) < TOL[wl.BF16]
 
 
 @pytest.fixture(scope="module")
