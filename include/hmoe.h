@@ -74,7 +74,7 @@ enum { HMOE_F32 = 0, HMOE_BF16 = 1, HMOE_BF16_W4 = 2 };
 /* Which FFN kernels hmoe_expert_ffn_grouped uses.  AUTO picks by token count. */
 enum {
   HMOE_FFN_AUTO = 0,
-  HMOE_FFN_REFERENCE = 1, /* one wave per output element; any shape; fp32 and bf16          */
+  HMOE_FFN_REFERENCE = 1, /* one wave per output element; any shape and dtype               */
   HMOE_FFN_SKINNY = 2,    /* decode: weight-streaming MFMA GEMV, <= 32 rows per expert pass */
   HMOE_FFN_TILED = 3      /* prefill: LDS-tiled grouped MFMA GEMM                           */
 };
@@ -292,7 +292,8 @@ int32_t hmoe_route_scores(const hmoe_layer_desc* desc, const float* logits, int3
  *       HMOE_ERR_NOT_RESIDENT, nothing enqueued.  Rows of experts that are not active or not
  *       resident are left untouched.
  *   workspace: hmoe_ffn_workspace_bytes(desc, A) bytes of device scratch (holds h [A, F]).
- *   path: HMOE_FFN_*; AUTO = SKINNY when T = A/K <= 32 (4-bit weights: 16) else TILED, REFERENCE for fp32.
+ *   path: HMOE_FFN_*; AUTO = SKINNY when T = A/K <= 32 (4-bit weights: 16) else TILED; for fp32 tiles of their own
+ *       when H and F are multiples of 4, else REFERENCE (the only path by name).
  * Shared experts (Section II-A) use the same call with a 1-expert layer (E = K = S = 1,
  * offsets {0, T}).
  */

@@ -438,6 +438,10 @@ extern "C" size_t hmoe_ffn_workspace_bytes(const hmoe_layer_desc* desc, int32_t 
   return (((size_t)A * desc->ffn * elem) + 255) & ~(size_t)255;
 }
 
+// What HMOE_FFN_AUTO resolves to for fp32 calls on matrix instructions; no path that a caller can name (an explicit
+// HMOE_FFN_REFERENCE takes the general kernels).
+constexpr int32_t FFN_F32_TILES = HMOE_FFN_TILED + 1;
+
 // Checks the arguments of one grouped-FFN call, fills the launch arguments and resolves HMOE_FFN_AUTO.
 // *skip is set when there is nothing to compute (A == 0).
 static int32_t ffn_prepare(const hmoe_layer_desc* desc, hmoe_cache* cache, const void* x_perm, const int32_t* row_map,
@@ -483,7 +487,7 @@ static int32_t ffn_prepare(const hmoe_layer_desc* desc, hmoe_cache* cache, const
   }
 
   if (*path == HMOE_FFN_AUTO) {
-    if (desc->dtype == HMOE_F32) *path = HMOE_FFN_REFERENCE;
+    if (desc->dtype == HMOE_F32) *path = ffn_f32_takes(*desc, A) ? FFN_F32_TILES : HMOE_FFN_REFERENCE;
     else if (desc->dtype == HMOE_BF16_W4)
       // Above 16 tokens, where an expert may need a second 16-row pass of the decode kernel, the prefill tiles are faster
       // (layers of 8 experts of 4096 x 14336, 64 of 2048 x 1408 and 16 of 2048 x 1024; decode kernel -> tiles): 24 tokens
@@ -491,11 +495,12 @@ static int32_t ffn_prepare(const hmoe_layer_desc* desc, hmoe_cache* cache, const
       *path = (A / desc->top_k <= 16) ? HMOE_FFN_SKINNY : HMOE_FFN_TILED;
     else *path = (A / desc->top_k <= 32) ? HMOE_FFN_SKINNY : HMOE_FFN_TILED;
   }
-  if (desc->dtype == HMOE_F32 && *path != HMOE_FFN_REFERENCE) return HMOE_ERR_UNSUPPORTED;
+  if (desc->dtype == HMOE_F32 && *path != HMOE_FFN_REFERENCE && *path != FFN_F32_TILES) return HMOE_ERR_UNSUPPORTED;
   return HMOE_OK;
 }
 
 static int32_t ffn_launch(const FfnArgs& a, int32_t path) {
+  if (path == FFN_F32_TILES) return launch_ffn_f32(a);
   if (path == HMOE_FFN_REFERENCE) return launch_ffn_reference(a);
   if (path == HMOE_FFN_SKINNY) return a.desc->dtype == HMOE_BF16_W4 ? launch_ffn_skinny_w4(a) : launch_ffn_skinny(a);
   return a.desc->dtype == HMOE_BF16_W4 ? launch_ffn_tiled_w4(a) : launch_ffn_tiled(a);

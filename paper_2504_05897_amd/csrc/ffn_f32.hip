@@ -1,5 +1,5 @@
-// fp32 FFN on matrix instructions (HMOE_F32, hidden and ffn multiples of 4; other shapes take the general kernels of
-// ffn_reference.hip).  Weights are plain row-major.
+// fp32 FFN on matrix instructions (HMOE_F32 with HMOE_FFN_AUTO, hidden and ffn multiples of 4; the rest takes the general
+// kernels of ffn_reference.hip).  Weights are plain row-major.
 //
 // A tile is 16 MR rows of one expert x 32 weight rows (gate and up of 16 features, or 32 columns of the down
 // projection); every weight row is read once per tile instead of once per token, in 16-byte loads.  With few rows the
@@ -137,6 +137,8 @@ bool ffn_f32_takes(const hmoe_layer_desc& d, int n_rows) {
 
 int launch_ffn_f32(const FfnArgs& a) {
   const hmoe_layer_desc& d = *a.desc;
+  if (a.n_rows == 0) return HMOE_OK;
+  if ((d.ffn + 3) / 4 > 65535 || (d.hidden + 3) / 4 > 65535) return HMOE_ERR_UNSUPPORTED;  // as the general kernels
   TiledCtx c{a.offsets, a.slot_of, a.slots, a.slot_bytes, a.active, d.n_experts, d.hidden, d.ffn, 0, 0, a.row_map, a.map_div};
   // MR: one 16-row fragment per tile while experts have fewer rows than that on average (a second one would be padding),
   // else two, which halve the reads of the weights

@@ -1,8 +1,8 @@
 // Reference FFN kernels (HMOE_FFN_REFERENCE): one wavefront per output element, lanes stride
 // the reduction dimension.  Any shape; fp32 (plain row-major slots), bf16 (packed slots) and 4-bit
 // weights (decoded element by element).
-// This is the in-library cross-check for the MFMA paths, and what fp32 layers take whose sizes are no multiples of 4 (the
-// others go to ffn_f32.hip).
+// This is the in-library cross-check for the matrix paths, and what HMOE_FFN_AUTO takes for fp32 calls that ffn_f32_takes
+// leaves to it.
 #include "common.h"
 
 namespace hmoe {
@@ -162,7 +162,6 @@ int launch_ffn_reference(const FfnArgs& a) {
   const hmoe_layer_desc& d = *a.desc;
   if (a.n_rows == 0) return HMOE_OK;
   if ((d.ffn + 3) / 4 > 65535 || (d.hidden + 3) / 4 > 65535) return HMOE_ERR_UNSUPPORTED;
-  if (ffn_f32_takes(d, a.n_rows)) return launch_ffn_f32(a);
   RefCtx c{a.offsets, a.slot_of, a.slots, a.slot_bytes, a.active, d.n_experts, d.hidden, d.ffn, a.n_rows, a.row_map, a.map_div};
   const dim3 g1((unsigned)a.n_rows, (unsigned)((d.ffn + 3) / 4)), g2((unsigned)a.n_rows, (unsigned)((d.hidden + 3) / 4));
   probe_before(a.stream);

@@ -51,8 +51,26 @@ def test_ffn_f32_tiles(hm, hidden, ffn, counts):
     d = desc_of(hm, shape, n_slots=len(counts))
     got = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_AUTO)
     # sums of K / 64 products each in fp32, then 64 bits: at most 24 roundings of 2^-24 per GEMM at these sizes, and a
-    # handful in silu: 2e-6 of the largest value leaves the margin of cancellation
+    # handful in silu: 2e-6 of the largest value, and as much again for cancellation
     assert max_rel_err(got, reference(x, offsets, lay.experts, hidden, wl.as_f64)) < 4e-6
+
+
+# An explicit HMOE_FFN_REFERENCE takes the general kernels whatever the sizes.  Rows and columns of zeros behind the
+# others leave every sum of theirs as it is, bit for bit, and make the sizes such that nothing else takes them.
+@pytest.mark.parametrize("hidden,ffn,counts", [(72, 100, [3, 0, 7]), (256, 512, [31, 0, 33, 64, 1])])
+def test_ffn_f32_reference_is_the_general_kernels(hm, hidden, ffn, counts):
+    print("ffn f32 reference", hidden, ffn, counts, flush=True)
+    shape, lay, offsets, x = case(wl.F32, hidden, ffn, counts)
+    d = desc_of(hm, shape, n_slots=len(counts))
+    got = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_REFERENCE)
+    assert max_rel_err(got, reference(x, offsets, lay.experts, hidden, wl.as_f64)) < 4e-6
+    pad = lambda m, rows, cols: np.pad(m, ((0, rows - m.shape[0]), (0, cols - m.shape[1])))
+    H, F = hidden + 1, ffn + 2
+    wide = [(pad(g, F, H), pad(u, F, H), pad(w, H, F)) for g, u, w in lay.experts]
+    dw = hm.make_desc(H, F, len(counts), 2, len(counts), hm.HMOE_F32)
+    for path in (hm.HMOE_FFN_REFERENCE, hm.HMOE_FFN_AUTO):
+        other = grouped_ffn(hm, dw, wide, pad(x, len(x), H), offsets, path)
+        assert np.array_equal(other[:, :hidden], got) and not other[:, hidden:].any()
 
 
 # every height of one tile (1 to 6 fragments), experts of several tiles with uneven heights, ragged last fragments, a
