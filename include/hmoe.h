@@ -293,7 +293,7 @@ int32_t hmoe_route_scores(const hmoe_layer_desc* desc, const float* logits, int3
  *       resident are left untouched.
  *   workspace: hmoe_ffn_workspace_bytes(desc, A) bytes of device scratch (holds h [A, F]).
  *   path: HMOE_FFN_*; AUTO = SKINNY when T = A/K <= 32 (4-bit weights: 16) else TILED; for fp32 tiles of their own
- *       when H and F are multiples of 4, else REFERENCE (the only path by name).
+ *       when H and F are multiples of 4 and there are more than a few rows, else REFERENCE (the only path by name).
  * Shared experts (Section II-A) use the same call with a 1-expert layer (E = K = S = 1,
  * offsets {0, T}).
  */

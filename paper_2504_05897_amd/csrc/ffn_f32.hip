@@ -1,5 +1,5 @@
-// fp32 FFN on matrix instructions (HMOE_F32 with HMOE_FFN_AUTO, hidden and ffn multiples of 4; the rest takes the general
-// kernels of ffn_reference.hip).  Weights are plain row-major.
+// fp32 FFN on matrix instructions (HMOE_F32 with HMOE_FFN_AUTO, hidden and ffn multiples of 4, more than a few rows; the
+// rest takes the general kernels of ffn_reference.hip, see ffn_f32_takes).  Weights are plain row-major.
 //
 // A tile is 16 MR rows of one expert x 32 weight rows (gate and up of 16 features, or 32 columns of the down
 // projection); every weight row is read once per tile instead of once per token, in 16-byte loads.  With few rows the
@@ -14,6 +14,7 @@
 //     partial sums per output over K / 64 products each (as many as one wavefront per output element would keep), which
 //     are added up in 64 bits and rounded once: error of the layer 1.27e-7 against 1.67e-7 (2-norm, 1024 tokens).
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "tile_locate.h"
@@ -129,10 +130,21 @@ static void launch_stage_f32(TiledCtx c, int n_rows, const float* in, float* out
   hipLaunchKernelGGL((ffn_f32_kernel<GATEUP, MR>), dim3((unsigned)c.grid_padded), dim3(256 * MR), 0, s, c, in, out);
 }
 
+// The general kernels read an expert's weights for every row again, out of the caches (about 6 TB/s); the tiles read them
+// once, but from memory at four fifths of the general kernels' rate, and their two launches start 5 us later (locating a
+// tile, one wave per piece of K, sums in LDS).  So the general kernels have it until the rows that find their expert's
+// weights already read, by uniform routing, re-read more than 30 MB (100 MB where all of the layer's weights stay in an L2)
+// and 15 % of what is read in any case.  Layers, general kernels / tiles, us: 8 experts of 256 x 512, top 2: 8 tokens
+// 15.1 / 19.6, 16 tokens 24.6 / 20.5; 8 of 1024 x 4096, top 2: 2 tokens 56.9 / 63.5, 3 tokens 68.5 / 65.6; 64 of 1024 x 512, top 8: 4
+// tokens 64.3 / 67.0, 6 tokens 85.2 / 81.0; one of 256 x 512: 33 tokens 19.8 / 23.1, 64 tokens 25.0 / 25.0; 4 of 64 x 96, top 2: 64 tokens
+// 15.6 / 19.3.
 bool ffn_f32_takes(const hmoe_layer_desc& d, int n_rows) {
   if (d.dtype != HMOE_F32 || d.hidden % 4 != 0 || d.ffn % 4 != 0) return false;
   const long n_tiles = std::max((d.ffn + 15) / 16, (d.hidden + 31) / 32);  // the grid has to fit its 32-bit dimension
-  return ((long)n_rows / 16 + std::min(d.n_experts, n_rows)) * n_tiles < (1l << 22);
+  if (((long)n_rows / 16 + std::min(d.n_experts, n_rows)) * n_tiles >= (1l << 22)) return false;
+  const double expert = 12.0 * d.hidden * d.ffn, layer = expert * d.n_experts;
+  const double touched = d.n_experts * (1.0 - std::pow(1.0 - (double)d.top_k / d.n_experts, (double)n_rows / d.top_k));
+  return (n_rows - touched) * expert > (layer <= 4e6 ? 100e6 : 30e6) + 0.15 * touched * expert;
 }
 
 int launch_ffn_f32(const FfnArgs& a) {

@@ -45,6 +45,9 @@ def reference(x, offsets, experts, hidden, to_f64):
 @pytest.mark.parametrize("hidden,ffn,counts", [
     (256, 512, [1, 0, 16, 5]), (4, 8, [3, 1]), (260, 36, [17, 2, 0, 1]), (516, 772, [2, 9]),
     (256, 512, [31, 0, 33, 64, 1]), (100, 44, [40, 15]), (1028, 20, [65, 32]),
+    # large enough for the tiles: one fragment per tile (fewer than 16 rows per expert on average), and two
+    (516, 772, [1, 17, 0, 16, 5, 2, 0, 9]), (260, 1540, [2, 0, 15, 16, 3, 17, 1, 1, 0, 40, 5, 9]), (4, 33028, [65, 40]),
+    (2052, 36, [33, 70, 64]), (1028, 300, [31, 0, 33, 64, 1]),
 ])
 def test_ffn_f32_tiles(hm, hidden, ffn, counts):
     shape, lay, offsets, x = case(wl.F32, hidden, ffn, counts)
@@ -53,6 +56,9 @@ def test_ffn_f32_tiles(hm, hidden, ffn, counts):
     # sums of K / 64 products each in fp32, then 64 bits: at most 24 roundings of 2^-24 per GEMM at these sizes, and a
     # handful in silu: 2e-6 of the largest value, and as much again for cancellation
     assert max_rel_err(got, reference(x, offsets, lay.experts, hidden, wl.as_f64)) < 4e-6
+    general = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_REFERENCE)
+    # the calls that are too small for the tiles take the general kernels
+    assert np.array_equal(got, general) == (12 * hidden * ffn * (int(offsets[-1]) - len(counts)) < 30e6)
 
 
 # An explicit HMOE_FFN_REFERENCE takes the general kernels whatever the sizes.  Rows and columns of zeros behind the
