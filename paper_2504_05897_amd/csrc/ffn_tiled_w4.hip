@@ -57,8 +57,10 @@ struct __attribute__((aligned(256))) W4TileLds {
 };
 
 // (`in` is not declared __restrict__: loads that nothing can alias are moved past a step's barrier, down to their uses.)
-// One tile of FM 16-row fragments: rows m0 .. m0 + 16 FM of the expert `loc` names.
-template <bool GATEUP, int FM, int KS>
+// One tile of FM 16-row fragments: rows m0 .. m0 + 16 FM of the expert `loc` names.  A lane addresses its input by a byte
+// offset from a scalar base: with a row map the input itself, 32 bits while it is smaller than 4 GiB (else FAR: 64);
+// without one the tile's first row.
+template <bool GATEUP, int FM, int KS, bool FAR>
 __device__ __forceinline__ void w4_tile(const TiledCtx& c, const TileLoc& loc, const int m0, const bf16_t* in, bf16_t* out, W4TileLds (&lds_of)[KS]) {
   constexpr int THREADS = 64 * W4T_WAVES;
   static_assert(FM * 256 % THREADS == 0, "");
@@ -88,15 +90,18 @@ __device__ __forceinline__ void w4_tile(const TiledCtx& c, const TileLoc& loc, c
     ws[u] = in_scalars(scales + unit * (size_t)n_groups * 16);
   }
   // the chunks of a stage this thread moves: chunk id = i * THREADS + tid -> row id / 16, k chunk id % 16
-  uint32_t a_src[COPIES];  // in bytes from `in` (the launch sees to it that 32 bits hold them)
+  typedef typename std::conditional<FAR, uint64_t, uint32_t>::type src_t;
+  src_t a_src[COPIES];
+  const bool mapped = GATEUP && c.row_map;
+  const char* const first = in_scalars((const char*)(in + (mapped ? 0 : (size_t)(loc.row_first + m0) * K)));
   const int a_dst = tid / 16 * 16 + ((tid % 16) ^ (tid / 16));  // + i * THREADS: 16 rows further, the same swizzle
   static_assert(THREADS == 256, "a copy instruction of the block moves 16 rows");
 #pragma unroll
   for (int i = 0; i < COPIES; ++i) {
     const int r = i * 16 + tid / 16;
-    const int row = m0 + r < loc.m_rows ? m0 + r : loc.m_rows - 1;  // clamped: never stored
-    const int in_row = GATEUP ? mapped_row(c.row_map, c.map_div, loc.row_first + row) : loc.row_first + row;
-    a_src[i] = (uint32_t)in_row * (uint32_t)(2 * K) + 16 * (tid % 16);
+    const int row = m0 + r < loc.m_rows ? r : loc.m_rows - 1 - m0;  // of the tile; clamped: never stored
+    const int in_row = mapped ? c.row_map[loc.row_first + m0 + row] / c.map_div : row;
+    a_src[i] = (src_t)in_row * (uint32_t)(2 * K) + 16 * (tid % 16);
   }
 
   u32x4 codes[W4T_RING][W4T_NU];
@@ -172,7 +177,7 @@ __device__ __forceinline__ void w4_tile(const TiledCtx& c, const TileLoc& loc, c
   constexpr int AHEAD = FM <= 4 ? 2 : 1;
   u32x4 ahead[AHEAD == 2 ? W4T_RING : 1][COPIES];
   auto load_stage = [&](int stage, int g) {
-    const char* from = (const char*)in + (size_t)min(KS * g + part_k, n_groups - 1) * (2 * W4_GROUP);  // clamped likewise
+    const char* from = first + (size_t)min(KS * g + part_k, n_groups - 1) * (2 * W4_GROUP);  // clamped likewise
 #pragma unroll
     for (int i = 0; i < COPIES; ++i) ahead[AHEAD == 2 ? stage : 0][i] = *(global_ptr<u32x4>)(from + a_src[i]);
   };
@@ -348,7 +353,7 @@ __device__ __forceinline__ void w4_tile(const TiledCtx& c, const TileLoc& loc, c
 }
 
 // KS = 2: two sets of waves take the scale groups in turn, each with its own stages, and add their sums at the end.
-template <bool GATEUP, int KS>
+template <bool GATEUP, int KS, bool FAR>
 __global__ __launch_bounds__(64 * W4T_WAVES * KS, 2) void ffn_tile_w4_kernel(TiledCtx c, const bf16_t* in, bf16_t* out) {
   __shared__ W4TileLds lds[KS];
   TileLoc loc;
@@ -359,12 +364,12 @@ __global__ __launch_bounds__(64 * W4T_WAVES * KS, 2) void ffn_tile_w4_kernel(Til
   const int fm = __builtin_amdgcn_readfirstlane(base + (loc.mt < rem ? 1 : 0));
   const int m0 = __builtin_amdgcn_readfirstlane(16 * (loc.mt * base + (loc.mt < rem ? loc.mt : rem)));
   switch (fm) {
-    case 1: w4_tile<GATEUP, 1, KS>(c, loc, m0, in, out, lds); break;
-    case 2: w4_tile<GATEUP, 2, KS>(c, loc, m0, in, out, lds); break;
-    case 3: w4_tile<GATEUP, 3, KS>(c, loc, m0, in, out, lds); break;
-    case 4: w4_tile<GATEUP, 4, KS>(c, loc, m0, in, out, lds); break;
-    case 5: w4_tile<GATEUP, 5, KS>(c, loc, m0, in, out, lds); break;
-    default: w4_tile<GATEUP, 6, KS>(c, loc, m0, in, out, lds); break;
+    case 1: w4_tile<GATEUP, 1, KS, FAR>(c, loc, m0, in, out, lds); break;
+    case 2: w4_tile<GATEUP, 2, KS, FAR>(c, loc, m0, in, out, lds); break;
+    case 3: w4_tile<GATEUP, 3, KS, FAR>(c, loc, m0, in, out, lds); break;
+    case 4: w4_tile<GATEUP, 4, KS, FAR>(c, loc, m0, in, out, lds); break;
+    case 5: w4_tile<GATEUP, 5, KS, FAR>(c, loc, m0, in, out, lds); break;
+    default: w4_tile<GATEUP, 6, KS, FAR>(c, loc, m0, in, out, lds); break;
   }
 }
 
@@ -378,18 +383,20 @@ static void launch_stage_tile_w4(TiledCtx c, int n_rows, const bf16_t* in, bf16_
   // At most one tile per CU (down projections, few experts): a CU then holds one wave per SIMD, and two sets of waves per
   // tile fill it (down projection above: 301 tokens 158 -> 137 us, 150 tokens 101 -> 82 us, 77 tokens 76 -> 66 us).  With
   // more tiles two blocks share a CU anyway.
-  if (tiles <= 256)
-    hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, 2>), dim3((unsigned)c.grid_padded), dim3(128 * W4T_WAVES), 0, s, c, in, out);
+  // (an input of 4 GiB or more is that many tokens that the tiles are always enough for two blocks per CU)
+  const bool far = GATEUP && c.row_map && (size_t)(n_rows / c.map_div) * (size_t)c.hidden * 2 > 0xffffffffu;
+  if (GATEUP && far)
+    hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, 1, GATEUP>), dim3((unsigned)c.grid_padded), dim3(64 * W4T_WAVES), 0, s, c, in, out);
+  else if (tiles <= 256)
+    hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, 2, false>), dim3((unsigned)c.grid_padded), dim3(128 * W4T_WAVES), 0, s, c, in, out);
   else
-    hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, 1>), dim3((unsigned)c.grid_padded), dim3(64 * W4T_WAVES), 0, s, c, in, out);
+    hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, 1, false>), dim3((unsigned)c.grid_padded), dim3(64 * W4T_WAVES), 0, s, c, in, out);
 }
 
 int launch_ffn_tiled_w4(const FfnArgs& a) {
   const hmoe_layer_desc& d = *a.desc;
   if (d.dtype != HMOE_BF16_W4) return HMOE_ERR_UNSUPPORTED;
   if (a.n_rows == 0) return HMOE_OK;
-  // the tiles address their input rows with 32 bits (150 thousand rows of 14336)
-  if ((size_t)a.n_rows * (size_t)std::max(d.hidden, d.ffn) * 2 > 0xffffffffu) return launch_ffn_skinny_w4(a);
   TiledCtx c{a.offsets, a.slot_of, a.slots, a.slot_bytes, a.active, d.n_experts, d.hidden, d.ffn, 0, 0, a.row_map, a.map_div};
   probe_before(a.stream);
   launch_stage_tile_w4<true>(c, a.n_rows, (const bf16_t*)a.x_perm, (bf16_t*)a.h, a.stream);

@@ -80,12 +80,14 @@ def test_ffn_f32_reference_is_the_general_kernels(hm, hidden, ffn, counts):
 
 
 # every height of one tile (1 to 6 fragments), experts of several tiles with uneven heights, ragged last fragments, a
-# column tile that is not full, and one, two, three and more scale groups (the ring holds three).  The last three have more
-# than 256 tiles in one projection, which then takes the blocks of one set of waves; fewer take those of two sets.
+# column tile that is not full, and one, two, three and more scale groups (the ring holds three).  The last six have more
+# than 256 tiles in one projection (the first four of them gate/up, with 3, 4, 5 and 7 scale groups and every height), which
+# then takes the blocks of one set of waves; fewer take those of two sets.
 @pytest.mark.parametrize("hidden,ffn,counts", [
     (256, 128, [1, 16, 17, 33, 49, 80, 81, 96]), (128, 256, [97, 0, 112, 113]), (384, 640, [193, 96, 290]),
     (512, 384, [64, 65]), (1152, 128, [95, 3]),
-    (384, 16768, [100]), (4096, 128, [97, 33, 16, 50, 81, 1, 2, 64, 96]), (4096, 640, [96, 34, 17, 51, 80, 2, 3, 64, 65]),
+    (384, 16768, [100]), (512, 4224, [1, 17, 33, 49, 80, 81, 96, 97]), (640, 4224, [97, 96, 2, 16, 47, 65, 81, 33]),
+    (896, 4224, [193, 1, 17, 33, 49, 80, 81, 96]), (4096, 128, [97, 33, 16, 50, 81, 1, 2, 64, 96]), (4096, 640, [96, 34, 17, 51, 80, 2, 3, 64, 65]),
 ])
 def test_ffn_w4_tile_heights(hm, hidden, ffn, counts):
     shape, lay, offsets, x = case(wl.BF16, hidden, ffn, counts)
@@ -94,6 +96,41 @@ def test_ffn_w4_tile_heights(hm, hidden, ffn, counts):
     got = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_TILED)
     ref = reference(x, offsets, lay.experts, hidden, lambda m: w4.dequantize_w4(*w4.quantize_w4(wl.as_f32(m))))
     assert max_rel_err(got, ref) < TOL[wl.BF16]
+
+
+# Inputs of 4 GiB and more: the intermediate of a wide expert, and tokens that the gate/up projection gathers from.
+@pytest.mark.parametrize("hidden,ffn,rows,gather", [(128, 16384, 131200, False), (128, 16384, 131200, True), (4096, 128, 524400, True)])
+def test_ffn_w4_large_inputs(hm, hidden, ffn, rows, gather):
+    """Same bits as for the first and the last rows by themselves (a row's sums do not depend on the tile it is in), some rows
+    against the oracle."""
+    print("w4 large inputs", hidden, ffn, rows, gather, flush=True)
+    shape, lay, _, _ = case(wl.BF16, hidden, ffn, [16])
+    d = hm.make_desc(hidden, ffn, 1, 1, 1, hm.HMOE_BF16_W4)
+    layer = hm.MoELayer(d, lay.experts, (), None, max_tokens=16)
+    x = torch.randn(rows, hidden, device=DEV, generator=torch.Generator(DEV).manual_seed(3)).bfloat16()
+
+    def ffn_of(xs):
+        n = len(xs)
+        o = torch.empty(n, hidden, dtype=torch.bfloat16, device=DEV)
+        ws_bytes = hm.hmoe_ffn_workspace_bytes(d, n)
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+        offsets = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+        if gather:  # the rows in descending order
+            perm = torch.arange(n - 1, -1, -1, dtype=torch.int32, device=DEV)
+            hm.hmoe_expert_ffn_grouped_gather(d, layer.cache, xs, perm, offsets, n, None, o, ws, ws_bytes, hm.HMOE_FFN_TILED)
+            o = o.flip(0)
+        else:
+            hm.hmoe_expert_ffn_grouped(d, layer.cache, xs, offsets, n, None, o, ws, ws_bytes, hm.HMOE_FFN_TILED)
+        torch.cuda.synchronize()
+        return o
+
+    got, part = ffn_of(x), 26000  # enough for more than one tile per CU, as the whole has
+    assert torch.equal(got[:part], ffn_of(x[:part].contiguous()))
+    assert torch.equal(got[-part:], ffn_of(x[-part:].contiguous()))
+    some = [0, 1, rows // 2, rows - 2, rows - 1]
+    ref = orc.expert_ffn(x[some].double().cpu().numpy(), *(w4.dequantize_w4(*w4.quantize_w4(wl.as_f32(m))) for m in lay.experts[0]))
+    assert max_rel_err(to_host_f32(got[some]), ref) < TOL[wl.BF16]
+    layer.close()
 
 
 # the edges of the rule that gives a dense expert's down projection 256x128 tiles (more than 256 rows, K of 12288 or more,
