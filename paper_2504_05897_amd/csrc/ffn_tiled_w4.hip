@@ -353,44 +353,62 @@ __device__ __forceinline__ void w4_tile(const TiledCtx& c, const TileLoc& loc, c
 }
 
 // KS = 2: two sets of waves take the scale groups in turn, each with its own stages, and add their sums at the end.
-template <bool GATEUP, int KS, bool FAR>
+// MOST: the most fragments a tile may have.
+template <bool GATEUP, int KS, int MOST, bool FAR>
 __global__ __launch_bounds__(64 * W4T_WAVES * KS, 2) void ffn_tile_w4_kernel(TiledCtx c, const bf16_t* in, bf16_t* out) {
+  static_assert(MOST <= W4T_FM_MAX, "");
   __shared__ W4TileLds lds[KS];
   TileLoc loc;
-  if (!locate_tile<16 * W4T_FM_MAX>(c, loc)) return;  // uniform over the block
+  if (!locate_tile<16 * MOST>(c, loc)) return;  // uniform over the block
   // the expert's fragments dealt evenly to its m-tiles
-  const int mts = (loc.m_rows + 16 * W4T_FM_MAX - 1) / (16 * W4T_FM_MAX);
+  const int mts = (loc.m_rows + 16 * MOST - 1) / (16 * MOST);
   const int frags = (loc.m_rows + 15) / 16, base = frags / mts, rem = frags % mts;
   const int fm = __builtin_amdgcn_readfirstlane(base + (loc.mt < rem ? 1 : 0));
   const int m0 = __builtin_amdgcn_readfirstlane(16 * (loc.mt * base + (loc.mt < rem ? loc.mt : rem)));
-  switch (fm) {
-    case 1: w4_tile<GATEUP, 1, KS, FAR>(c, loc, m0, in, out, lds); break;
-    case 2: w4_tile<GATEUP, 2, KS, FAR>(c, loc, m0, in, out, lds); break;
-    case 3: w4_tile<GATEUP, 3, KS, FAR>(c, loc, m0, in, out, lds); break;
-    case 4: w4_tile<GATEUP, 4, KS, FAR>(c, loc, m0, in, out, lds); break;
-    case 5: w4_tile<GATEUP, 5, KS, FAR>(c, loc, m0, in, out, lds); break;
-    default: w4_tile<GATEUP, 6, KS, FAR>(c, loc, m0, in, out, lds); break;
+#define HMOE_W4_TILE(FM)                                                                              \
+  if constexpr (FM <= MOST) {                                                                         \
+    if (fm == FM) return w4_tile<GATEUP, FM, KS, FAR>(c, loc, m0, in, out, lds);                      \
   }
+  HMOE_W4_TILE(1) HMOE_W4_TILE(2) HMOE_W4_TILE(3) HMOE_W4_TILE(4) HMOE_W4_TILE(5) HMOE_W4_TILE(6)
+#undef HMOE_W4_TILE
+}
+
+template <bool GATEUP, int KS, int MOST, bool FAR>
+static void launch_tiles_w4(TiledCtx c, int n_rows, const bf16_t* in, bf16_t* out, hipStream_t s) {
+  c.grid_padded = (int)((tiles_upper_bound(c, n_rows, 16 * MOST) + 7) / 8 * 8);
+  hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, KS, MOST, FAR>), dim3((unsigned)c.grid_padded), dim3(64 * KS * W4T_WAVES), 0, s, c, in, out);
 }
 
 template <bool GATEUP>
 static void launch_stage_tile_w4(TiledCtx c, int n_rows, const bf16_t* in, bf16_t* out, hipStream_t s) {
   const int units_total = (GATEUP ? 2 * c.ffn : c.hidden) / 16;
   c.n_tiles_n = (units_total + W4T_UNITS - 1) / W4T_UNITS;
-  c.grid_padded = (int)((tiles_upper_bound(c, n_rows, 16 * W4T_FM_MAX) + 7) / 8 * 8);
-  const long per_expert = (n_rows + c.n_experts - 1) / c.n_experts;
-  const long tiles = std::min(c.n_experts, n_rows) * ((per_expert + 16 * W4T_FM_MAX - 1) / (16 * W4T_FM_MAX)) * (long)c.n_tiles_n;
+  // (an input of 4 GiB or more is that many tokens that the tiles are always enough for two blocks per CU)
+  if constexpr (GATEUP) {
+    if (c.row_map && (size_t)(n_rows / c.map_div) * (size_t)c.hidden * 2 > 0xffffffffu)
+      return launch_tiles_w4<true, 1, W4T_FM_MAX, true>(c, n_rows, in, out, s);
+  }
+  const long busy = std::min(c.n_experts, n_rows), per_expert = (n_rows + c.n_experts - 1) / c.n_experts;
+  auto per = [](long rows, int most) { return (rows + 16 * most - 1) / (16 * most); };  // m-tiles of at most `most` fragments
+  // tiles when every expert has as many rows, and when some have twice as many (but no more than all rows can make)
+  auto even = [&](int most) { return busy * per(per_expert, most) * (long)c.n_tiles_n; };
+  auto uneven = [&](int most) {
+    const long all = busy == 1 ? per(n_rows, most) : std::min(busy * per(2 * per_expert, most), n_rows / (16 * most) + busy);
+    return all * (long)c.n_tiles_n;
+  };
   // At most one tile per CU (down projections, few experts): a CU then holds one wave per SIMD, and two sets of waves per
   // tile fill it (down projection above: 301 tokens 158 -> 137 us, 150 tokens 101 -> 82 us, 77 tokens 76 -> 66 us).  With
   // more tiles two blocks share a CU anyway.
-  // (an input of 4 GiB or more is that many tokens that the tiles are always enough for two blocks per CU)
-  const bool far = GATEUP && c.row_map && (size_t)(n_rows / c.map_div) * (size_t)c.hidden * 2 > 0xffffffffu;
-  if (GATEUP && far)
-    hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, 1, GATEUP>), dim3((unsigned)c.grid_padded), dim3(64 * W4T_WAVES), 0, s, c, in, out);
-  else if (tiles <= 256)
-    hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, 2, false>), dim3((unsigned)c.grid_padded), dim3(128 * W4T_WAVES), 0, s, c, in, out);
-  else
-    hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, 1, false>), dim3((unsigned)c.grid_padded), dim3(64 * W4T_WAVES), 0, s, c, in, out);
+  // The most fragments a tile may have: six, which read and unpack a weight for 96 rows -- unless lower tiles make no more
+  // rounds either (a step of 6, 4 and 2 fragments takes about 1.4, 1 and 0.6), also if some experts have more rows than
+  // average.  Layers, six at most -> now: one expert of 1024 x 512, 64 tokens 36.9 -> 26.9 us; one of 2048 x 2816, 301 tokens
+  // 57.9 -> 42.7 us (tiles of 64 rows and 256 columns before either: 46.5 and 63 us); one of 3584 x 20480, 1003 tokens,
+  // down launch 287 -> 211 us (200).
+  if (uneven(2) <= 256) launch_tiles_w4<GATEUP, 2, 2, false>(c, n_rows, in, out, s);
+  else if (uneven(4) <= 256) launch_tiles_w4<GATEUP, 2, 4, false>(c, n_rows, in, out, s);
+  else if (even(6) <= 256) launch_tiles_w4<GATEUP, 2, 6, false>(c, n_rows, in, out, s);
+  else if (uneven(4) <= 512) launch_tiles_w4<GATEUP, 1, 4, false>(c, n_rows, in, out, s);
+  else launch_tiles_w4<GATEUP, 1, 6, false>(c, n_rows, in, out, s);
 }
 
 int launch_ffn_tiled_w4(const FfnArgs& a) {

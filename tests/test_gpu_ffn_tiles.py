@@ -86,6 +86,9 @@ def test_ffn_f32_reference_is_the_general_kernels(hm, hidden, ffn, counts):
 @pytest.mark.parametrize("hidden,ffn,counts", [
     (256, 128, [1, 16, 17, 33, 49, 80, 81, 96]), (128, 256, [97, 0, 112, 113]), (384, 640, [193, 96, 290]),
     (512, 384, [64, 65]), (1152, 128, [95, 3]),
+    # two sets of waves with tiles of at most 2, 4 and 6 fragments, one set with at most 4
+    (256, 256, [33, 64, 65]), (640, 384, [129]), (1024, 1920, [64, 0, 129, 33, 16]), (1024, 4224, [128, 65]), (512, 8192, [256]),
+    (640, 4096, [129, 128, 65, 1]),
     (384, 16768, [100]), (512, 4224, [1, 17, 33, 49, 80, 81, 96, 97]), (640, 4224, [97, 96, 2, 16, 47, 65, 81, 33]),
     (896, 4224, [193, 1, 17, 33, 49, 80, 81, 96]), (4096, 128, [97, 33, 16, 50, 81, 1, 2, 64, 96]), (4096, 640, [96, 34, 17, 51, 80, 2, 3, 64, 65]),
 ])
