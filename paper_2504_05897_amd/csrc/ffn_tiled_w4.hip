@@ -25,6 +25,7 @@
 // 301 tokens 347 -> 262 and 164 -> 137 us, 1000 tokens 666 -> 698 and 413 -> 357 us (0.67 PFLOP/s; the card's large bf16
 // matrix product reaches 1.19).
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -58,9 +59,9 @@ struct __attribute__((aligned(256))) W4TileLds {
 
 // (`in` is not declared __restrict__: loads that nothing can alias are moved past a step's barrier, down to their uses.)
 // One tile of FM 16-row fragments: rows m0 .. m0 + 16 FM of the expert `loc` names.  A lane addresses its input by a byte
-// offset from a scalar base: with a row map the input itself, 32 bits while it is smaller than 4 GiB (else FAR: 64);
+// offset of 32 bits from a scalar base: with a row map the input itself (smaller than 4 GiB, the launch sees to it),
 // without one the tile's first row.
-template <bool GATEUP, int FM, int KS, bool FAR>
+template <bool GATEUP, int FM, int KS>
 __device__ __forceinline__ void w4_tile(const TiledCtx& c, const TileLoc& loc, const int m0, const bf16_t* in, bf16_t* out, W4TileLds (&lds_of)[KS]) {
   constexpr int THREADS = 64 * W4T_WAVES;
   static_assert(FM * 256 % THREADS == 0, "");
@@ -90,8 +91,7 @@ __device__ __forceinline__ void w4_tile(const TiledCtx& c, const TileLoc& loc, c
     ws[u] = in_scalars(scales + unit * (size_t)n_groups * 16);
   }
   // the chunks of a stage this thread moves: chunk id = i * THREADS + tid -> row id / 16, k chunk id % 16
-  typedef typename std::conditional<FAR, uint64_t, uint32_t>::type src_t;
-  src_t a_src[COPIES];
+  uint32_t a_src[COPIES];
   const bool mapped = GATEUP && c.row_map;
   const char* const first = in_scalars((const char*)(in + (mapped ? 0 : (size_t)(loc.row_first + m0) * K)));
   const int a_dst = tid / 16 * 16 + ((tid % 16) ^ (tid / 16));  // + i * THREADS: 16 rows further, the same swizzle
@@ -101,7 +101,7 @@ __device__ __forceinline__ void w4_tile(const TiledCtx& c, const TileLoc& loc, c
     const int r = i * 16 + tid / 16;
     const int row = m0 + r < loc.m_rows ? r : loc.m_rows - 1 - m0;  // of the tile; clamped: never stored
     const int in_row = mapped ? c.row_map[loc.row_first + m0 + row] / c.map_div : row;
-    a_src[i] = (src_t)in_row * (uint32_t)(2 * K) + 16 * (tid % 16);
+    a_src[i] = (uint32_t)in_row * (uint32_t)(2 * K) + 16 * (tid % 16);
   }
 
   u32x4 codes[W4T_RING][W4T_NU];
@@ -354,7 +354,7 @@ __device__ __forceinline__ void w4_tile(const TiledCtx& c, const TileLoc& loc, c
 
 // KS = 2: two sets of waves take the scale groups in turn, each with its own stages, and add their sums at the end.
 // MOST: the most fragments a tile may have.
-template <bool GATEUP, int KS, int MOST, bool FAR>
+template <bool GATEUP, int KS, int MOST>
 __global__ __launch_bounds__(64 * W4T_WAVES * KS, 2) void ffn_tile_w4_kernel(TiledCtx c, const bf16_t* in, bf16_t* out) {
   static_assert(MOST <= W4T_FM_MAX, "");
   __shared__ W4TileLds lds[KS];
@@ -367,31 +367,29 @@ __global__ __launch_bounds__(64 * W4T_WAVES * KS, 2) void ffn_tile_w4_kernel(Til
   const int m0 = __builtin_amdgcn_readfirstlane(16 * (loc.mt * base + (loc.mt < rem ? loc.mt : rem)));
 #define HMOE_W4_TILE(FM)                                                                              \
   if constexpr (FM <= MOST) {                                                                         \
-    if (fm == FM) return w4_tile<GATEUP, FM, KS, FAR>(c, loc, m0, in, out, lds);                      \
+    if (fm == FM) return w4_tile<GATEUP, FM, KS>(c, loc, m0, in, out, lds);                           \
   }
   HMOE_W4_TILE(1) HMOE_W4_TILE(2) HMOE_W4_TILE(3) HMOE_W4_TILE(4) HMOE_W4_TILE(5) HMOE_W4_TILE(6)
 #undef HMOE_W4_TILE
 }
 
-template <bool GATEUP, int KS, int MOST, bool FAR>
+template <bool GATEUP, int KS, int MOST>
 static void launch_tiles_w4(TiledCtx c, int n_rows, const bf16_t* in, bf16_t* out, hipStream_t s) {
   c.grid_padded = (int)((tiles_upper_bound(c, n_rows, 16 * MOST) + 7) / 8 * 8);
-  hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, KS, MOST, FAR>), dim3((unsigned)c.grid_padded), dim3(64 * KS * W4T_WAVES), 0, s, c, in, out);
+  hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, KS, MOST>), dim3((unsigned)c.grid_padded), dim3(64 * KS * W4T_WAVES), 0, s, c, in, out);
 }
 
 template <bool GATEUP>
 static void launch_stage_tile_w4(TiledCtx c, int n_rows, const bf16_t* in, bf16_t* out, hipStream_t s) {
   const int units_total = (GATEUP ? 2 * c.ffn : c.hidden) / 16;
   c.n_tiles_n = (units_total + W4T_UNITS - 1) / W4T_UNITS;
-  // (an input of 4 GiB or more is that many tokens that the tiles are always enough for two blocks per CU)
-  if constexpr (GATEUP) {
-    if (c.row_map && (size_t)(n_rows / c.map_div) * (size_t)c.hidden * 2 > 0xffffffffu)
-      return launch_tiles_w4<true, 1, W4T_FM_MAX, true>(c, n_rows, in, out, s);
-  }
   const long busy = std::min(c.n_experts, n_rows), per_expert = (n_rows + c.n_experts - 1) / c.n_experts;
   auto per = [](long rows, int most) { return (rows + 16 * most - 1) / (16 * most); };  // m-tiles of at most `most` fragments
-  // tiles when every expert has as many rows, and when some have twice as many (but no more than all rows can make)
+  // tiles when every expert has as many rows, or the few more that random routing gives some, and when some have twice as
+  // many (but no more than all rows can make)
   auto even = [&](int most) { return busy * per(per_expert, most) * (long)c.n_tiles_n; };
+  const long likely = busy == 1 ? n_rows : per_expert + (long)(2.0 * std::sqrt((double)per_expert));
+  const long likely6 = busy * per(likely, 6) * (long)c.n_tiles_n;
   auto uneven = [&](int most) {
     const long all = busy == 1 ? per(n_rows, most) : std::min(busy * per(2 * per_expert, most), n_rows / (16 * most) + busy);
     return all * (long)c.n_tiles_n;
@@ -404,11 +402,31 @@ static void launch_stage_tile_w4(TiledCtx c, int n_rows, const bf16_t* in, bf16_
   // average.  Layers, six at most -> now: one expert of 1024 x 512, 64 tokens 36.9 -> 26.9 us; one of 2048 x 2816, 301 tokens
   // 57.9 -> 42.7 us (tiles of 64 rows and 256 columns before either: 46.5 and 63 us); one of 3584 x 20480, 1003 tokens,
   // down launch 287 -> 211 us (200).
-  if (uneven(2) <= 256) launch_tiles_w4<GATEUP, 2, 2, false>(c, n_rows, in, out, s);
-  else if (uneven(4) <= 256) launch_tiles_w4<GATEUP, 2, 4, false>(c, n_rows, in, out, s);
-  else if (even(6) <= 256) launch_tiles_w4<GATEUP, 2, 6, false>(c, n_rows, in, out, s);
-  else if (uneven(4) <= 512) launch_tiles_w4<GATEUP, 1, 4, false>(c, n_rows, in, out, s);
-  else launch_tiles_w4<GATEUP, 1, 6, false>(c, n_rows, in, out, s);
+  // (Two sets with six fragments need a K range to share: below 16 scale groups two blocks of four are faster, one expert
+  // of 1024 x 512, 3000 tokens 50 -> 44 us.)
+  const bool two6 = likely6 <= 256 && ((GATEUP ? c.hidden : c.ffn) >= 16 * W4_GROUP || uneven(4) > 512);
+  const int most = uneven(2) <= 256 ? 2 : uneven(4) <= 256 || (!two6 && uneven(4) <= 512) ? 4 : 6;
+  const bool two_sets = most == 6 ? two6 : uneven(most) <= 256;
+  // Tiles of 64 x 256 (one block per CU) for experts of 320 rows or more, where the activations are read often enough to
+  // count, unless they make more rounds: a round of them takes about 0.92 of one of two blocks of 4 fragments.  Launches,
+  // these tiles / the others: 8 experts of 4096 x 14336, 375 rows each, gate/up 853 / 879 us and down 502 / 493, 512 rows
+  // 1156 / 1251 and 630 / 617, 1024 rows 2329 / 2467 and 1168 / 1263, but 250 rows 649 / 633 and 387 / 323; one expert of
+  // 3584 x 20480, 2048 rows 755 / 790 and 380 / 461; one of 2048 x 2816, 1000 rows (layer) 85 / 67.  They also take tokens of
+  // 4 GiB or more, which the others cannot address through a row map.
+  const bool far = GATEUP && c.row_map && (size_t)(n_rows / c.map_div) * (size_t)c.hidden * 2 > 0xffffffffu;
+  const long wide = busy * ((per_expert + W4_WIDE_ROWS - 1) / W4_WIDE_ROWS) * ((16l * units_total + W4_WIDE_COLUMNS - 1) / W4_WIDE_COLUMNS);
+  const double rounds_wide = 0.92 * (double)((wide + 255) / 256);
+  const double rounds = (most == 4 ? 1.0 : 1.41) * (double)((even(most) + 511) / 512);
+  if (far || (per_expert >= 320 && !two_sets && rounds_wide < rounds)) return launch_stage_w4_wide(GATEUP, c, n_rows, in, out, s);
+  if (two_sets) {
+    if (most == 2) launch_tiles_w4<GATEUP, 2, 2>(c, n_rows, in, out, s);
+    else if (most == 4) launch_tiles_w4<GATEUP, 2, 4>(c, n_rows, in, out, s);
+    else launch_tiles_w4<GATEUP, 2, 6>(c, n_rows, in, out, s);
+  } else if (most == 4) {
+    launch_tiles_w4<GATEUP, 1, 4>(c, n_rows, in, out, s);
+  } else {
+    launch_tiles_w4<GATEUP, 1, 6>(c, n_rows, in, out, s);
+  }
 }
 
 int launch_ffn_tiled_w4(const FfnArgs& a) {

@@ -179,4 +179,8 @@ static inline long tiles_upper_bound(const TiledCtx& c, int n_rows, int bm) {
   return ((long)n_rows / bm + (c.n_experts < n_rows ? c.n_experts : n_rows)) * c.n_tiles_n;
 }
 
+// 4-bit gate/up or down launch in tiles of W4_WIDE_ROWS x W4_WIDE_COLUMNS (ffn_tiled_w4_wide.hip)
+constexpr int W4_WIDE_ROWS = 64, W4_WIDE_COLUMNS = 256;
+void launch_stage_w4_wide(bool gate_up, const TiledCtx& c, int n_rows, const bf16_t* in, bf16_t* out, hipStream_t s);
+
 }  // namespace hmoe

@@ -86,9 +86,10 @@ def test_ffn_f32_reference_is_the_general_kernels(hm, hidden, ffn, counts):
 @pytest.mark.parametrize("hidden,ffn,counts", [
     (256, 128, [1, 16, 17, 33, 49, 80, 81, 96]), (128, 256, [97, 0, 112, 113]), (384, 640, [193, 96, 290]),
     (512, 384, [64, 65]), (1152, 128, [95, 3]),
-    # two sets of waves with tiles of at most 2, 4 and 6 fragments, one set with at most 4
+    # (the cases above take tiles of at most 2 fragments; gate/up of these of at most 2, 2, 4, then one set of waves with 4,
+    # then two with 6)
     (256, 256, [33, 64, 65]), (640, 384, [129]), (1024, 1920, [64, 0, 129, 33, 16]), (1024, 4224, [128, 65]), (512, 8192, [256]),
-    (640, 4096, [129, 128, 65, 1]),
+    (128, 4096, [96, 33, 81, 49]), (2048, 4096, [96, 33, 81, 17]), (2176, 4096, [97, 17, 64, 80]), (2304, 4096, [49, 81, 90, 65]),
     (384, 16768, [100]), (512, 4224, [1, 17, 33, 49, 80, 81, 96, 97]), (640, 4224, [97, 96, 2, 16, 47, 65, 81, 33]),
     (896, 4224, [193, 1, 17, 33, 49, 80, 81, 96]), (4096, 128, [97, 33, 16, 50, 81, 1, 2, 64, 96]), (4096, 640, [96, 34, 17, 51, 80, 2, 3, 64, 65]),
 ])
@@ -151,6 +152,24 @@ def test_dense_down_tiles(hm, monkeypatch, rows, hidden, ffn):
     some = np.unique(np.r_[0:min(rows, 260):37, rows - 3:rows])
     ref = orc.expert_ffn(wl.as_f64(x[some]), *(wl.as_f64(m) for m in lay.experts[0]))
     assert max_rel_err(got[some], ref) < TOL[wl.BF16]
+
+
+# experts of 320 rows and more on average: tiles of 64 x 256 where they make fewer rounds than the others.  Ragged heights, column
+# tiles that are half full (gate/up and down), one to seven scale groups (four are in flight).
+@pytest.mark.parametrize("hidden,ffn,counts", [(128, 8192, [1000, 40, 0, 300]), (384, 16768, [700]), (640, 8320, [512, 129]),
+                                               (896, 4224, [650, 1, 700, 0]), (4224, 128, [1900, 77, 64])])
+def test_ffn_w4_wide_tiles(hm, hidden, ffn, counts):
+    print("w4 wide tiles", hidden, ffn, counts, flush=True)
+    shape, lay, offsets, x = case(wl.BF16, hidden, ffn, counts)
+    E = len(counts)
+    d = hm.make_desc(hidden, ffn, E, min(2, E), E, hm.HMOE_BF16_W4)
+    got = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_TILED)
+    some = np.unique(np.concatenate([np.r_[lo:hi:61, max(lo, hi - 2):hi] for lo, hi in zip(offsets[:-1], offsets[1:])])).astype(int)
+    for e, (lo, hi) in enumerate(zip(offsets[:-1], offsets[1:])):
+        rows = some[(some >= lo) & (some < hi)]
+        if len(rows):
+            ref = orc.expert_ffn(wl.as_f64(x[rows]), *(w4.dequantize_w4(*w4.quantize_w4(wl.as_f32(m))) for m in lay.experts[e]))
+            assert max_rel_err(got[rows], ref) < TOL[wl.BF16], e
 
 
 @pytest.fixture(scope="module")
