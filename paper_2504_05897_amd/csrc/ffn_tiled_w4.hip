@@ -359,7 +359,7 @@ __global__ __launch_bounds__(64 * W4T_WAVES * KS, 2) void ffn_tile_w4_kernel(Til
   static_assert(MOST <= W4T_FM_MAX, "");
   __shared__ W4TileLds lds[KS];
   TileLoc loc;
-  if (!locate_tile<16 * MOST>(c, loc)) return;  // uniform over the block
+  if (!(c.spread ? locate_tile_spread<16 * MOST>(c, loc) : locate_tile<16 * MOST>(c, loc))) return;  // uniform over the block
   // the expert's fragments dealt evenly to its m-tiles
   const int mts = (loc.m_rows + 16 * MOST - 1) / (16 * MOST);
   const int frags = (loc.m_rows + 15) / 16, base = frags / mts, rem = frags % mts;
@@ -375,7 +375,9 @@ __global__ __launch_bounds__(64 * W4T_WAVES * KS, 2) void ffn_tile_w4_kernel(Til
 
 template <bool GATEUP, int KS, int MOST>
 static void launch_tiles_w4(TiledCtx c, int n_rows, const bf16_t* in, bf16_t* out, hipStream_t s) {
-  c.grid_padded = (int)((tiles_upper_bound(c, n_rows, 16 * MOST) + 7) / 8 * 8);
+  // (one expert's tiles are as high as each other, and few columns would be too few to divide)
+  c.spread = c.n_experts > 1 && (long)std::min(c.n_experts, n_rows) * c.n_tiles_n >= 64;
+  c.grid_padded = (int)(c.spread ? blocks_spread(c, n_rows, 16 * MOST) : (tiles_upper_bound(c, n_rows, 16 * MOST) + 7) / 8 * 8);
   hipLaunchKernelGGL((ffn_tile_w4_kernel<GATEUP, KS, MOST>), dim3((unsigned)c.grid_padded), dim3(64 * KS * W4T_WAVES), 0, s, c, in, out);
 }
 

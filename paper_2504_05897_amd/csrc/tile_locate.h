@@ -20,6 +20,7 @@ struct TiledCtx {
   // map_div as a multiplication: for 0 <= x < 2^31, x / map_div == umulhi(x, map_mul) >> map_shift (map_div >= 2)
   uint32_t map_mul = 0;
   int map_shift = 0;
+  bool spread = false;  // the 4-bit tiles: which division of the list among the XCDs
 };
 
 // Division by the invariant map_div (Granlund and Montgomery's round-up multiplier): with l = ceil(log2 d) and
@@ -98,6 +99,70 @@ __device__ __forceinline__ bool locate_tile(const TiledCtx& c, TileLoc& t) {
     }
   }
   return false;
+}
+
+// Another division of the list among the XCDs, for tiles that cost as much as their expert has rows: column i of the list (an
+// n-tile of a busy expert, with all its m-tiles, which share a weight panel) goes to XCD i % 8.  With contiguous eighths the
+// XCD that holds the busiest experts finishes last: 64 experts of 2048 x 1408 in 4 bits, top 6, popularity falling with the
+// id, shared 2816: 200 tokens 154 -> 107 us, 1024 tokens 290 -> 246 us.  Activations are read by all XCDs instead of one, and
+// every XCD works on the same expert at a time (even routing: 8 experts of 4096 x 14336, 301 tokens 342 -> 338 us; 60 of 1024 x
+// 512, top 4, 400 tokens 38 -> 40 us).
+template <int BM>
+__device__ __forceinline__ bool locate_tile_spread(const TiledCtx& c, TileLoc& t) {
+  constexpr int CH = HMOE_MAX_EXPERTS / 64;
+  const int lane = threadIdx.x % 64;
+  const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
+  int first[CH], rows[CH], incl[CH], slot[CH], col0[CH], cols[CH];
+  int total = 0, columns = 0;  // tiles of this XCD; columns of the whole list
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    first[j] = rows[j] = col0[j] = cols[j] = 0;
+    slot[j] = -1;
+    incl[j] = total;
+    if (j * 64 < c.n_experts) {  // uniform
+      const int i = j * 64 + lane;
+      if (i < c.n_experts) slot[j] = c.slot_of[i];
+      if (i < c.n_experts && ((c.active.w[j] >> lane) & 1ull) && slot[j] >= 0) {
+        first[j] = c.offsets[i];
+        rows[j] = c.offsets[i + 1] - first[j];
+      }
+      const uint64_t busy = __ballot(rows[j] > 0);
+      const int before = columns + __popcll(busy & ((1ull << lane) - 1ull)) * c.n_tiles_n;
+      columns += __popcll(busy) * c.n_tiles_n;
+      col0[j] = (xcd - before) & 7;  // the expert's first column on this XCD; every eighth follows
+      cols[j] = rows[j] > 0 && col0[j] < c.n_tiles_n ? (c.n_tiles_n - col0[j] + 7) / 8 : 0;
+      int v = cols[j] * ((rows[j] + BM - 1) / BM);
+#pragma unroll
+      for (int d = 1; d < 64; d *= 2) {
+        const int below = __shfl_up(v, d);
+        if (lane >= d) v += below;
+      }
+      incl[j] = total + v;
+      total += __shfl(v, 63);
+    }
+  }
+  if (idx >= total) return false;
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    const unsigned long long past = __ballot(incl[j] > idx);
+    if (past) {
+      const int src = __ffsll((long long)past) - 1;
+      t.e = j * 64 + src;
+      t.row_first = __builtin_amdgcn_readfirstlane(__shfl(first[j], src));
+      t.m_rows = __builtin_amdgcn_readfirstlane(__shfl(rows[j], src));
+      t.slot = __builtin_amdgcn_readfirstlane(__shfl(slot[j], src));
+      const int mts = (t.m_rows + BM - 1) / BM;
+      const int within = __builtin_amdgcn_readfirstlane(idx - (__shfl(incl[j], src) - __shfl(cols[j], src) * mts));
+      t.nt = __builtin_amdgcn_readfirstlane(__shfl(col0[j], src)) + 8 * (within / mts);
+      t.mt = within % mts;
+      return true;
+    }
+  }
+  return false;
+}
+// blocks that cover it: every XCD gets at most this many eighths of an expert's columns
+static inline long blocks_spread(const TiledCtx& c, int n_rows, int bm) {
+  return 8 * ((c.n_tiles_n + 7l) / 8) * ((long)n_rows / bm + (c.n_experts < n_rows ? c.n_experts : n_rows));
 }
 
 // The same tile list for a block that works through several tiles: the per-expert prefix sums are computed once into

@@ -90,6 +90,8 @@ def test_ffn_f32_reference_is_the_general_kernels(hm, hidden, ffn, counts):
     # then two with 6)
     (256, 256, [33, 64, 65]), (640, 384, [129]), (1024, 1920, [64, 0, 129, 33, 16]), (1024, 4224, [128, 65]), (512, 8192, [256]),
     (128, 4096, [96, 33, 81, 49]), (2048, 4096, [96, 33, 81, 17]), (2176, 4096, [97, 17, 64, 80]), (2304, 4096, [49, 81, 90, 65]),
+    # idle experts between busy ones, more than 64 and 128 of them, columns that eight does not divide
+    (256, 1152, [i % 7 * 20 if i % 3 else 0 for i in range(130)]), (384, 640, [0, 130, 0, 0, 33, 300, 0, 1, 96, 97, 0, 5, 20, 64, 0, 2]),
     (384, 16768, [100]), (512, 4224, [1, 17, 33, 49, 80, 81, 96, 97]), (640, 4224, [97, 96, 2, 16, 47, 65, 81, 33]),
     (896, 4224, [193, 1, 17, 33, 49, 80, 81, 96]), (4096, 128, [97, 33, 16, 50, 81, 1, 2, 64, 96]), (4096, 640, [96, 34, 17, 51, 80, 2, 3, 64, 65]),
 ])
