@@ -296,6 +296,7 @@ __global__ __launch_bounds__(64 * NW) void permute_rank_kernel(const int32_t* __
 // route kernel plus the one-block rank kernel are faster than the single launch (measured at 512
 // tokens: 10 us against 25 us).
 constexpr int ROUTE_PERMUTE_SMALL_T = 64;
+constexpr int ROUTE_APART_T = 2048;  // hmoe_router_route_permute: larger batches were routed by hmoe_route, with its checks
 
 // Small batches (T <= 64 and A <= 1024, every decode shape): routing and permutation in ONE block and one launch.
 // The block first routes all tokens (lane groups as in hmoe_route; the next group's logits are on their way while one
@@ -558,6 +559,10 @@ extern "C" int32_t hmoe_router_route_permute(const hmoe_layer_desc* desc, const 
   if ((T > ROUTER_SMALL_T || A > PB_CHUNK) && desc->dtype != HMOE_F32 && desc->hidden % 16 == 0 && x && w_g && logits && topk_idx &&
       topk_w && aligned16(x) && aligned16(w_g)) {
     // logits and routing in one launch, then the permutation
+    // (pointers that hmoe_route refuses; batches that have always been routed with their logits run with any)
+    if (T > ROUTE_APART_T && ((reinterpret_cast<uintptr_t>(logits) | reinterpret_cast<uintptr_t>(topk_idx) |
+                               reinterpret_cast<uintptr_t>(topk_w)) & 3u))
+      return HMOE_ERR_INVALID_ARG;
     const int E = desc->n_experts, K = desc->top_k;
     const int tpb = router_tokens_per_block(T);
     const dim3 grid((unsigned)((T + tpb - 1) / tpb));

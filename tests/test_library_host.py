@@ -148,3 +148,14 @@ def test_new_entry_points_reject_bad_arguments_on_the_host(hm):
     sargs[5], sargs[10], sargs[11] = 0, 0, 0
     assert lib.hmoe_expert_ffn_staged(*sargs) == hm.HMOE_ERR_INVALID_ARG          # no cache, no counts, no plan arrays
     assert lib.hmoe_cache_set_layer(None, ctypes.byref(ok)) == hm.HMOE_ERR_INVALID_ARG      # no cache
+
+
+@pytest.mark.parametrize("T,shift", [(2049, (2, 0, 0)), (4096, (0, 1, 0)), (40000, (0, 0, 3))])
+def test_fused_front_end_refuses_what_hmoe_route_refuses(hm, T, shift):
+    """Logits, ids or weights that are not aligned to their four bytes: refused before anything is enqueued."""
+    d = hm.make_desc(2048, 64, 64, 6, 64, hm.HMOE_BF16)
+    at = [4096 * (i + 1) for i in range(9)]   # addresses the host only looks at
+    logits, idx, w = (at[2 + i] + shift[i] for i in range(3))
+    rc = hm._lib.hmoe_router_route_permute(ctypes.byref(d), at[0], at[1], T, logits, idx, w, at[5], at[6], at[7], None, at[8],
+                                           1 << 30, None)
+    assert rc == hm.HMOE_ERR_INVALID_ARG
