@@ -102,3 +102,46 @@ def test_equal_logits_go_to_the_smaller_id(hm, T, E, K):
         torch.cuda.synchronize()
         assert np.array_equal(idx.cpu().numpy(), ridx) and np.abs(w.cpu().numpy() - rw).max() < 1e-6
         assert np.array_equal(offs.cpu().numpy(), ro) and np.array_equal(perm.cpu().numpy(), rp) and np.array_equal(inv.cpu().numpy(), ri)
+
+
+@pytest.mark.parametrize("T,E,K", [(3, 8, 2), (40, 16, 3), (64, 30, 8), (200, 64, 6), (70, 100, 9), (33, 256, 31)])
+def test_masked_and_undefined_logits(hm, T, E, K):
+    """Experts masked with -inf or with the type's lowest value: the choice among the others is the oracle's, a token with fewer
+    unmasked experts than K chooses those first and its masked ones with weight 0, no expert twice.  Logits that are NaN or +inf
+    leave the result open, but ids stay ids and the permutation a permutation."""
+    print("masked logits", T, E, K, flush=True)
+    rng = np.random.default_rng(T + E + K)
+    lg = rng.standard_normal((T, E)).astype(np.float32)
+    masked = rng.random((T, E)) < 0.5
+    masked[:, :1] = False
+    lg[masked] = np.where(rng.random((T, E)) < 0.5, -np.inf, np.finfo(np.float32).min)[masked]
+    odd = lg.copy()
+    odd[rng.random((T, E)) < 0.2] = np.nan
+    odd[::3, -1] = np.inf
+    odd[1::3, 0] = np.array([0xFFC00000], np.uint32).view(np.float32)[0]  # NaN with its sign bit set
+    d = hm.make_desc(64, 64, E, K, E, hm.HMOE_BF16)
+    ws_bytes = hm.hmoe_permute_workspace_bytes(d, T)
+    for values in (lg, odd):
+        for fused in (False, True):
+            idx = torch.full((T, K), -5, dtype=torch.int32, device=DEV)
+            w = torch.zeros(T, K, dtype=torch.float32, device=DEV)
+            offs = torch.full((E + 1,), -7, dtype=torch.int32, device=DEV)
+            perm, inv = (torch.full((T * K,), -7, dtype=torch.int32, device=DEV) for _ in range(2))
+            ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+            if fused:
+                hm.hmoe_route_permute(d, to_device(values), T, idx, w, offs, perm, inv, None, ws, ws_bytes)
+            else:
+                hm.hmoe_route(d, to_device(values), T, idx, w)
+                hm.hmoe_permute(d, idx, T, None, None, offs, perm, inv, None, ws, ws_bytes)
+            torch.cuda.synchronize()
+            got = idx.cpu().numpy()
+            assert got.min() >= 0 and got.max() < E
+            ro, rp, ri = orc.permute(got, E)
+            assert np.array_equal(offs.cpu().numpy(), ro) and np.array_equal(perm.cpu().numpy(), rp) and np.array_equal(inv.cpu().numpy(), ri)
+            if values is lg:
+                assert all(len(set(row)) == K for row in got.tolist())
+                order = np.argsort(-values.astype(np.float64), axis=1, kind="stable")[:, :K]   # equal logits: smaller id first
+                assert np.array_equal(got, order)
+                chosen = np.take_along_axis(values, got, 1).astype(np.float64)
+                ref = np.exp(chosen - chosen[:, :1])
+                assert np.abs(w.cpu().numpy() - ref / ref.sum(1, keepdims=True)).max() < 1e-6

@@ -139,7 +139,7 @@ def test_router_logits(hm, name, T):
 
 @pytest.mark.parametrize("E,H", [(8, 4096), (60, 128), (64, 2048), (100, 3584), (256, 64)])
 def test_router_logits_decode_batches(hm, E, H):
-    """T <= 8 takes the one-block kernel: against the oracle, and the same bits as the many-token kernel
+    """T <= 16 takes the one-block kernel: against the oracle, and the same bits as the many-token kernel
     gives for the same rows."""
     say("router_logits small", E, H)
     rng = np.random.default_rng(E + H)
@@ -568,7 +568,7 @@ def test_route_permute_fused_equals_the_two_calls(hm, T, E, K):
                                      (0, 8, 2, 64), (40, 128, 8, 64), (100, 256, 32, 64), (300, 200, 9, 192),
                                      (1024, 64, 6, 2048), (2048, 64, 8, 3584), (2049, 64, 8, 128)])
 def test_front_end_fused_equals_the_separate_calls(hm, T, E, K, H):
-    """hmoe_router_route_permute (one launch for bf16, T <= 8; the separate calls otherwise) writes the same
+    """hmoe_router_route_permute (one launch for bf16, T <= 16; logits and routing in one, then the permutation, beyond) writes the same
     bits as hmoe_router_logits + hmoe_route + hmoe_permute, and the integers the oracle derives from them."""
     say("router_route_permute", T, E, K, H)
     rng = np.random.default_rng(T + E + K + H)
