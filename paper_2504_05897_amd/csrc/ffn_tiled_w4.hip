@@ -19,11 +19,13 @@
 //     per accumulator register.
 //   * What bounds it: the matrix instructions and the vector ALU instructions of a SIMD hardly overlap, so a step takes
 //     about the sum of both (5 fragments: 48 and 120), and with few rows the trip to memory that a step waits for.
+//   * A tile costs as much as its expert has rows, so the n-tiles of every expert are dealt to the XCDs in turn
+//     (locate_tile_spread).
 //   * Rows past the end of the expert and units past the end of the matrix are computed from clamped
 //     addresses and never stored.
-// Measured (8 experts of 4096 x 14336, top 2; gate/up and down launch, before -> now): 65 tokens 187 -> 118 and 145 -> 66 us,
-// 301 tokens 347 -> 262 and 164 -> 137 us, 1000 tokens 666 -> 698 and 413 -> 357 us (0.67 PFLOP/s; the card's large bf16
-// matrix product reaches 1.19).
+// Measured (8 experts of 4096 x 14336, top 2; gate/up and down launch, tiles of 64 x 256 -> these): 65 tokens 187 -> 118 and
+// 145 -> 66 us, 301 tokens 347 -> 262 and 164 -> 137 us, 1003 tokens 649 -> 633 and 387 -> 323 us (0.74 PFLOP/s).  From 320
+// rows per expert on the former are the faster ones (ffn_tiled_w4_wide.hip, chosen in launch_stage_tile_w4).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
