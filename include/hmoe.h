@@ -386,6 +386,23 @@ int32_t hmoe_expert_ffn_combine(
     void* shared_workspace, size_t shared_workspace_bytes, void* y, void* sync, size_t sync_bytes, int32_t path, void* stream);
 
 /* ------------------------------------------------------------------------------------
+ * A whole layer from router logits to y in one call: stands for
+ *     hmoe_route_permute(desc, logits, T, topk_idx, topk_w, expert_offsets, perm, inv_perm, NULL, perm_workspace, ...)
+ *     hmoe_expert_ffn_grouped_with_shared(...), or hmoe_expert_ffn_grouped_gather(...) when shared_desc is NULL
+ *     hmoe_combine(desc, o_perm, inv_perm, topk_w, o_shared, T, y)
+ * with the same bits in every output.  For decode batches of bf16 layers (T <= 8, T*K <= 64, path resolves to
+ * HMOE_FFN_SKINNY) the routing is part of the FFN's first launch: its blocks work the choice out from the logits
+ * themselves, and one more block writes topk_idx, topk_w, expert_offsets, perm and inv_perm.
+ * logits must not overlap any output.  Arguments and errors as in the calls above.
+ */
+int32_t hmoe_route_ffn_combine(
+    const hmoe_layer_desc* desc, hmoe_cache* cache, const void* x, const float* logits, int32_t T, int32_t* topk_idx, float* topk_w,
+    int32_t* expert_offsets, int32_t* perm, int32_t* inv_perm, void* perm_workspace, size_t perm_workspace_bytes, void* o_perm,
+    void* workspace, size_t workspace_bytes, const hmoe_layer_desc* shared_desc, hmoe_cache* shared_cache,
+    const int32_t* shared_offsets, void* o_shared, void* shared_workspace, size_t shared_workspace_bytes, void* y, int32_t path,
+    void* stream);
+
+/* ------------------------------------------------------------------------------------
  * Hybrid CPU-GPU scheduling simulation (Section IV-B).  HOST ONLY: no device work, no stream.
  * The activated experts of a layer (load > 0) are placed on three timelines -- CPU compute, GPU
  * compute, host-to-GPU transfer -- by the paper's priority rules: the GPU takes experts whose weights

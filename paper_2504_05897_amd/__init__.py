@@ -41,6 +41,7 @@ EXPORTS = [
     "hmoe_cache_evict", "hmoe_cache_pin_slot", "hmoe_cache_stage", "hmoe_cache_plan",
     "hmoe_ffn_workspace_bytes", "hmoe_expert_ffn_grouped", "hmoe_expert_ffn_grouped_gather", "hmoe_route_permute",
     "hmoe_router_route_permute", "hmoe_expert_ffn_grouped_with_shared", "hmoe_ffn_combine_sync_bytes", "hmoe_expert_ffn_combine",
+    "hmoe_route_ffn_combine",
     "hmoe_expert_ffn_staged",
     "hmoe_combine",
     "hmoe_cache_set_policy", "hmoe_cache_update_scores", "hmoe_cache_get_scores", "hmoe_cache_set_layer",
@@ -111,6 +112,8 @@ def _load() -> ctypes.CDLL:
     lib.hmoe_ffn_combine_sync_bytes.restype = sz
     lib.hmoe_ffn_combine_sync_bytes.argtypes = [dp]
     lib.hmoe_expert_ffn_combine.argtypes = [dp, vp, vp, vp, vp, vp, vp, i32, vp, vp, sz, dp, vp, vp, vp, vp, sz, vp, vp, sz, i32, vp]
+    lib.hmoe_route_ffn_combine.argtypes = [dp, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, sz, vp, vp, sz, dp, vp, vp, vp, vp, sz, vp, i32,
+                                           vp]
     lib.hmoe_expert_ffn_staged.argtypes = [dp, vp, vp, vp, vp, i32, vp, vp, vp, vp, sz, i32, vp, vp, vp, vp, vp,
                                            ctypes.POINTER(i32), ctypes.POINTER(ctypes.c_uint64)]
     lib.hmoe_route_permute.argtypes = [dp, vp, i32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
@@ -323,6 +326,16 @@ def hmoe_expert_ffn_combine(desc, cache, x, perm, inv_perm, topk_w, expert_offse
         _ptr(workspace), workspace_bytes, None if shared_desc is None else ctypes.byref(shared_desc), shared_cache,
         _ptr(shared_offsets), _ptr(o_shared), _ptr(shared_workspace), shared_workspace_bytes, _ptr(y), _ptr(sync), sync_bytes,
         path, _stream(stream)), "hmoe_expert_ffn_combine")
+
+
+def hmoe_route_ffn_combine(desc, cache, x, logits, T, topk_idx, topk_w, expert_offsets, perm, inv_perm, perm_workspace,
+                           perm_workspace_bytes, o_perm, workspace, workspace_bytes, shared_desc, shared_cache, shared_offsets,
+                           o_shared, shared_workspace, shared_workspace_bytes, y, path=HMOE_FFN_AUTO, stream=None):
+    _check(_lib.hmoe_route_ffn_combine(
+        ctypes.byref(desc), cache, _ptr(x), _ptr(logits), T, _ptr(topk_idx), _ptr(topk_w), _ptr(expert_offsets), _ptr(perm),
+        _ptr(inv_perm), _ptr(perm_workspace), perm_workspace_bytes, _ptr(o_perm), _ptr(workspace), workspace_bytes,
+        None if shared_desc is None else ctypes.byref(shared_desc), shared_cache, _ptr(shared_offsets), _ptr(o_shared),
+        _ptr(shared_workspace), shared_workspace_bytes, _ptr(y), path, _stream(stream)), "hmoe_route_ffn_combine")
 
 
 def hmoe_route_permute(desc, logits, T, topk_idx, topk_w, expert_offsets, perm, inv_perm, h_counts_pinned, workspace,
@@ -574,6 +587,17 @@ class MoELayer:
                     hmoe_expert_ffn_grouped(self.shared_desc, self.shared_cache, x, self.shared_offsets, T, None,
                                             self.o_shared, self.shared_ws, self.shared_ws_bytes, path)
                     self.ev_join.record(self.side_stream)
+        if (logits is not None and self.fused and all_resident and not self.merge_combine
+                and (self.shared_desc is None or merged)):
+            # routing, FFN (routed and shared) and the sum in one call: for decode batches with the routing inside the
+            # FFN's first launch
+            sd = self.shared_desc
+            hmoe_route_ffn_combine(d, self.cache, x, logits, T, self.topk_idx, self.topk_w, self.offsets, self.perm, self.inv_perm,
+                                   self.perm_ws, self.perm_ws_bytes, self.o_perm, self.ffn_ws, self.ffn_ws_bytes, sd,
+                                   None if sd is None else self.shared_cache, None if sd is None else self.shared_offsets,
+                                   o_shared, None if sd is None else self.shared_ws, 0 if sd is None else self.shared_ws_bytes,
+                                   self.y, path)
+            return self.y[:T]
         if logits is None and self.fused:
             hmoe_router_route_permute(d, x, self.w_router, T, self.logits, self.topk_idx, self.topk_w, self.offsets,
                                       self.perm, self.inv_perm, counts, self.perm_ws, self.perm_ws_bytes)

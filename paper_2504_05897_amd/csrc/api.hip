@@ -649,6 +649,65 @@ extern "C" int32_t hmoe_expert_ffn_combine(
   return HMOE_OK;
 }
 
+extern "C" int32_t hmoe_route_ffn_combine(
+    const hmoe_layer_desc* desc, hmoe_cache* cache, const void* x, const float* logits, int32_t T, int32_t* topk_idx, float* topk_w,
+    int32_t* expert_offsets, int32_t* perm, int32_t* inv_perm, void* perm_workspace, size_t perm_workspace_bytes, void* o_perm,
+    void* workspace, size_t workspace_bytes, const hmoe_layer_desc* shared_desc, hmoe_cache* shared_cache,
+    const int32_t* shared_offsets, void* o_shared, void* shared_workspace, size_t shared_workspace_bytes, void* y, int32_t path,
+    void* stream) {
+  int rc = check_desc(desc);
+  if (rc != HMOE_OK) return rc;
+  if (T < 0 || T > 0x7fffffff / desc->top_k || !expert_offsets) return HMOE_ERR_INVALID_ARG;
+  if (T == 0) return HMOE_OK;
+  const int32_t A = T * desc->top_k;
+  if (!logits || !topk_idx || !topk_w || !perm || !inv_perm || !y || !aligned16(y)) return HMOE_ERR_INVALID_ARG;
+  if (shared_desc && !o_shared) return HMOE_ERR_INVALID_ARG;
+  if ((reinterpret_cast<uintptr_t>(logits) | reinterpret_cast<uintptr_t>(topk_idx) | reinterpret_cast<uintptr_t>(topk_w)) & 3u)
+    return HMOE_ERR_INVALID_ARG;
+  // Decode batches of bf16 layers: routing inside the first launch of the FFN.  Everything else, and whatever these
+  // checks refuse: the calls this one stands for, one after the other.
+  if (ffn_skinny_routes(*desc, T) && (!shared_desc || (shared_desc->n_experts == 1 && shared_desc->n_slots == 1 &&
+                                                       shared_desc->top_k == 1 && shared_desc->hidden == desc->hidden &&
+                                                       shared_desc->dtype == desc->dtype))) {
+    FfnArgs routed, dense;
+    bool skip_routed = false, skip_dense = true;
+    int32_t path_routed = path, path_dense = path;
+    rc = ffn_prepare(desc, cache, x, perm, expert_offsets, A, nullptr, 0, o_perm, workspace, workspace_bytes, &path_routed, stream,
+                     &routed, &skip_routed);
+    if (rc == HMOE_OK && shared_desc)
+      rc = ffn_prepare(shared_desc, shared_cache, x, nullptr, shared_offsets, T, nullptr, 0, o_shared, shared_workspace,
+                       shared_workspace_bytes, &path_dense, stream, &dense, &skip_dense);
+    if (rc != HMOE_OK) return rc;
+    if (path_routed == HMOE_FFN_SKINNY && (!shared_desc || (path_dense == HMOE_FFN_SKINNY && shared_cache->slot_of[0] >= 0))) {
+      if (!perm_workspace || perm_workspace_bytes < hmoe_permute_workspace_bytes(desc, T)) return HMOE_ERR_WORKSPACE;
+      if (shared_desc) dense.slots = shared_cache->slots + (size_t)shared_cache->slot_of[0] * shared_cache->slot_bytes;
+      RouteArgs route;
+      route.logits = logits;
+      route.topk_idx = topk_idx;
+      route.topk_w = topk_w;
+      route.offsets = expert_offsets;
+      route.perm = perm;
+      route.inv_perm = inv_perm;
+      route.n_tokens = T;
+      rc = launch_ffn_skinny(routed, shared_desc ? &dense : nullptr, nullptr, &route);
+      if (rc != HMOE_OK) return rc;
+      if ((rc = ffn_record_reads(cache, routed)) != HMOE_OK) return rc;
+      if (shared_desc && (rc = ffn_record_reads(shared_cache, dense)) != HMOE_OK) return rc;
+      return hmoe_combine(desc, o_perm, inv_perm, topk_w, shared_desc ? o_shared : nullptr, T, y, stream);
+    }
+  }
+  rc = hmoe_route_permute(desc, logits, T, topk_idx, topk_w, expert_offsets, perm, inv_perm, nullptr, perm_workspace,
+                          perm_workspace_bytes, stream);
+  if (rc != HMOE_OK) return rc;
+  rc = shared_desc ? hmoe_expert_ffn_grouped_with_shared(desc, cache, x, perm, expert_offsets, A, nullptr, 0, o_perm, workspace,
+                                                         workspace_bytes, shared_desc, shared_cache, shared_offsets, T, o_shared,
+                                                         shared_workspace, shared_workspace_bytes, path, stream)
+                   : hmoe_expert_ffn_grouped_gather(desc, cache, x, perm, expert_offsets, A, nullptr, 0, o_perm, workspace,
+                                                    workspace_bytes, path, stream);
+  if (rc != HMOE_OK) return rc;
+  return hmoe_combine(desc, o_perm, inv_perm, topk_w, shared_desc ? o_shared : nullptr, T, y, stream);
+}
+
 extern "C" int32_t hmoe_expert_ffn_staged(const hmoe_layer_desc* desc, hmoe_cache* cache, const void* x, const int32_t* perm,
                                           const int32_t* expert_offsets, int32_t A, const int32_t* h_counts_pinned,
                                           const void* const* h_packed_pinned, void* o_perm, void* workspace,

@@ -153,10 +153,22 @@ struct CombineArgs {
   unsigned int* tickets = nullptr;   // device counters, zero before and after the call
   int32_t n_tokens = 0;
 };
+// routing inside the decode kernel's first launch: the logits and where the choice and the permutation go
+struct RouteArgs {
+  const float* logits = nullptr;
+  int32_t* topk_idx = nullptr;
+  float* topk_w = nullptr;
+  int32_t* offsets = nullptr;
+  int32_t* perm = nullptr;
+  int32_t* inv_perm = nullptr;
+  int32_t n_tokens = 0;
+};
 int launch_ffn_reference(const FfnArgs& a);
 bool ffn_f32_takes(const hmoe_layer_desc& d, int n_rows);
 int launch_ffn_f32(const FfnArgs& a);
-int launch_ffn_skinny(const FfnArgs& a, const FfnArgs* dense = nullptr, const CombineArgs* combine = nullptr);
+int launch_ffn_skinny(const FfnArgs& a, const FfnArgs* dense = nullptr, const CombineArgs* combine = nullptr,
+                      const RouteArgs* route = nullptr);
+bool ffn_skinny_routes(const hmoe_layer_desc& d, int T);
 int launch_ffn_tiled(const FfnArgs& a);
 int launch_ffn_skinny_w4(const FfnArgs& a);
 int launch_ffn_tiled_w4(const FfnArgs& a);

@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "route_body.h"
 
 namespace hmoe {
 
@@ -54,6 +55,26 @@ struct SkinnyCombine {
   int n_tokens, top_k, on;
 };
 
+// Routing inside the gate/up launch, for a batch of at most 8 tokens and 64 assignments whose router logits are at hand.
+// Every routed block works the choice of all tokens out for itself (a wave per token, no output but LDS), and from it its
+// expert and rows; one extra block (the last grid row) writes what the launches behind this one read.  The routing launch
+// of such a batch is latency only (4 us, and the gap to the next one); in here the trip to memory for the logits takes the
+// place of the trips for offsets, slot and row map, and the shared experts' blocks wait for none of it.  Layer, routing
+// launch -> in here: 64 experts of 2048 x 1408, top 6, 1 / 4 / 8 tokens 39.0 -> 35.3, 60.2 -> 57.0, 72.6 -> 69.6 us; of 3584 x
+// 2560, top 8, 2 / 8 tokens 204 -> 199, 409 -> 403; 200 of 1024 x 512, top 8, 5 tokens 33.7 -> 29.2; 96 of 1024 x 1024, top 8,
+// 8 tokens 47.2 -> 47.6, the only one of 18 that did not gain.  More than 8 tokens would be two to a wave; more than 64
+// assignments no longer fit a lane each.
+struct SkinnyRoute {
+  const float* logits;   // [T, E]
+  int32_t* topk_idx;     // [T, K]
+  float* topk_w;
+  int32_t* offsets;      // [E + 1]
+  int32_t* perm;         // [A]
+  int32_t* inv_perm;
+  int n_tokens, top_k;
+};
+constexpr int SKINNY_ROUTE_TOKENS = 8, SKINNY_ROUTE_ASSIGN = 64;
+
 struct SkinnyCtx {
   const int32_t* offsets;
   const int32_t* slot_of;
@@ -66,6 +87,7 @@ struct SkinnyCtx {
   int map_div;
   SkinnyShared shared;
   SkinnyCombine combine;
+  SkinnyRoute route;
 };
 
 // number of experts that are active, resident and have rows
@@ -98,7 +120,8 @@ __device__ __forceinline__ int nth_busy_expert(const SkinnyCtx& c, int want, int
 
 // GATEUP: in = x_perm [A, H], out = h [A, F];  else: in = h [A, F], out = o_perm [A, H].
 // NW waves per block, MR = rows kept per pass (8 or 32), U = tiles per register set and matrix.
-template <bool GATEUP, int NW, int MR, int U>
+// RV: experts per lane with the routing in this launch (1 up to 64 experts, 2 up to 128, 4 up to 256), or 0: offsets and row map are given.
+template <bool GATEUP, int NW, int MR, int U, int RV = 0>
 __global__ __launch_bounds__(64 * NW) void ffn_skinny_kernel(SkinnyCtx c, const bf16_t* __restrict__ in,
                                                               bf16_t* __restrict__ out) {
   constexpr int NMAT = GATEUP ? 2 : 1;
@@ -111,6 +134,7 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_kernel(SkinnyCtx c, const 
   // that shares the launch.  Everything below is uniform over the block.
   const bool dense = (int)blockIdx.y < c.shared.grid_rows;
   int row_first, row_end, ffn, block_in_matrix;
+  int token = 0;  // RV > 0: input row of this lane's column of the token operand
   const char* slot;
   const int32_t* row_map = nullptr;
   if (dense) {
@@ -121,6 +145,58 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_kernel(SkinnyCtx c, const 
     block_in_matrix = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
     in = GATEUP ? c.shared.x : c.shared.h;
     out = GATEUP ? c.shared.h : c.shared.o;
+  } else if constexpr (RV > 0) {
+    static_assert(GATEUP && MR == 8 && NW >= SKINNY_ROUTE_TOKENS, "");
+    __shared__ int32_t chosen[SKINNY_ROUTE_ASSIGN];
+    __shared__ uint8_t named[NW][64 * RV];  // a wave's own: experts that some token names
+    const SkinnyRoute& rt = c.route;
+    int slot_of[RV];
+#pragma unroll
+    for (int i = 0; i < RV; ++i) named[wave][i * 64 + lane] = 0;
+#pragma unroll
+    for (int i = 0; i < RV; ++i) slot_of[i] = i * 64 + lane < c.n_experts ? c.slot_of[i * 64 + lane] : -1;
+    const bool writes = blockIdx.y == gridDim.y - 1;  // the extra block
+    if (writes && blockIdx.x > 0) return;
+    if (wave < rt.n_tokens) {
+      uint32_t key[RV];
+      load_keys<64, RV>(rt.logits, c.n_experts, wave, true, lane, key);
+      if (writes) route_keys<64, RV>(key, c.n_experts, rt.top_k, wave, true, lane, rt.topk_idx, rt.topk_w, chosen);
+      else route_keys<64, RV, false>(key, c.n_experts, rt.top_k, wave, true, lane, nullptr, nullptr, chosen);
+    }
+    __syncthreads();
+    const int n_assign = rt.n_tokens * rt.top_k;
+    if (writes) {
+      if (wave == 0) permute_rank_one_wave<RV>(chosen, n_assign, c.n_experts, rt.offsets, nullptr, rt.perm, rt.inv_perm);
+      return;
+    }
+    // The block's expert: the want-th that is active, resident and named.  (LDS serves a wave's accesses in order.)
+    const int mine = lane < n_assign ? chosen[lane] : 64 * RV;
+    if (lane < n_assign) named[wave][mine] = 1;
+    int want = (int)blockIdx.y - c.shared.grid_rows, e = -1, s = -1;
+#pragma unroll
+    for (int i = 0; i < RV; ++i) {
+      uint64_t m = __ballot(named[wave][i * 64 + lane] && slot_of[i] >= 0 && ((c.active.w[i] >> lane) & 1ull));
+      const int n = __popcll(m);
+      if (e < 0 && want < n) {  // uniform
+        for (int k = 0; k < want; ++k) m &= m - 1;
+        const int l = __ffsll((long long)m) - 1;
+        e = i * 64 + l;
+        s = __builtin_amdgcn_readlane(slot_of[i], l);
+      }
+      want -= n;
+    }
+    if (e < 0) return;  // uniform over the block
+    row_first = __popcll(__ballot(mine < e));
+    uint64_t assigned = __ballot(mine == e);  // its assignments in ascending order are its rows
+    row_end = row_first + __popcll(assigned);
+    for (int r = 0; assigned; ++r) {
+      const int a = __ffsll((long long)assigned) - 1;
+      assigned &= assigned - 1;
+      if (lane % 32 == r) token = a / rt.top_k;
+    }
+    ffn = c.ffn;
+    slot = c.slots + (size_t)s * c.slot_bytes;
+    block_in_matrix = blockIdx.x;
   } else {
     const int e = nth_busy_expert(c, (int)blockIdx.y - c.shared.grid_rows, lane);
     if (e < 0) return;
@@ -147,7 +223,9 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_kernel(SkinnyCtx c, const 
   for (int row0 = row_first; row0 < row_end; row0 += MR) {
     const int rows = min(MR, row_end - row0);
     const bool has_row = col < rows;
-    const int in_row = GATEUP ? mapped_row(row_map, c.map_div, row0 + (has_row ? col : 0)) : row0 + (has_row ? col : 0);
+    int in_row = row0 + (has_row ? col : 0);
+    if (RV > 0 && !dense) in_row = token;  // (at most 8 rows: a single pass)
+    else if (GATEUP) in_row = mapped_row(row_map, c.map_div, in_row);
     const u32x4* xin = (const u32x4*)(in + (size_t)in_row * K) + half;
 
     u32x4 wa[2][U], wb[2][U], xa[2][U];
@@ -346,16 +424,34 @@ static void launch_stage(SkinnyCtx c, int n_groups, int busy_max, int max_rows, 
   (max_rows > 8 ? pick<GATEUP, 32>(shape) : pick<GATEUP, 8>(shape))(c, grid, in, out, s);
 }
 
+// The gate/up launch with the routing inside (SkinnyRoute): a last grid row for the block that writes the permutation.
+template <int RV>
+static void launch_gate_up_routed(SkinnyCtx c, int n_groups, int busy_max, int n_groups_dense, const bf16_t* in, bf16_t* out,
+                                  hipStream_t s) {
+  c.gpb = 1;
+  c.shared.grid_rows = (n_groups_dense + n_groups - 1) / n_groups;
+  const dim3 grid((unsigned)n_groups, (unsigned)(c.shared.grid_rows + busy_max + 1));
+  if ((long)n_groups * busy_max + n_groups_dense < 200)   // as in launch_stage
+    hipLaunchKernelGGL((ffn_skinny_kernel<true, 16, 8, 2, RV>), grid, dim3(1024), 0, s, c, in, out);
+  else
+    hipLaunchKernelGGL((ffn_skinny_kernel<true, 8, 8, 2, RV>), grid, dim3(512), 0, s, c, in, out);
+}
+
+bool ffn_skinny_routes(const hmoe_layer_desc& d, int T) {
+  return d.dtype == HMOE_BF16 && T <= SKINNY_ROUTE_TOKENS && T * d.top_k <= SKINNY_ROUTE_ASSIGN && !getenv("HMOE_SKINNY");
+}
+
 // dense (or NULL): a dense FFN of the same hidden size over dense->n_rows rows (one resident expert: weights
 // at dense->slots, offsets {0, n_rows} implied), computed by extra blocks of the same two launches.
-int launch_ffn_skinny(const FfnArgs& a, const FfnArgs* dense, const CombineArgs* combine) {
+// route (or NULL; ffn_skinny_routes): the first launch routes as well, and a.offsets and a.row_map are its outputs.
+int launch_ffn_skinny(const FfnArgs& a, const FfnArgs* dense, const CombineArgs* combine, const RouteArgs* route) {
   const hmoe_layer_desc& d = *a.desc;
   if (d.dtype != HMOE_BF16) return HMOE_ERR_UNSUPPORTED;
   if (dense && (dense->desc->dtype != HMOE_BF16 || dense->desc->hidden != d.hidden)) return HMOE_ERR_UNSUPPORTED;
   if (dense && dense->n_rows == 0) dense = nullptr;
   if (combine && a.n_rows == 0) return HMOE_ERR_INVALID_ARG;  // without routed rows nothing would draw the tickets
   if (a.n_rows == 0 && !dense) return HMOE_OK;
-  SkinnyCtx c{a.offsets, a.slot_of, a.slots, a.slot_bytes, a.active, d.n_experts, d.hidden, d.ffn, 1, a.row_map, a.map_div, {}, {}};
+  SkinnyCtx c{a.offsets, a.slot_of, a.slots, a.slot_bytes, a.active, d.n_experts, d.hidden, d.ffn, 1, a.row_map, a.map_div, {}, {}, {}};
   int ffn_dense = 0;
   if (dense) {
     ffn_dense = dense->desc->ffn;
@@ -366,7 +462,15 @@ int launch_ffn_skinny(const FfnArgs& a, const FfnArgs* dense, const CombineArgs*
   int max_rows = std::max(1, a.n_rows / d.top_k);           // a token names an expert at most once
   if (dense) max_rows = std::max(max_rows, dense->n_rows);
   probe_before(a.stream);
-  launch_stage<true>(c, d.ffn / TILE_N, busy_max, max_rows, ffn_dense / TILE_N, (const bf16_t*)a.x_perm, (bf16_t*)a.h, a.stream);
+  if (route) {
+    c.route = SkinnyRoute{route->logits, route->topk_idx, route->topk_w, route->offsets, route->perm, route->inv_perm,
+                          route->n_tokens, d.top_k};
+    (d.n_experts <= 64 ? launch_gate_up_routed<1> : d.n_experts <= 128 ? launch_gate_up_routed<2> : launch_gate_up_routed<4>)(
+        c, d.ffn / TILE_N, busy_max, ffn_dense / TILE_N,
+                                                                              (const bf16_t*)a.x_perm, (bf16_t*)a.h, a.stream);
+  } else {
+    launch_stage<true>(c, d.ffn / TILE_N, busy_max, max_rows, ffn_dense / TILE_N, (const bf16_t*)a.x_perm, (bf16_t*)a.h, a.stream);
+  }
   probe_after(a.stream);
   probe_before(a.stream);
   if (combine) {
@@ -563,7 +667,7 @@ int launch_ffn_skinny_w4(const FfnArgs& a) {
   const hmoe_layer_desc& d = *a.desc;
   if (d.dtype != HMOE_BF16_W4) return HMOE_ERR_UNSUPPORTED;
   if (a.n_rows == 0) return HMOE_OK;
-  SkinnyCtx c{a.offsets, a.slot_of, a.slots, a.slot_bytes, a.active, d.n_experts, d.hidden, d.ffn, 1, a.row_map, a.map_div, {}, {}};
+  SkinnyCtx c{a.offsets, a.slot_of, a.slots, a.slot_bytes, a.active, d.n_experts, d.hidden, d.ffn, 1, a.row_map, a.map_div, {}, {}, {}};
   const int busy_max = std::min(d.n_experts, a.n_rows);  // every busy expert has at least one row
   probe_before(a.stream);
   launch_stage_w4<true>(c, d.ffn, busy_max, (const bf16_t*)a.x_perm, (bf16_t*)a.h, a.stream);

@@ -32,10 +32,6 @@ constexpr int PR_THREADS = PB_CHUNK;         // one-block permutation: one assig
 constexpr int PR_SELF_COUNT_CHUNKS = 4;      // up to here every rank block counts all keys itself
 constexpr int PR_SELF_SCAN_CHUNKS = 256;     // up to here every rank block adds up the histogram's counts itself
 
-__device__ __forceinline__ int clamp_key(int key, int n_experts) {
-  return key < 0 ? 0 : (key >= n_experts ? n_experts - 1 : key);
-}
-
 // lanes of this wavefront (among `valid` ones) that hold the same key as the caller
 __device__ __forceinline__ uint64_t same_key_mask(int key, bool valid, int key_bits) {
   uint64_t m = __ballot(valid);
@@ -105,46 +101,6 @@ __global__ __launch_bounds__(PB_THREADS) void permute_scan_kernel(int32_t* __res
         if (b0 + i < n_blocks) block_counts[(long)(b0 + i) * n_experts + e] = c[i] + s;
     }
   }
-}
-
-// The whole permutation of at most 64 assignments (every decode batch) by one wavefront, without LDS and
-// without barriers: lane a holds assignment a, learns every other key through readlane, and counts the
-// keys that sort before its own (smaller key, or equal key in a lower lane: the stable order); lane l
-// does the same counting for experts l, 64 + l, ... (CH of them) to produce the offsets.  Same integers as the general
-// path.  Call with the first wavefront of a block.
-template <int CH>
-__device__ __forceinline__ void permute_rank_one_wave(const int32_t* topk_idx, int n_assign, int n_experts,
-                                                      int32_t* __restrict__ expert_offsets,
-                                                      int32_t* __restrict__ counts_out, int32_t* __restrict__ perm,
-                                                      int32_t* __restrict__ inv_perm) {
-  const int lane = threadIdx.x % 64;
-  const bool valid = lane < n_assign;
-  const int key = valid ? clamp_key(topk_idx[lane], n_experts) : n_experts;
-  int before = 0, below[CH], equal[CH];
-#pragma unroll
-  for (int j = 0; j < CH; ++j) below[j] = equal[j] = 0;
-  for (int i = 0; i < n_assign; ++i) {  // uniform
-    const int ki = __builtin_amdgcn_readlane(key, i);
-    before += (ki < key) | ((ki == key) & (i < lane));
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      below[j] += ki < j * 64 + lane;
-      equal[j] += ki == j * 64 + lane;
-    }
-  }
-  if (valid) {
-    perm[before] = lane;
-    inv_perm[lane] = before;
-  }
-#pragma unroll
-  for (int j = 0; j < CH; ++j) {
-    const int e = j * 64 + lane;
-    if (e < n_experts) {
-      expert_offsets[e] = below[j];
-      if (counts_out) counts_out[e] = equal[j];
-    }
-  }
-  if (lane == 0) expert_offsets[n_experts] = n_assign;
 }
 
 // Where a rank block learns what lies outside its chunk.

@@ -56,8 +56,9 @@ __device__ __forceinline__ void load_keys(const float* __restrict__ logits, int 
 // What bounds it: the latency of K dependent rounds.  Moving (value, id) pairs through six butterfly exchanges of the
 // LDS crossbar instead took about 0.6 us per round: 21 tokens of 64 experts, K = 8, by one block (with four waves
 // then, sixteen now) 36 -> 8.4 us, one token, K = 6 6.3 -> 4.0 us.
-// lds_idx (or NULL): a copy of topk_idx in LDS.  `live` must be uniform over the group; every lane of the wavefront takes part.
-template <int G, int VPL>
+// lds_idx (or NULL): a copy of topk_idx in LDS; with OUT = false the only output.
+// `live` must be uniform over the group; every lane of the wavefront takes part.
+template <int G, int VPL, bool OUT = true>
 __device__ __forceinline__ void route_keys(uint32_t (&key)[VPL], int n_experts, int top_k, long token, bool live, int gl,
                                            int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* lds_idx) {
   float win_v[VPL];  // winner j is kept by lane j % G in register j / G
@@ -100,9 +101,11 @@ __device__ __forceinline__ void route_keys(uint32_t (&key)[VPL], int n_experts, 
     const int j = gl + i * G;
     if (j < top_k) {
       const int e = win_i[i] < n_experts ? win_i[i] : n_experts - 1;  // only reachable with non-finite input
-      topk_idx[token * top_k + j] = e;
       if (lds_idx) lds_idx[token * top_k + j] = e;
-      topk_w[token * top_k + j] = expf(win_v[i] - v_max) * inv;
+      if constexpr (OUT) {
+        topk_idx[token * top_k + j] = e;
+        topk_w[token * top_k + j] = expf(win_v[i] - v_max) * inv;
+      }
     }
   }
 }
@@ -114,6 +117,50 @@ __device__ __forceinline__ void route_token(const float* __restrict__ logits, in
   uint32_t key[VPL];
   load_keys<G, VPL>(logits, n_experts, token, live, gl, key);
   route_keys<G, VPL>(key, n_experts, top_k, token, live, gl, topk_idx, topk_w, lds_idx);
+}
+
+__device__ __forceinline__ int clamp_key(int key, int n_experts) {
+  return key < 0 ? 0 : (key >= n_experts ? n_experts - 1 : key);
+}
+
+// The whole permutation of at most 64 assignments (every decode batch) by one wavefront, without LDS and
+// without barriers: lane a holds assignment a, learns every other key through readlane, and counts the
+// keys that sort before its own (smaller key, or equal key in a lower lane: the stable order); lane l
+// does the same counting for experts l, 64 + l, ... (CH of them) to produce the offsets.  Same integers as the general
+// path.  Call with the first wavefront of a block.
+template <int CH>
+__device__ __forceinline__ void permute_rank_one_wave(const int32_t* topk_idx, int n_assign, int n_experts,
+                                                      int32_t* __restrict__ expert_offsets,
+                                                      int32_t* __restrict__ counts_out, int32_t* __restrict__ perm,
+                                                      int32_t* __restrict__ inv_perm) {
+  const int lane = threadIdx.x % 64;
+  const bool valid = lane < n_assign;
+  const int key = valid ? clamp_key(topk_idx[lane], n_experts) : n_experts;
+  int before = 0, below[CH], equal[CH];
+#pragma unroll
+  for (int j = 0; j < CH; ++j) below[j] = equal[j] = 0;
+  for (int i = 0; i < n_assign; ++i) {  // uniform
+    const int ki = __builtin_amdgcn_readlane(key, i);
+    before += (ki < key) | ((ki == key) & (i < lane));
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      below[j] += ki < j * 64 + lane;
+      equal[j] += ki == j * 64 + lane;
+    }
+  }
+  if (valid) {
+    perm[before] = lane;
+    inv_perm[lane] = before;
+  }
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    const int e = j * 64 + lane;
+    if (e < n_experts) {
+      expert_offsets[e] = below[j];
+      if (counts_out) counts_out[e] = equal[j];
+    }
+  }
+  if (lane == 0) expert_offsets[n_experts] = n_assign;
 }
 
 }  // namespace hmoe

@@ -1,0 +1,74 @@
+"""hmoe_route_ffn_combine against the calls it stands for, at the sizes where its dispatch changes."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from hmoe_testlib import build_layer, to_device
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def hm():
+    import paper_2504_05897_amd as module
+    return module
+
+
+@pytest.mark.parametrize("E,K,hidden,ffn,shared_ffn,tokens", [
+    (8, 2, 128, 192, (64,), (1, 3, 8, 9)),          # 9 tokens: routing in a launch of its own
+    (64, 6, 256, 64, (192,), (1, 8)),
+    (64, 8, 64, 320, (), (1, 8)),                   # 64 assignments, the most
+    (65, 9, 64, 64, (64,), (1, 7, 8)),              # four experts per lane; 63 and 72 assignments
+    (256, 32, 64, 64, (), (1, 2, 3)),               # 64 and 96 assignments
+    (200, 3, 128, 64, (448,), (2, 8)),              # more shared groups than routed ones: several grid rows
+    (1, 1, 64, 128, (), (1, 8)),
+    (16, 4, 64, 8192, (64,), (1, 4)),               # 200 blocks and more: eight waves
+])
+def test_route_ffn_combine_equals_the_separate_calls(hm, E, K, hidden, ffn, shared_ffn, tokens):
+    """Every output the same bits as hmoe_route_permute, the FFN call and hmoe_combine; ties and masked logits among them."""
+    shape = wl.small_shape(dtype=wl.BF16, hidden=hidden, ffn=ffn, n_experts=E, top_k=K, shared_ffn=shared_ffn, x_mode="rmsnorm")
+    lay = wl.make_layer(shape, 21 + E, max(tokens))
+    layer = build_layer(hm, lay, max_tokens=max(tokens))
+    d, sd, c = layer.desc, layer.shared_desc, layer.cache
+    rng = np.random.default_rng(E + K)
+    for T in tokens:
+        print("route_ffn_combine", E, K, hidden, ffn, shared_ffn, T, flush=True)
+        lg = rng.standard_normal((T, E)).astype(np.float32)
+        lg[0] = np.round(lg[0])                                       # ties
+        if E > K:
+            lg[T - 1, : (E - K) // 2] = -np.inf                       # masked experts
+        lg = to_device(lg)
+        x = to_device(lay.x[:T])
+        if sd is not None:
+            layer.shared_offsets.copy_(torch.tensor([0, T], dtype=torch.int32))
+        shared = (sd, layer.shared_cache, layer.shared_offsets) if sd is not None else (None, None, None)
+        outs = []
+        for fused in (True, False):
+            layer.ffn_ws.fill_(0xFF)
+            idx, w = torch.full((T, K), -7, dtype=torch.int32, device=DEV), torch.full((T, K), 7.0, device=DEV)
+            offs = torch.full((E + 1,), -7, dtype=torch.int32, device=DEV)
+            perm, inv = (torch.full((T * K,), -7, dtype=torch.int32, device=DEV) for _ in range(2))
+            o = torch.full((T * K, hidden), 7.0, dtype=torch.bfloat16, device=DEV)
+            osh = torch.full((T, hidden), 7.0, dtype=torch.bfloat16, device=DEV) if sd is not None else None
+            sws = (layer.shared_ws, layer.shared_ws_bytes) if sd is not None else (None, 0)
+            y = torch.full((T, hidden), 7.0, dtype=torch.bfloat16, device=DEV)
+            if fused:
+                hm.hmoe_route_ffn_combine(d, c, x, lg, T, idx, w, offs, perm, inv, layer.perm_ws, layer.perm_ws_bytes, o, layer.ffn_ws,
+                                          layer.ffn_ws_bytes, *shared, osh, *sws, y)
+            else:
+                hm.hmoe_route_permute(d, lg, T, idx, w, offs, perm, inv, None, layer.perm_ws, layer.perm_ws_bytes)
+                hm.hmoe_expert_ffn_grouped_gather(d, c, x, perm, offs, T * K, None, o, layer.ffn_ws, layer.ffn_ws_bytes)
+                if sd is not None:
+                    hm.hmoe_expert_ffn_grouped(*shared[:2], x, layer.shared_offsets, T, None, osh, *sws)
+                hm.hmoe_combine(d, o, inv, w, osh, T, y)
+            torch.cuda.synchronize()
+            outs.append([t.cpu() for t in (idx, w, offs, perm, inv, o, y) + (() if osh is None else (osh,))])
+        for a, b in zip(*outs):
+            assert torch.equal(a, b), T
+    with pytest.raises(hm.HmoeError) as ei:                           # refused before anything is enqueued
+        hm.hmoe_route_ffn_combine(d, c, x, lg, 1, idx, w, offs, perm, inv, layer.perm_ws, 0, o, layer.ffn_ws, layer.ffn_ws_bytes,
+                                  *shared, osh, *sws, y)
+    assert ei.value.status == hm.HMOE_ERR_WORKSPACE
+    layer.close()
