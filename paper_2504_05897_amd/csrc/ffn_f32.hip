@@ -1,18 +1,20 @@
 // fp32 FFN on matrix instructions (HMOE_F32 with HMOE_FFN_AUTO, hidden and ffn multiples of 4, more than a few rows; the
 // rest takes the general kernels of ffn_reference.hip, see ffn_f32_takes).  Weights are plain row-major.
 //
-// A tile is 16 MR rows of one expert x 32 weight rows (gate and up of 16 features, or 32 columns of the down
-// projection); every weight row is read once per tile instead of once per token, in 16-byte loads.  With few rows the
-// path is bound by latency, with many by the operands' way through the caches.  K is split over the NW = 4 MR waves of the
-// block, so each has a quarter or an eighth of the trips to memory, all of a round issued at once.
-// Measured (8 experts of 256 x 512, top 2, whole layer, against one wavefront per output element): 77 tokens 61 -> 35 us,
-// 300 tokens 173 -> 38 us, 1024 tokens 527 -> 88 us (gate/up 53 us); with 16 tokens the calls on the host take longer.
-//   * v_mfma_f32_16x16x4_f32 is a full fp32 multiply-add.  Lane (j, kblk) loads four consecutive k of row j; element i
-//     of both operands forms the k-step {i, 4 + i, 8 + i, 12 + i} of a 16-wide piece of K, so no data moves between
-//     lanes.
-//   * Every element i and every one of S = 16 / NW consecutive pieces has an accumulator of its own: NW * S * 4 = 64
-//     partial sums per output over K / 64 products each (as many as one wavefront per output element would keep), which
-//     are added up in 64 bits and rounded once: error of the layer 1.27e-7 against 1.67e-7 (2-norm, 1024 tokens).
+// v_mfma_f64_16x16x4_f64 on operands widened to 64 bits: products are exact, sums are kept in 64 bits and rounded once, so
+// the order of the sums needs no care: error of the layer 1.07e-7 -> 7.3e-8 (2-norm, against 64 bits throughout).  It runs at
+// half the rate of the fp32 instruction, but that one needed 64 partial sums per output to be as exact as one wavefront per
+// output element: eight waves per tile with an eighth of K each, whose 64 KB of partial sums met in LDS, and gate/up of 1000
+// tokens took 8 times what its matrix instructions do.
+//   * A tile is 16 MR rows of one expert x 32 weight rows (gate and up of 16 features, or 32 columns of the down
+//     projection); every weight row is read once per tile instead of once per token.  The NW waves of the block share K in
+//     pieces of 16, dealt in turn, and their sums meet in LDS: eight waves with few rows, where latency counts, four with
+//     two row fragments (one, two or eight are slower from 64 to 1000 tokens: K is short, and a tile ends sooner).
+//   * Lane (j, kblk) loads four consecutive k of row j; element i of both operands forms the k-step {i, 4 + i, 8 + i,
+//     12 + i} of a piece, so no data moves between lanes.  Loads are unconditional (clamped, and cleared past the end of K),
+//     a set of two pieces ahead, weights first: the rows of gate/up hang on the row map.
+// Layer of 8 experts of 256 x 512, top 2, us in a graph, fp32 instruction -> this: 16 tokens 27.9 -> 27.6, 77 31.4 -> 32.0, 130 37.1
+// -> 36.6, 300 42.7 -> 40.1, 500 60.4 -> 53.6, 1000 89.5 -> 73.8 (gate/up 52.4 -> 37.2).
 #include <algorithm>
 #include <cmath>
 
@@ -21,17 +23,20 @@
 
 namespace hmoe {
 
-__device__ __forceinline__ f32x4_t mfma_16x16x4_f32(float a, float b, f32x4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+// D = A(16x4) * B(4x16) + C in 64 bits.  Lane l supplies A[l%16][l/16] and B[l/16][l%16]; register r of lane l is
+// D[4 r + l/16][l%16].
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f64x4_t mfma_16x16x4_f64(double a, double b, f64x4_t c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-template <bool GATEUP, int MR>
-__global__ __launch_bounds__(256 * MR, 2) void ffn_f32_kernel(TiledCtx c, const float* __restrict__ in, float* __restrict__ out) {
-  constexpr int NW = 4 * MR, S = 16 / NW, NU = 2;
+template <bool GATEUP, int MR, int NW>
+__global__ __launch_bounds__(64 * NW) void ffn_f32_kernel(TiledCtx c, const float* __restrict__ in, float* __restrict__ out) {
+  constexpr int NU = 2, SET = 2;  // pieces per register set; two sets alternate
   __shared__ double red[NW][MR][NU][4][64];
   TileLoc loc;
   if (!locate_tile<16 * MR>(c, loc)) return;  // uniform over the block
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, j = lane % 16, kblk = lane / 16;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, j = lane % 16, kblk = lane / 16;
   const int K = GATEUP ? c.hidden : c.ffn;
   const int n_out = GATEUP ? c.ffn : c.hidden;
   const int m0 = loc.mt * 16 * MR;
@@ -43,41 +48,70 @@ __global__ __launch_bounds__(256 * MR, 2) void ffn_f32_kernel(TiledCtx c, const 
     const int n = GATEUP ? min(loc.nt * 16 + j, n_out - 1) + u * n_out : min(loc.nt * 32 + u * 16 + j, n_out - 1);
     ws[u] = w + (size_t)n * K;
   }
-  const float* xs[MR];
+  int row[MR];
 #pragma unroll
   for (int i = 0; i < MR; ++i) {
-    const int row = loc.row_first + min(m0 + i * 16 + j, loc.m_rows - 1);
-    xs[i] = in + (size_t)(GATEUP ? mapped_row(c.row_map, c.map_div, row) : row) * K;
+    row[i] = loc.row_first + min(m0 + i * 16 + j, loc.m_rows - 1);
+    if (GATEUP && c.row_map) row[i] = c.row_map[row[i]];
   }
 
-  f32x4_t acc[S][4][MR][NU];
+  const int pieces = (K + 15) / 16;
+  f32x4_t a[2][SET][MR], b[2][SET][NU];
+  const float* xs[MR];
+  auto load_weights = [&](int s, int p0) {
 #pragma unroll
-  for (int s = 0; s < S; ++s)
+    for (int d = 0; d < SET; ++d) {
+      const int k = min((p0 + d * NW) * 16 + kblk * 4, K - 4);  // K is a multiple of 4: four k are all inside or all outside
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int i = 0; i < MR; ++i)
-#pragma unroll
-        for (int u = 0; u < NU; ++u) acc[s][e][i][u] = f32x4_t{0, 0, 0, 0};
-  for (int k0 = 0; k0 < K; k0 += 256) {  // 256 k per round of the block: S pieces of 16 per wave
-    f32x4_t a[S][MR], b[S][NU];
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const int k = k0 + (s * NW + wave) * 16 + kblk * 4;
-      const bool ok = k < K;  // K is a multiple of 4: four k are all inside or all outside
-#pragma unroll
-      for (int i = 0; i < MR; ++i) a[s][i] = ok ? *(const f32x4_t*)(xs[i] + k) : f32x4_t{0, 0, 0, 0};
-#pragma unroll
-      for (int u = 0; u < NU; ++u) b[s][u] = ok ? *(const f32x4_t*)(ws[u] + k) : f32x4_t{0, 0, 0, 0};
+      for (int u = 0; u < NU; ++u) b[s][d][u] = *(const f32x4_t*)(ws[u] + k);
     }
+  };
+  auto load_rows = [&](int s, int p0) {
 #pragma unroll
-    for (int s = 0; s < S; ++s)
+    for (int d = 0; d < SET; ++d) {
+      const int k = min((p0 + d * NW) * 16 + kblk * 4, K - 4);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int i = 0; i < MR; ++i) a[s][d][i] = *(const f32x4_t*)(xs[i] + k);
+    }
+  };
+  f64x4_t acc[MR][NU];
 #pragma unroll
-        for (int i = 0; i < MR; ++i)
+  for (int i = 0; i < MR; ++i)
 #pragma unroll
-          for (int u = 0; u < NU; ++u) acc[s][e][i][u] = mfma_16x16x4_f32(a[s][i][e], b[s][u][e], acc[s][e][i][u]);
+    for (int u = 0; u < NU; ++u) acc[i][u] = f64x4_t{0, 0, 0, 0};
+  auto multiply = [&](int s, int p0) {
+#pragma unroll
+    for (int d = 0; d < SET; ++d) {
+      const bool ok = (p0 + d * NW) * 16 + kblk * 4 < K;  // (both cleared past the end: what was read instead may not be finite)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        double bd[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) bd[u] = (double)(ok ? b[s][d][u][e] : 0.0f);
+#pragma unroll
+        for (int i = 0; i < MR; ++i) {
+          const double ad = (double)(ok ? a[s][d][i][e] : 0.0f);
+#pragma unroll
+          for (int u = 0; u < NU; ++u) acc[i][u] = mfma_16x16x4_f64(ad, bd[u], acc[i][u]);
+        }
+      }
+    }
+  };
+  load_weights(0, wave);
+#pragma unroll
+  for (int i = 0; i < MR; ++i) xs[i] = in + (size_t)(GATEUP && c.row_map ? row[i] / c.map_div : row[i]) * K;
+  load_rows(0, wave);
+  for (int p = wave; p < pieces; p += 2 * SET * NW) {
+    load_weights(1, p + SET * NW);
+    load_rows(1, p + SET * NW);
+    __builtin_amdgcn_sched_barrier(0);  // (the compiler would move the loads down to their uses)
+    multiply(0, p);
+    __builtin_amdgcn_sched_barrier(0);
+    load_weights(0, p + 2 * SET * NW);
+    load_rows(0, p + 2 * SET * NW);
+    __builtin_amdgcn_sched_barrier(0);
+    if (p + SET * NW < pieces) multiply(1, p + SET * NW);  // uniform
+    __builtin_amdgcn_sched_barrier(0);
   }
 
 #pragma unroll
@@ -85,49 +119,37 @@ __global__ __launch_bounds__(256 * MR, 2) void ffn_f32_kernel(TiledCtx c, const 
 #pragma unroll
     for (int u = 0; u < NU; ++u)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        double p[S];
-#pragma unroll
-        for (int s = 0; s < S; ++s) p[s] = ((double)acc[s][0][i][u][r] + acc[s][1][i][u][r]) + ((double)acc[s][2][i][u][r] + acc[s][3][i][u][r]);
-#pragma unroll
-        for (int d = 1; d < S; d *= 2)
-#pragma unroll
-          for (int s = 0; s + d < S; s += 2 * d) p[s] += p[s + d];
-        red[wave][i][u][r][lane] = p[0];
-      }
+      for (int r = 0; r < 4; ++r) red[wave][i][u][r][lane] = acc[i][u][r];
   __syncthreads();
-  // NW waves, 4 MR registers of 64 lanes per unit: wave w finishes register w % 4 of row fragment w / 4
-  const int i = wave / 4, r = wave % 4;
-  const int m = m0 + i * 16 + kblk * 4 + r;
-  float v[NU];
+  for (int q = wave; q < 4 * MR; q += NW) {  // register r of row fragment i: output row 4 r + kblk of the fragment
+    const int i = q / 4, r = q % 4;
+    float v[NU];
 #pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    double p[NW];
+    for (int u = 0; u < NU; ++u) {
+      double sum = 0.0;
 #pragma unroll
-    for (int o = 0; o < NW; ++o) p[o] = red[o][i][u][r][lane];
-#pragma unroll
-    for (int d = 1; d < NW; d *= 2)
-#pragma unroll
-      for (int o = 0; o + d < NW; o += 2 * d) p[o] += p[o + d];
-    v[u] = (float)p[0];
-  }
-  if (m >= loc.m_rows) return;
-  float* orow = out + (size_t)(loc.row_first + m) * n_out;
-  if (GATEUP) {
-    const int n = loc.nt * 16 + j;
-    if (n < n_out) orow[n] = v[0] / (1.0f + expf(-v[0])) * v[1];
-  } else {
-    const int n = loc.nt * 32 + j;
-    if (n < n_out) orow[n] = v[0];
-    if (n + 16 < n_out) orow[n + 16] = v[1];
+      for (int o = 0; o < NW; ++o) sum += red[o][i][u][r][lane];
+      v[u] = (float)sum;
+    }
+    const int m = m0 + i * 16 + 4 * r + kblk;
+    if (m >= loc.m_rows) continue;
+    float* orow = out + (size_t)(loc.row_first + m) * n_out;
+    if (GATEUP) {
+      const int n = loc.nt * 16 + j;
+      if (n < n_out) orow[n] = v[0] / (1.0f + expf(-v[0])) * v[1];
+    } else {
+      const int n = loc.nt * 32 + j;
+      if (n < n_out) orow[n] = v[0];
+      if (n + 16 < n_out) orow[n + 16] = v[1];
+    }
   }
 }
 
-template <bool GATEUP, int MR>
+template <bool GATEUP, int MR, int NW>
 static void launch_stage_f32(TiledCtx c, int n_rows, const float* in, float* out, hipStream_t s) {
   c.n_tiles_n = GATEUP ? (c.ffn + 15) / 16 : (c.hidden + 31) / 32;
   c.grid_padded = (int)((tiles_upper_bound(c, n_rows, 16 * MR) + 7) / 8 * 8);
-  hipLaunchKernelGGL((ffn_f32_kernel<GATEUP, MR>), dim3((unsigned)c.grid_padded), dim3(256 * MR), 0, s, c, in, out);
+  hipLaunchKernelGGL((ffn_f32_kernel<GATEUP, MR, NW>), dim3((unsigned)c.grid_padded), dim3(64 * NW), 0, s, c, in, out);
 }
 
 // The general kernels read an expert's weights for every row again, out of the caches (about 6 TB/s); the tiles read them
@@ -156,12 +178,10 @@ int launch_ffn_f32(const FfnArgs& a) {
   // else two, which halve the reads of the weights
   const bool one = a.n_rows < 16 * d.n_experts;
   probe_before(a.stream);
-  if (one) launch_stage_f32<true, 1>(c, a.n_rows, (const float*)a.x_perm, (float*)a.h, a.stream);
-  else launch_stage_f32<true, 2>(c, a.n_rows, (const float*)a.x_perm, (float*)a.h, a.stream);
+  (one ? launch_stage_f32<true, 1, 8> : launch_stage_f32<true, 2, 4>)(c, a.n_rows, (const float*)a.x_perm, (float*)a.h, a.stream);
   probe_after(a.stream);
   probe_before(a.stream);
-  if (one) launch_stage_f32<false, 1>(c, a.n_rows, (const float*)a.h, (float*)a.o_perm, a.stream);
-  else launch_stage_f32<false, 2>(c, a.n_rows, (const float*)a.h, (float*)a.o_perm, a.stream);
+  (one ? launch_stage_f32<false, 1, 8> : launch_stage_f32<false, 2, 4>)(c, a.n_rows, (const float*)a.h, (float*)a.o_perm, a.stream);
   probe_after(a.stream);
   HMOE_HIP(hipGetLastError());
   return HMOE_OK;

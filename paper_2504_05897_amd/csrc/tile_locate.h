@@ -49,6 +49,16 @@ struct TileLoc {
   int slot;  // cache slot that holds expert e
   int m0, fm;  // TileWalk only: first row of the tile within the expert, and its height in 32-row fragments
 };
+// First row, rows and slot of expert i as a launch sees it: no rows unless it is selected and resident.  The three loads go
+// out together (one trip to memory at the start of every block; the rows behind a test of the slot were a second one).
+__device__ __forceinline__ void load_expert(const TiledCtx& c, int i, bool selected, int& first, int& rows, int& slot) {
+  const int at = i < c.n_experts ? i : c.n_experts - 1;
+  const int s = c.slot_of[at], begin = c.offsets[at], end = c.offsets[at + 1];
+  const bool takes_part = i < c.n_experts && selected && s >= 0;
+  slot = i < c.n_experts ? s : -1;
+  first = takes_part ? begin : 0;
+  rows = takes_part ? end - begin : 0;
+}
 template <int BM>
 __device__ __forceinline__ bool locate_tile(const TiledCtx& c, TileLoc& t) {
   constexpr int CH = HMOE_MAX_EXPERTS / 64;
@@ -62,11 +72,7 @@ __device__ __forceinline__ bool locate_tile(const TiledCtx& c, TileLoc& t) {
     incl[j] = total;
     if (j * 64 < c.n_experts) {  // uniform
       const int i = j * 64 + lane;
-      if (i < c.n_experts) slot[j] = c.slot_of[i];
-      if (i < c.n_experts && ((c.active.w[j] >> lane) & 1ull) && slot[j] >= 0) {
-        first[j] = c.offsets[i];
-        rows[j] = c.offsets[i + 1] - first[j];
-      }
+      load_expert(c, i, (c.active.w[j] >> lane) & 1ull, first[j], rows[j], slot[j]);
       int v = (rows[j] + BM - 1) / BM * c.n_tiles_n;
 #pragma unroll
       for (int d = 1; d < 64; d *= 2) {
@@ -121,11 +127,7 @@ __device__ __forceinline__ bool locate_tile_spread(const TiledCtx& c, TileLoc& t
     incl[j] = total;
     if (j * 64 < c.n_experts) {  // uniform
       const int i = j * 64 + lane;
-      if (i < c.n_experts) slot[j] = c.slot_of[i];
-      if (i < c.n_experts && ((c.active.w[j] >> lane) & 1ull) && slot[j] >= 0) {
-        first[j] = c.offsets[i];
-        rows[j] = c.offsets[i + 1] - first[j];
-      }
+      load_expert(c, i, (c.active.w[j] >> lane) & 1ull, first[j], rows[j], slot[j]);
       const uint64_t busy = __ballot(rows[j] > 0);
       const int before = columns + __popcll(busy & ((1ull << lane) - 1ull)) * c.n_tiles_n;
       columns += __popcll(busy) * c.n_tiles_n;
@@ -185,11 +187,7 @@ struct TileWalk {
       int first = 0, rows = 0, incl = sum, slot = -1;
       if (j * 64 < c.n_experts) {  // uniform
         const int i = j * 64 + lane;
-        if (i < c.n_experts) slot = c.slot_of[i];
-        if (i < c.n_experts && ((c.active.w[j] >> lane) & 1ull) && slot >= 0) {
-          first = c.offsets[i];
-          rows = c.offsets[i + 1] - first;
-        }
+        load_expert(c, i, (c.active.w[j] >> lane) & 1ull, first, rows, slot);
         int v = (rows + bm - 1) / bm * c.n_tiles_n;
 #pragma unroll
         for (int d = 1; d < 64; d *= 2) {
