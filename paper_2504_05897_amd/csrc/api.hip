@@ -19,6 +19,16 @@ int set_hip_error(hipError_t err, const char* what) {
   return HMOE_ERR_HIP;
 }
 
+void* device_view_of_pinned(void* host) {
+  hipPointerAttribute_t attr;
+  if (!host) return nullptr;
+  if (hipPointerGetAttributes(&attr, host) != hipSuccess) {
+    (void)hipGetLastError();  // memory that HIP does not know
+    return nullptr;
+  }
+  return attr.type == hipMemoryTypeHost && attr.devicePointer == host ? host : nullptr;
+}
+
 int set_error_text(int status, const char* text) {
   g_last_error = text;
   return status;

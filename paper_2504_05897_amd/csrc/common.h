@@ -85,6 +85,10 @@ int set_error_text(int status, const char* text);  // text for hmoe_last_error; 
 int check_desc(const hmoe_layer_desc* d);
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// The address under which kernels can write pinned host memory themselves, or NULL (pageable memory, or pinned memory that the
+// device sees elsewhere): a few values then need no copy behind the kernel.
+void* device_view_of_pinned(void* host);
+
 #define HMOE_HIP(call)                                                  \
   do {                                                                  \
     hipError_t hmoe_e_ = (call);                                        \

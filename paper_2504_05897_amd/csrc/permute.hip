@@ -379,7 +379,8 @@ static int32_t permute_with_workspace(const hmoe_layer_desc* desc, const int32_t
   while ((1 << key_bits) < E) ++key_bits;
   const int nblk = n_chunks(A);
   int32_t* block_counts = (int32_t*)workspace;
-  int32_t* counts_dev = block_counts + (size_t)(nblk > 0 ? nblk : 0) * E;
+  int32_t* const counts_host = (int32_t*)device_view_of_pinned(h_counts_pinned);
+  int32_t* const counts_dev = counts_host ? counts_host : block_counts + (size_t)(nblk > 0 ? nblk : 0) * E;
 
 #define HMOE_LAUNCH_RANK(SRC, NW, FROM, OFFSETS, COUNTS)                                                              \
   hipLaunchKernelGGL((permute_rank_kernel<SRC, NW>), dim3(A > 0 ? (unsigned)((A + 64 * NW - 1) / (64 * NW)) : 1), dim3(64 * NW), 0, s, \
@@ -400,7 +401,7 @@ static int32_t permute_with_workspace(const hmoe_layer_desc* desc, const int32_t
   }
 #undef HMOE_LAUNCH_RANK
   HMOE_HIP(hipGetLastError());
-  if (h_counts_pinned)
+  if (h_counts_pinned && !counts_host)  // (where kernels cannot write the host memory themselves)
     HMOE_HIP(hipMemcpyAsync(h_counts_pinned, counts_dev, (size_t)E * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   if (x && A > 0) {
     hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)A), dim3(256), 0, s, (const uint4*)x, perm, desc->top_k,
@@ -486,7 +487,8 @@ extern "C" int32_t hmoe_route_permute(const hmoe_layer_desc* desc, const float* 
   const int E = desc->n_experts, K = desc->top_k;
   int key_bits = 0;
   while ((1 << key_bits) < E) ++key_bits;
-  int32_t* counts_dev = (int32_t*)workspace + (size_t)n_chunks(A) * E;
+  int32_t* const counts_host = (int32_t*)device_view_of_pinned(h_counts_pinned);
+  int32_t* const counts_dev = counts_host ? counts_host : (int32_t*)workspace + (size_t)n_chunks(A) * E;
 #define HMOE_LAUNCH_SMALL(G, VPL)                                                                                   \
   hipLaunchKernelGGL((route_permute_small_kernel<G, VPL>), dim3(1), dim3(PR_THREADS), 0, s, logits, (int)T, E, K, key_bits, \
                      topk_idx, topk_w, expert_offsets, counts_dev, perm, inv_perm)
@@ -498,7 +500,7 @@ extern "C" int32_t hmoe_route_permute(const hmoe_layer_desc* desc, const float* 
   else HMOE_LAUNCH_SMALL(64, 4);
 #undef HMOE_LAUNCH_SMALL
   HMOE_HIP(hipGetLastError());
-  if (h_counts_pinned)
+  if (h_counts_pinned && !counts_host)  // (where kernels cannot write the host memory themselves)
     HMOE_HIP(hipMemcpyAsync(h_counts_pinned, counts_dev, (size_t)E * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   return HMOE_OK;
 }
@@ -546,7 +548,8 @@ extern "C" int32_t hmoe_router_route_permute(const hmoe_layer_desc* desc, const 
   const int E = desc->n_experts, K = desc->top_k;
   int key_bits = 0;
   while ((1 << key_bits) < E) ++key_bits;
-  int32_t* counts_dev = (int32_t*)workspace + (size_t)n_chunks(A) * E;
+  int32_t* const counts_host = (int32_t*)device_view_of_pinned(h_counts_pinned);
+  int32_t* const counts_dev = counts_host ? counts_host : (int32_t*)workspace + (size_t)n_chunks(A) * E;
 #define HMOE_LAUNCH_FRONT(G, VPL, MA, NF, KS, NW)                                                                            \
   hipLaunchKernelGGL((front_small_kernel<G, VPL, RouterShape<MA, NF, KS, NW>>), dim3(1), dim3(PR_THREADS), 0, s, (const bf16_t*)x, \
                      (const bf16_t*)w_g, desc->hidden, logits, (int)T, E, K, key_bits, topk_idx, topk_w, expert_offsets,   \
@@ -554,7 +557,7 @@ extern "C" int32_t hmoe_router_route_permute(const hmoe_layer_desc* desc, const 
   HMOE_ROUTER_SHAPES_ONE_BLOCK(E, HMOE_LAUNCH_FRONT);
 #undef HMOE_LAUNCH_FRONT
   HMOE_HIP(hipGetLastError());
-  if (h_counts_pinned)
+  if (h_counts_pinned && !counts_host)  // (where kernels cannot write the host memory themselves)
     HMOE_HIP(hipMemcpyAsync(h_counts_pinned, counts_dev, (size_t)E * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   return HMOE_OK;
 }

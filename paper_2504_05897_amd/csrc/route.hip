@@ -20,11 +20,14 @@ static void launch_route(const float* logits, int T, int E, int K, int32_t* idx,
 
 // Batch-mean full softmax per expert (the routing scores s of Eq. (3)).  A block takes 256 tokens, a
 // wave walks its 64 tokens in order with the E logits spread over its lanes (VPL per lane), sums stay in
-// registers; waves, then blocks, are added in a fixed order, so the result does not depend on timing.
+// registers; waves, then blocks, are added in a fixed order, so the result does not depend on timing.  A single block (most
+// decode batches) finishes the scores itself; either kernel also writes them to `host` (pinned memory, or NULL).  Decode step of
+// four tokens whose host waits for the scores: three operations of 2 to 4 us and their gaps (partial sums, finish, copy) -> one.
 constexpr int SC_TOKENS = 256;
 template <int VPL>
 __global__ __launch_bounds__(256) void route_scores_kernel(const float* __restrict__ logits, int n_tokens, int n_experts,
-                                                           float* __restrict__ partial) {
+                                                           float* __restrict__ partial, float inv_tokens,
+                                                           float* __restrict__ scores, float* __restrict__ host) {
   __shared__ float wsum[4][64 * VPL];
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   const float NEG_INF = -__builtin_inff();
@@ -32,16 +35,25 @@ __global__ __launch_bounds__(256) void route_scores_kernel(const float* __restri
 #pragma unroll
   for (int i = 0; i < VPL; ++i) acc[i] = 0.0f;
   const long t0 = (long)blockIdx.x * SC_TOKENS + wave * 64;
+  float next[VPL];  // the next token's logits are on their way while one is summed
+  auto load = [&](long t) {
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+      const int e = lane + j * 64;
+      next[j] = e < n_experts ? logits[(t < n_tokens ? t : n_tokens - 1) * n_experts + e] : NEG_INF;
+    }
+  };
+  load(t0);
   for (int i = 0; i < 64; ++i) {
     const long t = t0 + i;
     if (t >= n_tokens) break;  // uniform over the wave
     float v[VPL], m = NEG_INF;
 #pragma unroll
     for (int j = 0; j < VPL; ++j) {
-      const int e = lane + j * 64;
-      v[j] = e < n_experts ? logits[t * n_experts + e] : NEG_INF;
+      v[j] = next[j];
       m = fmaxf(m, v[j]);
     }
+    load(t + 1);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
     float sum = 0.0f;
@@ -56,18 +68,27 @@ __global__ __launch_bounds__(256) void route_scores_kernel(const float* __restri
 #pragma unroll
   for (int j = 0; j < VPL; ++j) wsum[wave][lane + j * 64] = acc[j];
   __syncthreads();
-  for (int e = threadIdx.x; e < n_experts; e += 256)
-    partial[(long)blockIdx.x * n_experts + e] = ((wsum[0][e] + wsum[1][e]) + wsum[2][e]) + wsum[3][e];
+  for (int e = threadIdx.x; e < n_experts; e += 256) {
+    const float sum = ((wsum[0][e] + wsum[1][e]) + wsum[2][e]) + wsum[3][e];
+    if (gridDim.x > 1) {
+      partial[(long)blockIdx.x * n_experts + e] = sum;
+    } else {
+      const float score = (0.0f + sum) * inv_tokens;
+      scores[e] = score;
+      if (host) host[e] = score;
+    }
+  }
 }
 
 __global__ __launch_bounds__(256) void route_scores_finish_kernel(const float* __restrict__ partial, int n_blocks,
                                                                   int n_experts, float inv_tokens,
-                                                                  float* __restrict__ scores) {
+                                                                  float* __restrict__ scores, float* __restrict__ host) {
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= n_experts) return;
   float s = 0.0f;
   for (int b = 0; b < n_blocks; ++b) s += partial[(long)b * n_experts + e];
   scores[e] = s * inv_tokens;
+  if (host) host[e] = s * inv_tokens;
 }
 
 }  // namespace hmoe
@@ -89,13 +110,16 @@ extern "C" int32_t hmoe_route_scores(const hmoe_layer_desc* desc, const float* l
   hipStream_t s = (hipStream_t)stream;
   const int E = desc->n_experts, blocks = (T + SC_TOKENS - 1) / SC_TOKENS;
   float* partial = (float*)workspace;
-  if (E <= 64) hipLaunchKernelGGL((route_scores_kernel<1>), dim3(blocks), dim3(256), 0, s, logits, T, E, partial);
-  else if (E <= 128) hipLaunchKernelGGL((route_scores_kernel<2>), dim3(blocks), dim3(256), 0, s, logits, T, E, partial);
-  else hipLaunchKernelGGL((route_scores_kernel<4>), dim3(blocks), dim3(256), 0, s, logits, T, E, partial);
-  hipLaunchKernelGGL(route_scores_finish_kernel, dim3((E + 255) / 256), dim3(256), 0, s, partial, blocks, E, 1.0f / (float)T,
-                     scores);
+  float* const host = (float*)device_view_of_pinned(h_scores_pinned);
+  const float inv = 1.0f / (float)T;
+  float* const host_now = blocks == 1 ? host : nullptr;
+  if (E <= 64) hipLaunchKernelGGL((route_scores_kernel<1>), dim3(blocks), dim3(256), 0, s, logits, T, E, partial, inv, scores, host_now);
+  else if (E <= 128) hipLaunchKernelGGL((route_scores_kernel<2>), dim3(blocks), dim3(256), 0, s, logits, T, E, partial, inv, scores, host_now);
+  else hipLaunchKernelGGL((route_scores_kernel<4>), dim3(blocks), dim3(256), 0, s, logits, T, E, partial, inv, scores, host_now);
+  if (blocks > 1)
+    hipLaunchKernelGGL(route_scores_finish_kernel, dim3((E + 255) / 256), dim3(256), 0, s, partial, blocks, E, inv, scores, host);
   HMOE_HIP(hipGetLastError());
-  if (h_scores_pinned)
+  if (h_scores_pinned && !host)  // (where kernels cannot write the host memory themselves)
     HMOE_HIP(hipMemcpyAsync(h_scores_pinned, scores, (size_t)E * sizeof(float), hipMemcpyDeviceToHost, s));
   return HMOE_OK;
 }

@@ -145,3 +145,39 @@ def test_masked_and_undefined_logits(hm, T, E, K):
                 chosen = np.take_along_axis(values, got, 1).astype(np.float64)
                 ref = np.exp(chosen - chosen[:, :1])
                 assert np.abs(w.cpu().numpy() - ref / ref.sum(1, keepdims=True)).max() < 1e-6
+
+
+@pytest.mark.parametrize("memory", ["pinned", "inside pinned", "pageable"])
+@pytest.mark.parametrize("T,E,K", [(3, 8, 2), (70, 64, 6), (300, 70, 6), (2000, 200, 8), (40000, 64, 7)])
+def test_counts_and_scores_to_host_memory(hm, memory, T, E, K):
+    """Pinned memory is written by the kernels, any other by a copy behind them: every way of the permutation and of the
+    routing scores (one block, several), at an offset into an allocation too."""
+    print("host memory", memory, T, E, K, flush=True)
+    pinned = memory != "pageable"
+    shift = 5 if memory == "inside pinned" else 0
+    rng = np.random.default_rng(T + E)
+    lg = rng.standard_normal((T, E)).astype(np.float32)
+    d = hm.make_desc(64, 64, E, K, E, hm.HMOE_BF16)
+    counts = torch.full((E + 2 * shift,), -7, dtype=torch.int32, pin_memory=pinned)
+    scores_h = torch.full((E + 2 * shift,), -7.0, pin_memory=pinned)
+    idx, w = torch.empty(T, K, dtype=torch.int32, device=DEV), torch.empty(T, K, device=DEV)
+    offs = torch.empty(E + 1, dtype=torch.int32, device=DEV)
+    perm, inv = (torch.empty(T * K, dtype=torch.int32, device=DEV) for _ in range(2))
+    ws_bytes = max(hm.hmoe_permute_workspace_bytes(d, T), hm.hmoe_route_scores_workspace_bytes(d, T))
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+    scores = torch.empty(E, device=DEV)
+    lg_dev = to_device(lg)
+    hm.hmoe_route_permute(d, lg_dev, T, idx, w, offs, perm, inv, counts[shift:shift + E], ws, ws_bytes)
+    torch.cuda.synchronize()
+    hm.hmoe_route_scores(d, lg_dev, T, scores, scores_h[shift:shift + E], ws, ws_bytes)
+    torch.cuda.synchronize()
+    ridx, _ = orc.route(lg, K)
+    ro, _, _ = orc.permute(ridx, E)
+    assert np.array_equal(counts[shift:shift + E].numpy(), np.diff(ro))
+    assert np.array_equal(scores_h[shift:shift + E].numpy(), scores.cpu().numpy())
+    p = np.exp(lg.astype(np.float64) - lg.max(1, keepdims=True))
+    ref = (p / p.sum(1, keepdims=True)).mean(0)
+    # expf and the division to a few ulp, then fp32 sums of up to 64 tokens per wave and T / 64 partial sums
+    assert np.abs(scores.cpu().numpy() - ref).max() <= (16 + 64 + T / 64) * 2.0 ** -24 * ref.max()
+    if shift:
+        assert set(counts[:shift].tolist() + counts[-shift:].tolist()) == {-7} and set(scores_h[:shift].tolist()) == {-7.0}
