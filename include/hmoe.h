@@ -403,6 +403,51 @@ int32_t hmoe_route_ffn_combine(
     void* stream);
 
 /* ------------------------------------------------------------------------------------
+ * One forward pass of a layer, with every buffer named once in a struct the caller keeps: the calls that make up a
+ * pass (below) without a trip through the caller's language for each of them and for the events between two streams.
+ *   shared experts (shared_desc != NULL): inside the routed launches (hmoe_expert_ffn_grouped_with_shared) when
+ *       all_resident is set, T <= 32 and the layer is bf16; else hmoe_expert_ffn_grouped on side_stream, forked from
+ *       `stream` before the front end and joined before the sum;
+ *   logits == NULL: hmoe_router_route_permute(x, w_router); else hmoe_route_ffn_combine where that is the whole
+ *       rest of the pass, or hmoe_route_permute;
+ *   all_resident: hmoe_expert_ffn_grouped_gather (or _with_shared) over all experts; else hmoe_expert_ffn_staged, with
+ *       h_wave, h_slot, h_victim, n_waves and staged_bytes as there (else they are not touched and may be NULL);
+ *   hmoe_combine into y.
+ * shared_offsets holds {0, T} on the device.  Errors as in those calls.
+ */
+typedef struct {
+  const hmoe_layer_desc* desc;
+  hmoe_cache* cache;
+  const hmoe_layer_desc* shared_desc;   /* or NULL, then the shared_* and o_shared fields are not read */
+  hmoe_cache* shared_cache;
+  const void* w_router;                 /* or NULL: logits are always given */
+  float* logits;                        /* [T, E], written when none are given */
+  int32_t* topk_idx;
+  float* topk_w;
+  int32_t* expert_offsets;
+  int32_t* perm;
+  int32_t* inv_perm;
+  int32_t* h_counts_pinned;             /* read when all_resident is not set */
+  void* perm_workspace;
+  size_t perm_workspace_bytes;
+  void* o_perm;
+  void* workspace;
+  size_t workspace_bytes;
+  void* y;
+  const int32_t* shared_offsets;
+  void* o_shared;
+  void* shared_workspace;
+  size_t shared_workspace_bytes;
+  const void* const* h_packed_pinned;   /* read when all_resident is not set */
+  void* copy_stream;
+  void* side_stream;
+} hmoe_layer_call;
+
+int32_t hmoe_layer_forward(const hmoe_layer_call* call, const void* x, const float* logits, int32_t T, int32_t path,
+                           int32_t all_resident, int32_t* h_wave, int32_t* h_slot, int32_t* h_victim, int32_t* n_waves,
+                           uint64_t* staged_bytes, void* stream);
+
+/* ------------------------------------------------------------------------------------
  * Hybrid CPU-GPU scheduling simulation (Section IV-B).  HOST ONLY: no device work, no stream.
  * The activated experts of a layer (load > 0) are placed on three timelines -- CPU compute, GPU
  * compute, host-to-GPU transfer -- by the paper's priority rules: the GPU takes experts whose weights

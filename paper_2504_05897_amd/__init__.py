@@ -41,7 +41,7 @@ EXPORTS = [
     "hmoe_cache_evict", "hmoe_cache_pin_slot", "hmoe_cache_stage", "hmoe_cache_plan",
     "hmoe_ffn_workspace_bytes", "hmoe_expert_ffn_grouped", "hmoe_expert_ffn_grouped_gather", "hmoe_route_permute",
     "hmoe_router_route_permute", "hmoe_expert_ffn_grouped_with_shared", "hmoe_ffn_combine_sync_bytes", "hmoe_expert_ffn_combine",
-    "hmoe_route_ffn_combine",
+    "hmoe_route_ffn_combine", "hmoe_layer_forward",
     "hmoe_expert_ffn_staged",
     "hmoe_combine",
     "hmoe_cache_set_policy", "hmoe_cache_update_scores", "hmoe_cache_get_scores", "hmoe_cache_set_layer",
@@ -73,6 +73,16 @@ class LayerDesc(ctypes.Structure):
     def __repr__(self):
         return "LayerDesc(H=%d, F=%d, E=%d, K=%d, S=%d, %s)" % (
             self.hidden, self.ffn, self.n_experts, self.top_k, self.n_slots, "bf16" if self.dtype else "f32")
+
+
+class LayerCall(ctypes.Structure):
+    """Every buffer of one layer, for hmoe_layer_forward."""
+    _fields_ = [("desc", ctypes.POINTER(LayerDesc)), ("cache", ctypes.c_void_p), ("shared_desc", ctypes.POINTER(LayerDesc)),
+                ("shared_cache", ctypes.c_void_p)] + \
+               [(n, ctypes.c_size_t if n.endswith("_bytes") else ctypes.c_void_p) for n in (
+                   "w_router", "logits", "topk_idx", "topk_w", "expert_offsets", "perm", "inv_perm", "h_counts_pinned",
+                   "perm_workspace", "perm_workspace_bytes", "o_perm", "workspace", "workspace_bytes", "y", "shared_offsets",
+                   "o_shared", "shared_workspace", "shared_workspace_bytes", "h_packed_pinned", "copy_stream", "side_stream")]
 
 
 def _load() -> ctypes.CDLL:
@@ -114,6 +124,7 @@ def _load() -> ctypes.CDLL:
     lib.hmoe_expert_ffn_combine.argtypes = [dp, vp, vp, vp, vp, vp, vp, i32, vp, vp, sz, dp, vp, vp, vp, vp, sz, vp, vp, sz, i32, vp]
     lib.hmoe_route_ffn_combine.argtypes = [dp, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, sz, vp, vp, sz, dp, vp, vp, vp, vp, sz, vp, i32,
                                            vp]
+    lib.hmoe_layer_forward.argtypes = [ctypes.POINTER(LayerCall), vp, vp, i32, i32, i32, vp, vp, vp, vp, vp, vp]
     lib.hmoe_expert_ffn_staged.argtypes = [dp, vp, vp, vp, vp, i32, vp, vp, vp, vp, sz, i32, vp, vp, vp, vp, vp,
                                            ctypes.POINTER(i32), ctypes.POINTER(ctypes.c_uint64)]
     lib.hmoe_route_permute.argtypes = [dp, vp, i32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
@@ -539,12 +550,23 @@ class MoELayer:
             self.shared_ws_bytes = hmoe_ffn_workspace_bytes(self.shared_desc, T)
             self.shared_ws = torch.empty(max(self.shared_ws_bytes, 256), dtype=torch.uint8, device=dev)
             self._shared_T = -1
+        # what a forward pass in one library call needs: the layer's own buffers, which live as long as it does
+        has = self.shared_desc is not None
+        self._call = LayerCall(
+            ctypes.pointer(d), self.cache, ctypes.pointer(self.shared_desc) if has else None, self.shared_cache if has else None,
+            _ptr(self.w_router), _ptr(self.logits), _ptr(self.topk_idx), _ptr(self.topk_w), _ptr(self.offsets), _ptr(self.perm),
+            _ptr(self.inv_perm), _ptr(self.h_counts), _ptr(self.perm_ws), self.perm_ws_bytes, _ptr(self.o_perm), _ptr(self.ffn_ws),
+            self.ffn_ws_bytes, _ptr(self.y), _ptr(self.shared_offsets) if has else None, _ptr(self.o_shared) if has else None,
+            _ptr(self.shared_ws) if has else None, self.shared_ws_bytes if has else 0,
+            None if self.h_packed_ptrs is None else ctypes.addressof(self.h_packed_ptrs), self.copy_stream.cuda_stream,
+            self.side_stream.cuda_stream)
+        self._call_ref = ctypes.byref(self._call)
 
     def close(self):
         if getattr(self, "cache", None):
             torch.cuda.synchronize(self.dev)
             hmoe_cache_destroy(self.cache)
-            self.cache = None
+            self.cache = self._call.cache = None
             if self.shared_desc is not None:
                 hmoe_cache_destroy(self.shared_cache)
 
@@ -560,12 +582,30 @@ class MoELayer:
         """x [T, H] on the device (layer dtype); logits [T, E] fp32 or None (then x . W_g).
         Returns y [T, H] (a view of an internal buffer, valid until the next call)."""
         d = self.desc
-        T = int(x.shape[0])
+        T = x.shape[0]
         assert T <= self.max_tokens and x.dtype == self.dt and x.is_contiguous()
-        K, E = d.top_k, d.n_experts
-        A = T * K
         if all_resident is None:
             all_resident = d.n_slots == d.n_experts
+        if self.shared_desc is not None and self._shared_T != T:
+            self.shared_offsets.copy_(torch.tensor([0, T], dtype=torch.int32))
+            self._shared_T = T
+        if self.fused and self.overlap_shared and self.merge_shared and not self.merge_combine:
+            # the whole pass in one library call
+            plan = [None] * 5
+            if not all_resident:
+                wave, slot, victim = (np.empty(d.n_experts, np.int32) for _ in range(3))
+                n_waves, staged = ctypes.c_int32(), ctypes.c_uint64()
+                plan = [_ptr(wave), _ptr(slot), _ptr(victim), ctypes.addressof(n_waves), ctypes.addressof(staged)]
+            rc = _lib.hmoe_layer_forward(self._call_ref, x.data_ptr(), None if logits is None else logits.data_ptr(), T, path,
+                                         1 if all_resident else 0, *plan, torch.cuda.current_stream().cuda_stream)
+            if rc:
+                _check(rc, "hmoe_layer_forward")
+            if not all_resident:
+                self.last_plan = (wave, slot, victim, n_waves.value)
+                self.staged_bytes += int(staged.value)
+            return self.y[:T]
+        K, E = d.top_k, d.n_experts
+        A = T * K
         counts = None if all_resident else self.h_counts
         cur = torch.cuda.current_stream()
         o_shared = None
@@ -576,9 +616,6 @@ class MoELayer:
         if self.shared_desc is not None:
             # shared experts (Section II-A) see every token and do not depend on the routing: with
             # `fused` they run on a side stream next to the routed path
-            if self._shared_T != T:
-                self.shared_offsets.copy_(torch.tensor([0, T], dtype=torch.int32))
-                self._shared_T = T
             o_shared = self.o_shared
             if self.overlap_shared and not merged:
                 self.ev_fork.record(cur)
@@ -587,17 +624,6 @@ class MoELayer:
                     hmoe_expert_ffn_grouped(self.shared_desc, self.shared_cache, x, self.shared_offsets, T, None,
                                             self.o_shared, self.shared_ws, self.shared_ws_bytes, path)
                     self.ev_join.record(self.side_stream)
-        if (logits is not None and self.fused and all_resident and not self.merge_combine
-                and (self.shared_desc is None or merged)):
-            # routing, FFN (routed and shared) and the sum in one call: for decode batches with the routing inside the
-            # FFN's first launch
-            sd = self.shared_desc
-            hmoe_route_ffn_combine(d, self.cache, x, logits, T, self.topk_idx, self.topk_w, self.offsets, self.perm, self.inv_perm,
-                                   self.perm_ws, self.perm_ws_bytes, self.o_perm, self.ffn_ws, self.ffn_ws_bytes, sd,
-                                   None if sd is None else self.shared_cache, None if sd is None else self.shared_offsets,
-                                   o_shared, None if sd is None else self.shared_ws, 0 if sd is None else self.shared_ws_bytes,
-                                   self.y, path)
-            return self.y[:T]
         if logits is None and self.fused:
             hmoe_router_route_permute(d, x, self.w_router, T, self.logits, self.topk_idx, self.topk_w, self.offsets,
                                       self.perm, self.inv_perm, counts, self.perm_ws, self.perm_ws_bytes)

@@ -246,13 +246,14 @@ extern "C" int32_t hmoe_cache_create(const hmoe_layer_desc* desc, void* slot_sto
   c->slot_last_read.assign(desc->n_slots, 0);
   c->ready_ev.assign(desc->n_slots, nullptr);
   for (auto& e : c->use_ev) e = nullptr;
-  c->fence_ev = nullptr;
+  c->fence_ev = c->fork_ev = c->join_ev = nullptr;
   hipError_t err = hipGetDevice(&c->device);
   for (int i = 0; err == hipSuccess && i < hmoe_cache::RING; ++i)
     err = hipEventCreateWithFlags(&c->use_ev[i], hipEventDisableTiming);
   for (int i = 0; err == hipSuccess && i < desc->n_slots; ++i)
     err = hipEventCreateWithFlags(&c->ready_ev[i], hipEventDisableTiming);
-  if (err == hipSuccess) err = hipEventCreateWithFlags(&c->fence_ev, hipEventDisableTiming);
+  for (hipEvent_t* ev : {&c->fence_ev, &c->fork_ev, &c->join_ev})
+    if (err == hipSuccess) err = hipEventCreateWithFlags(ev, hipEventDisableTiming);
   if (err == hipSuccess)
     err = hipMemcpy(d_slot_of, c->slot_of.data(), sizeof(int32_t) * desc->n_experts, hipMemcpyHostToDevice);
   if (err != hipSuccess) {
@@ -269,7 +270,8 @@ extern "C" int32_t hmoe_cache_destroy(hmoe_cache* c) {
     if (e) (void)hipEventDestroy(e);
   for (auto e : c->ready_ev)
     if (e) (void)hipEventDestroy(e);
-  if (c->fence_ev) (void)hipEventDestroy(c->fence_ev);
+  for (auto e : {c->fence_ev, c->fork_ev, c->join_ev})
+    if (e) (void)hipEventDestroy(e);
   delete c;
   return HMOE_OK;
 }
@@ -758,4 +760,59 @@ extern "C" int32_t hmoe_expert_ffn_staged(const hmoe_layer_desc* desc, hmoe_cach
   }
   if (staged_bytes) *staged_bytes = staged;
   return HMOE_OK;
+}
+
+extern "C" int32_t hmoe_layer_forward(const hmoe_layer_call* call, const void* x, const float* logits, int32_t T, int32_t path,
+                                      int32_t all_resident, int32_t* h_wave, int32_t* h_slot, int32_t* h_victim, int32_t* n_waves,
+                                      uint64_t* staged_bytes, void* stream) {
+  if (!call || !call->cache) return HMOE_ERR_INVALID_ARG;
+  const hmoe_layer_call& c = *call;
+  int rc = check_desc(c.desc);
+  if (rc != HMOE_OK) return rc;
+  if (T < 0 || T > 0x7fffffff / c.desc->top_k) return HMOE_ERR_INVALID_ARG;
+  if (c.shared_desc && !c.shared_cache) return HMOE_ERR_INVALID_ARG;
+  const int32_t A = T * c.desc->top_k;
+  hipStream_t s = (hipStream_t)stream, side = (hipStream_t)c.side_stream;
+  const bool merged = c.shared_desc && all_resident && T <= 32 && c.desc->dtype == HMOE_BF16;
+  const bool aside = c.shared_desc && !merged;
+  if (aside) {
+    HMOE_HIP(hipEventRecord(c.shared_cache->fork_ev, s));
+    HMOE_HIP(hipStreamWaitEvent(side, c.shared_cache->fork_ev, 0));
+    rc = hmoe_expert_ffn_grouped(c.shared_desc, c.shared_cache, x, c.shared_offsets, T, nullptr, 0, c.o_shared, c.shared_workspace,
+                                 c.shared_workspace_bytes, path, side);
+    // (joined whatever it returned: `stream` must not run ahead of, nor a capture end without, the side stream)
+    HMOE_HIP(hipEventRecord(c.shared_cache->join_ev, side));
+  }
+  auto rest = [&]() -> int32_t {
+    if (rc != HMOE_OK) return rc;
+    int32_t* counts = all_resident ? nullptr : c.h_counts_pinned;
+    if (!logits) {
+      rc = hmoe_router_route_permute(c.desc, x, c.w_router, T, c.logits, c.topk_idx, c.topk_w, c.expert_offsets, c.perm, c.inv_perm,
+                                     counts, c.perm_workspace, c.perm_workspace_bytes, stream);
+    } else if (all_resident && !aside) {
+      return hmoe_route_ffn_combine(c.desc, c.cache, x, logits, T, c.topk_idx, c.topk_w, c.expert_offsets, c.perm, c.inv_perm,
+                                    c.perm_workspace, c.perm_workspace_bytes, c.o_perm, c.workspace, c.workspace_bytes, c.shared_desc,
+                                    c.shared_cache, c.shared_offsets, c.o_shared, c.shared_workspace, c.shared_workspace_bytes, c.y,
+                                    path, stream);
+    } else {
+      rc = hmoe_route_permute(c.desc, logits, T, c.topk_idx, c.topk_w, c.expert_offsets, c.perm, c.inv_perm, counts, c.perm_workspace,
+                              c.perm_workspace_bytes, stream);
+    }
+    if (rc != HMOE_OK) return rc;
+    if (!all_resident)
+      return hmoe_expert_ffn_staged(c.desc, c.cache, x, c.perm, c.expert_offsets, A, c.h_counts_pinned, c.h_packed_pinned, c.o_perm,
+                                    c.workspace, c.workspace_bytes, path, stream, c.copy_stream, h_wave, h_slot, h_victim, n_waves,
+                                    staged_bytes);
+    if (merged)
+      return hmoe_expert_ffn_grouped_with_shared(c.desc, c.cache, x, c.perm, c.expert_offsets, A, nullptr, 0, c.o_perm, c.workspace,
+                                                 c.workspace_bytes, c.shared_desc, c.shared_cache, c.shared_offsets, T, c.o_shared,
+                                                 c.shared_workspace, c.shared_workspace_bytes, path, stream);
+    return hmoe_expert_ffn_grouped_gather(c.desc, c.cache, x, c.perm, c.expert_offsets, A, nullptr, 0, c.o_perm, c.workspace,
+                                          c.workspace_bytes, path, stream);
+  };
+  rc = rest();
+  if (aside) HMOE_HIP(hipStreamWaitEvent(s, c.shared_cache->join_ev, 0));
+  if (rc != HMOE_OK) return rc;
+  if (logits && all_resident && !aside) return HMOE_OK;  // summed already
+  return hmoe_combine(c.desc, c.o_perm, c.inv_perm, c.topk_w, c.shared_desc ? c.o_shared : nullptr, T, c.y, stream);
 }

@@ -204,6 +204,7 @@ struct hmoe_cache {
   std::vector<uint64_t> slot_last_read;  // [S], 0 = never
   std::vector<hipEvent_t> ready_ev;      // [S]
   hipEvent_t fence_ev;
+  hipEvent_t fork_ev, join_ev;           // hmoe_layer_forward: around the shared experts' FFN on its side stream
   hmoe_layer_desc beside;                // hmoe_cache_set_layer: the routed layer these (shared) experts belong to
   bool has_beside;
 };

@@ -72,3 +72,43 @@ def test_route_ffn_combine_equals_the_separate_calls(hm, E, K, hidden, ffn, shar
                                   *shared, osh, *sws, y)
     assert ei.value.status == hm.HMOE_ERR_WORKSPACE
     layer.close()
+
+
+@pytest.mark.parametrize("dtype,shared_ffn,n_slots,logits_mode,tokens", [
+    ("bf16", (64,), 8, "zipf", (1, 8, 9, 32, 33, 70)),      # shared experts in the routed launches, then beside them
+    ("bf16", (64,), 8, "router", (1, 16, 17, 33, 5)),
+    ("bf16", (), 8, "router", (2, 40)),
+    ("bf16", (128,), 3, "zipf", (4, 40, 1)),                # staged, several waves
+    ("w4", (128,), 8, "zipf", (1, 16, 17)),
+    ("f32", (64,), 8, "router", (1, 33)),
+    ("f32", (), 4, "zipf", (3, 20)),
+])
+def test_forward_in_one_call_equals_the_calls(hm, dtype, shared_ffn, n_slots, logits_mode, tokens):
+    """MoELayer.forward (one library call) against the same layer with its switches set to make the calls itself: the same
+    bits, plans and slot maps, for batches of changing size, eagerly on a stream of the caller's."""
+    hidden, ffn = (128, 256) if dtype == "w4" else (128, 192)
+    shape = wl.small_shape(dtype=wl.F32 if dtype == "f32" else wl.BF16, hidden=hidden, ffn=ffn, n_experts=8, top_k=2,
+                           shared_ffn=shared_ffn, x_mode="rmsnorm", logits_mode=logits_mode)
+    base = wl.make_layer(shape, 61, 1)
+    d = hm.make_desc(hidden, ffn, 8, 2, n_slots, {"bf16": hm.HMOE_BF16, "f32": hm.HMOE_F32, "w4": hm.HMOE_BF16_W4}[dtype])
+    one, calls = (hm.MoELayer(d, base.experts, base.shared, base.w_router, max_tokens=max(tokens)) for _ in range(2))
+    calls.overlap_shared = calls.merge_shared = False
+    stream = torch.cuda.Stream()
+    for rep, T in enumerate(tokens):
+        print("forward in one call", dtype, shared_ffn, n_slots, T, flush=True)
+        lay = wl.make_layer(shape, 100 + rep, T, with_weights=False)
+        x = to_device(lay.x)
+        lg = None if logits_mode == "router" else to_device(lay.logits)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            a, b = one.forward(x, lg), calls.forward(x, lg)
+            stream.synchronize()
+        for p, q in ((a, b), (one.topk_w[:T], calls.topk_w[:T]), (one.perm[:2 * T], calls.perm[:2 * T]), (one.offsets, calls.offsets)):
+            assert torch.equal(p.cpu(), q.cpu()), T
+        assert one.slot_map() == calls.slot_map() and one.staged_bytes == calls.staged_bytes
+        if n_slots < 8:
+            assert all(np.array_equal(p, q) for p, q in zip(one.last_plan, calls.last_plan))
+    one.close()
+    with pytest.raises(hm.HmoeError):
+        one.forward(x, lg)
+    calls.close()
