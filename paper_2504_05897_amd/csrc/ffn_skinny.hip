@@ -101,21 +101,25 @@ __device__ __forceinline__ int count_busy_experts(const SkinnyCtx& c, int lane) 
   return seen;
 }
 
-// id of the `want`-th expert (ascending) that is active, resident and has rows; -1 if fewer
-__device__ __forceinline__ int nth_busy_expert(const SkinnyCtx& c, int want, int lane) {
-  int seen = 0;
+// The `want`-th expert (ascending) that is active, resident and has rows: its cache slot and sorted rows [first, end), uniform over
+// the wave; false if there are fewer.  Slots and offsets come in one trip to memory (64 experts at a time).
+__device__ __forceinline__ bool nth_busy_expert(const SkinnyCtx& c, int want, int lane, int& slot, int& first, int& end) {
   for (int base = 0; base < c.n_experts; base += 64) {
-    const int e = base + lane;
-    const bool busy = e < c.n_experts && c.active.test(e) && c.slot_of[e] >= 0 && c.offsets[e + 1] > c.offsets[e];
-    uint64_t m = __ballot(busy);
-    const int n = __popcll(m);
-    if (want < seen + n) {
-      for (int i = seen; i < want; ++i) m &= m - 1;
-      return base + __ffsll((long long)m) - 1;
+    const int e = base + lane, at = min(e, c.n_experts - 1);
+    const int s = c.slot_of[at], b = c.offsets[at], n = c.offsets[at + 1];
+    uint64_t m = __ballot(e < c.n_experts && c.active.test(at) && s >= 0 && n > b);
+    const int busy = __popcll(m);
+    if (want < busy) {
+      for (int i = 0; i < want; ++i) m &= m - 1;
+      const int l = __ffsll((long long)m) - 1;
+      slot = __builtin_amdgcn_readlane(s, l);
+      first = __builtin_amdgcn_readlane(b, l);
+      end = __builtin_amdgcn_readlane(n, l);
+      return true;
     }
-    seen += n;
+    want -= busy;
   }
-  return -1;
+  return false;
 }
 
 // GATEUP: in = x_perm [A, H], out = h [A, F];  else: in = h [A, F], out = o_perm [A, H].
@@ -198,12 +202,10 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_kernel(SkinnyCtx c, const 
     slot = c.slots + (size_t)s * c.slot_bytes;
     block_in_matrix = blockIdx.x;
   } else {
-    const int e = nth_busy_expert(c, (int)blockIdx.y - c.shared.grid_rows, lane);
-    if (e < 0) return;
-    row_first = c.offsets[e];
-    row_end = c.offsets[e + 1];
+    int s;
+    if (!nth_busy_expert(c, (int)blockIdx.y - c.shared.grid_rows, lane, s, row_first, row_end)) return;
     ffn = c.ffn;
-    slot = c.slots + (size_t)c.slot_of[e] * c.slot_bytes;
+    slot = c.slots + (size_t)s * c.slot_bytes;
     block_in_matrix = blockIdx.x;
     row_map = c.row_map;
   }
@@ -487,13 +489,20 @@ int launch_ffn_skinny(const FfnArgs& a, const FfnArgs* dense, const CombineArgs*
 // ---------------------------------------------------------------------------------------------
 // 4-bit weights (HMOE_BF16_W4): the same organisation around the weight stream, a quarter of the bytes.
 //
-// A block owns two adjacent packed 16-row groups of one busy expert: gate and up of 16 features, or 32
+// A block owns P pairs of adjacent packed 16-row groups of one busy expert: gate and up of 16 features, or 32
 // features of the down projection.  The unit of work is a scale
 // group of 128 k: one 1 KiB unit of codes per 16-row group (one 16-byte non-temporal load per lane), four
 // token fragments and one scale per lane and 16-row group.  Scale groups are dealt round-robin to the NW
-// waves (the block sweeps a contiguous stretch of the stream) and the codes of DEPTH groups are in
-// flight per wave: a group is multiplied in a fraction of the memory latency, so a single group of
-// lookahead would leave the wave waiting.
+// waves (the block sweeps a contiguous stretch of the stream) and DEPTH groups are in flight per wave.
+//
+// Everything is loaded through buffer descriptors: a scalar base, a scalar offset per load and one lane offset for all, and
+// lanes without a token get an offset past the end, which fetches nothing.  With 64-bit addresses per lane the kernel held
+// 190 registers, so 8 waves per CU, spent as many vector instructions on addresses as on codes, and every wave fetched the
+// first token 16 times over.  At 124 registers twice the waves are resident, two groups each in flight are enough (more are
+// slower), and there is room for two pairs per block (see launch_stage_w4).  Layers, before -> now, us: 8 experts of 4096 x
+// 14336, top 2, 1 / 2 / 4 / 8 / 16 tokens 59.1 -> 50.4, 84.0 -> 77.2, 120.7 -> 110.2, 140.3 -> 127.9, 159.8 -> 143.8; 64 of
+// 2048 x 1408, top 6, 1 / 16 tokens 36.1 -> 33.8, 81.0 -> 76.5; 40 of 3584 x 2560, top 8, one shared, 1 / 8 tokens 72.7 -> 61.4,
+// 109.5 -> 100.2; 8 of 1024 x 2048, top 2, 3 tokens 26.7 -> 22.1.
 //
 // The matrix instruction is v_mfma_f32_16x16x32_bf16: up to 16 tokens x 16 features x 32 k, four
 // accumulator registers, which suits decode (the 32x32x16 shape spends twice the cycles and four times the
@@ -505,54 +514,49 @@ int launch_ffn_skinny(const FfnArgs& a, const FfnArgs* dense, const CombineArgs*
 // and the group's scale (per feature = per lane) multiplies that difference as it is added to the
 // running fp32 result.  Products x * (128 + q) are exact in fp32; the cancellation costs about 5 of
 // its 24 mantissa bits.
-template <bool GATEUP, int NW>
-__global__ __launch_bounds__(64 * NW) void ffn_skinny_w4_kernel(SkinnyCtx c, const bf16_t* __restrict__ in,
-                                                                 bf16_t* __restrict__ out) {
-  constexpr int NU = 2;                    // packed 16-row groups per block
-  constexpr int FEAT = GATEUP ? 16 : 32;   // output features per block
-  constexpr int MR = 16;              // rows per pass
-  constexpr int DEPTH = 4;
+template <bool GATEUP, int NW, int P>
+__global__ __launch_bounds__(64 * NW, P == 1 ? 4 : 3) void ffn_skinny_w4_kernel(SkinnyCtx c, const bf16_t* __restrict__ in,
+                                                                               bf16_t* __restrict__ out, uint32_t in_bytes) {
+  constexpr int NU = 2 * P;                         // packed 16-row groups per block
+  constexpr int FEAT = GATEUP ? 16 * P : 32 * P;    // output features per block
+  constexpr int MR = 16;                            // rows per pass
+  constexpr int DEPTH = GATEUP && P == 1 ? 3 : 2;   // scale groups in flight per wave
   __shared__ float red[(NW > 1 ? NW - 1 : 1) * NU * 4 * 64];
 
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int e = nth_busy_expert(c, blockIdx.y, lane);
-  if (e < 0) return;  // uniform over the block
-  const int row_first = c.offsets[e], row_end = c.offsets[e + 1];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  int cache_slot, row_first, row_end;
+  if (!nth_busy_expert(c, blockIdx.y, lane, cache_slot, row_first, row_end)) return;  // uniform over the block
   const int K = GATEUP ? c.hidden : c.ffn;      // reduction length
   const int n_out = GATEUP ? c.ffn : c.hidden;  // row length of `out`
   const int n_groups = K / W4_GROUP;
   const int fb = blockIdx.x;                    // features [FEAT fb, FEAT fb + FEAT) of `out`
-  if (fb >= n_out / FEAT) return;
   const int j = lane % 16, kblk = lane / 16;
-  const char* slot = c.slots + (size_t)c.slot_of[e] * c.slot_bytes;
+  const char* slot = c.slots + (size_t)cache_slot * c.slot_bytes;
   const W4Offsets off = w4_offsets((size_t)c.hidden, (size_t)c.ffn);
-  const u32x4* units = (const u32x4*)(slot + (GATEUP ? 0 : off.down_units));
-  const bf16_t* scales = (const bf16_t*)(slot + (GATEUP ? off.gate_up_scales : off.down_scales));
-  // packed 16-row group 2 fb + u: gate/up u = 0, 1 are gate and up of features 16 fb .. + 16; down u = 0, 1 are
-  // features 32 fb .. + 16 and the next 16
-  const u32x4* wq[NU];
-  const bf16_t* ws[NU];
-#pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    const size_t grp = (size_t)NU * fb + u;
-    wq[u] = units + grp * (size_t)n_groups * 64 + lane;
-    ws[u] = scales + grp * (size_t)n_groups * 16 + j;
-  }
+  const char* units = slot + (GATEUP ? 0 : off.down_units);
+  const char* scales = slot + (GATEUP ? off.gate_up_scales : off.down_scales);
+  // Packed groups NU fb + u: gate/up u = 0, 1 are gate and up of features 16 P fb .. + 16, u = 2, 3 of the next 16; down u is
+  // features 32 P fb + 16 u .. + 16.  (hidden and ffn are multiples of 128: every block has all of its groups.)
+  const __amdgpu_buffer_rsrc_t w_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(units + (size_t)NU * fb * n_groups * 1024), 0, NU * n_groups * 1024, 0x00027000);
+  const __amdgpu_buffer_rsrc_t s_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(scales + (size_t)NU * fb * n_groups * 32), 0, NU * n_groups * 32, 0x00027000);
+  const uint32_t code_lane = 16 * lane, scale_lane = 2 * j;
   const int per_wave = (n_groups + NW - 1) / NW;  // scale groups per wave (the last ones may lie past the end)
   const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+  const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)in, 0, in_bytes, 0x00027000);
 
   for (int row0 = row_first; row0 < row_end; row0 += MR) {
     const int rows = min(MR, row_end - row0);
-    const int tok = j < rows ? j : 0;  // lane (j, kblk) supplies token j, k block kblk of the token operand (clamped)
+    const int tok = j < rows ? j : 0;  // lane (j, kblk) supplies token j, k block kblk of the token operand
     const int in_row = GATEUP ? mapped_row(c.row_map, c.map_div, row0 + tok) : row0 + tok;
-    const u32x4* xin = (const u32x4*)(in + (size_t)in_row * K) + kblk;
+    // (lanes without a token: an offset past the end, which fetches nothing and returns zero)
+    const uint32_t xin = j < rows ? (uint32_t)in_row * (uint32_t)(2 * K) + 16 * kblk : 0xFFFFFFF0u;
 
-    // ring of DEPTH scale groups per wave: codes, scales and the matching token fragments (the fragments
-    // come from L1/L2, but a group is multiplied faster than even that latency).  Every load is issued
-    // unconditionally from a clamped, valid address -- no branches around loads, so the compiler's count
-    // of outstanding loads stays exact and a multiply waits only for its own group.  A group past the end
-    // contributes nothing because its scale is replaced by zero at use; token rows past `rows` only reach
-    // accumulator rows that are never stored.
+    // Ring of DEPTH scale groups per wave: codes, scales and the matching token fragments.  Every load is issued
+    // unconditionally -- no branches around loads, so the compiler's count of outstanding loads stays exact and a multiply
+    // waits only for its own group.  A group past the end is the last one once more and contributes nothing because its
+    // scale is replaced by zero at use.
     u32x4 codes[DEPTH][NU], xa[DEPTH][4];
     uint32_t scale_bits[DEPTH][NU];  // raw bfloat16: converting here would make the wave wait for the load at once
     bool live[DEPTH];
@@ -562,11 +566,12 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_w4_kernel(SkinnyCtx c, con
       const int gc = min(g, n_groups - 1);
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
-        codes[slot_id][u] = __builtin_nontemporal_load(wq[u] + (size_t)gc * 64);
-        scale_bits[slot_id][u] = (uint32_t)ws[u][(size_t)gc * 16];
+        codes[slot_id][u] = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, code_lane, (u * n_groups + gc) * 1024, 2);
+        scale_bits[slot_id][u] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(s_rsrc, scale_lane, (u * n_groups + gc) * 32, 0);
       }
 #pragma unroll
-      for (int t = 0; t < 4; ++t) xa[slot_id][t] = xin[(size_t)(16 * gc + 4 * t)];
+      for (int t = 0; t < 4; ++t)
+        xa[slot_id][t] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, xin, 256 * gc + 64 * t, 0);
     };
 
     f32x4_t acc[NU];
@@ -631,11 +636,14 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_w4_kernel(SkinnyCtx c, con
         const int m = 4 * kblk + r;
         if (m >= rows) continue;
         bf16_t* orow = out + (size_t)(row0 + m) * n_out + FEAT * fb + j;
-        if (GATEUP) {
-          orow[0] = f32_to_bf16(silu_f32(acc[0][r]) * acc[1][r]);
-        } else {
-          orow[0] = f32_to_bf16(acc[0][r]);
-          orow[16] = f32_to_bf16(acc[1][r]);
+#pragma unroll
+        for (int u = 0; u < NU; u += 2) {
+          if (GATEUP) {
+            orow[8 * u] = f32_to_bf16(silu_f32(acc[u][r]) * acc[u + 1][r]);
+          } else {
+            orow[16 * u] = f32_to_bf16(acc[u][r]);
+            orow[16 * u + 16] = f32_to_bf16(acc[u + 1][r]);
+          }
         }
       }
     }
@@ -643,23 +651,30 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_w4_kernel(SkinnyCtx c, con
   }
 }
 
+// Two pairs of packed groups per block once that leaves the launch blocks enough (gate/up four per CU, the down projection with
+// its longer K one): the token fragments and their sums then serve twice the codes.  Four waves share K then, eight where there
+// are fewer than two such blocks per CU.  8 experts of 4096 x 14336 (layer, us), one pair / two: gate/up at 1 token 50.4 / 51.8, 2
+// tokens 78.8 / 76.5, 8 tokens 138 / 130; down at 1 token 51.8 / 57.6, 2 tokens 78.8 / 76.5; two pairs with one / four waves at
+// 16 tokens 144.1 / 141.7.  One pair: as few waves per block as still put six on every CU (one wave walks its groups without
+// draining: gate/up at 1 token with one / two waves 50.4 / 55.5).
 template <bool GATEUP>
-static void launch_stage_w4(const SkinnyCtx& c, int n_out, int busy_max, const bf16_t* in, bf16_t* out, hipStream_t s) {
-  const dim3 grid((unsigned)(n_out / (GATEUP ? 16 : 32)), (unsigned)busy_max);
-  // Waves per block (they split K).  A wave that walks many scale groups keeps its ring of loads full; a
-  // block whose waves each see only a few groups spends its life filling and draining it.  So: as few waves
-  // per block as still put about eight waves on every CU (measured: one wave per block is best for the wide
-  // gate/up launch, eight for the down projection of two experts).
-  const long blocks = (long)grid.x * grid.y;
+static void launch_stage_w4(const SkinnyCtx& c, int n_out, int busy_max, const bf16_t* in, uint32_t in_bytes, bf16_t* out,
+                            hipStream_t s) {
+  const int feat = GATEUP ? 16 : 32;  // output features per pair
   const int n_groups = (GATEUP ? c.hidden : c.ffn) / W4_GROUP;
-  int waves = 1;
-  while (waves < 8 && blocks * waves < 2048 && n_groups / (2 * waves) >= 2) waves *= 2;
+  const long blocks2 = (long)(n_out / (2 * feat)) * busy_max;
+  const bool two = blocks2 >= (GATEUP ? 1024 : 256) && n_groups >= 8;
+  const dim3 grid((unsigned)(n_out / ((two ? 2 : 1) * feat)), (unsigned)busy_max);
+  const long blocks = (long)grid.x * grid.y;
+  int waves = two ? (blocks < 512 && n_groups >= 16 ? 8 : 4) : 1;
+  while (!two && waves < 8 && blocks * waves < 1536 && n_groups / (2 * waves) >= 2) waves *= 2;
   if (const char* env = getenv("HMOE_W4_WAVES")) waves = atoi(env);  // tuning override: 1, 2, 4 or 8
+  auto launch = [&](auto kernel, int nw) { hipLaunchKernelGGL(kernel, grid, dim3(64 * nw), 0, s, c, in, out, in_bytes); };
   switch (waves) {
-    case 1: hipLaunchKernelGGL((ffn_skinny_w4_kernel<GATEUP, 1>), grid, dim3(64), 0, s, c, in, out); break;
-    case 2: hipLaunchKernelGGL((ffn_skinny_w4_kernel<GATEUP, 2>), grid, dim3(128), 0, s, c, in, out); break;
-    case 4: hipLaunchKernelGGL((ffn_skinny_w4_kernel<GATEUP, 4>), grid, dim3(256), 0, s, c, in, out); break;
-    default: hipLaunchKernelGGL((ffn_skinny_w4_kernel<GATEUP, 8>), grid, dim3(512), 0, s, c, in, out); break;
+    case 1: two ? launch(&ffn_skinny_w4_kernel<GATEUP, 1, 2>, 1) : launch(&ffn_skinny_w4_kernel<GATEUP, 1, 1>, 1); break;
+    case 2: two ? launch(&ffn_skinny_w4_kernel<GATEUP, 2, 2>, 2) : launch(&ffn_skinny_w4_kernel<GATEUP, 2, 1>, 2); break;
+    case 4: two ? launch(&ffn_skinny_w4_kernel<GATEUP, 4, 2>, 4) : launch(&ffn_skinny_w4_kernel<GATEUP, 4, 1>, 4); break;
+    default: two ? launch(&ffn_skinny_w4_kernel<GATEUP, 8, 2>, 8) : launch(&ffn_skinny_w4_kernel<GATEUP, 8, 1>, 8); break;
   }
 }
 
@@ -669,11 +684,14 @@ int launch_ffn_skinny_w4(const FfnArgs& a) {
   if (a.n_rows == 0) return HMOE_OK;
   SkinnyCtx c{a.offsets, a.slot_of, a.slots, a.slot_bytes, a.active, d.n_experts, d.hidden, d.ffn, 1, a.row_map, a.map_div, {}, {}, {}};
   const int busy_max = std::min(d.n_experts, a.n_rows);  // every busy expert has at least one row
+  const size_t in_rows = a.row_map ? (size_t)a.n_rows / a.map_div : a.n_rows;
+  const size_t in_bytes = in_rows * d.hidden * 2, h_bytes = (size_t)a.n_rows * d.ffn * 2;
+  if (in_bytes > 0xF0000000u || h_bytes > 0xF0000000u) return launch_ffn_tiled_w4(a);
   probe_before(a.stream);
-  launch_stage_w4<true>(c, d.ffn, busy_max, (const bf16_t*)a.x_perm, (bf16_t*)a.h, a.stream);
+  launch_stage_w4<true>(c, d.ffn, busy_max, (const bf16_t*)a.x_perm, (uint32_t)in_bytes, (bf16_t*)a.h, a.stream);
   probe_after(a.stream);
   probe_before(a.stream);
-  launch_stage_w4<false>(c, d.hidden, busy_max, (const bf16_t*)a.h, (bf16_t*)a.o_perm, a.stream);
+  launch_stage_w4<false>(c, d.hidden, busy_max, (const bf16_t*)a.h, (uint32_t)h_bytes, (bf16_t*)a.o_perm, a.stream);
   probe_after(a.stream);
   HMOE_HIP(hipGetLastError());
   return HMOE_OK;

@@ -98,3 +98,34 @@ def test_mixtral_w4_full_size(hm, T):
     ref = orc.moe_layer(wl.as_f64(lay.x), logits, shape.top_k, lay.experts, (), token_subset=sub, to_f64=as_quantised)
     assert max_rel_err(to_host_f32(y)[sub], ref) < TOL[wl.BF16]
     layer.close()
+
+
+# The decode kernel's blocks of two pairs of packed groups: gate/up takes them from 1024 blocks on (with four waves), the down
+# projection from 256 (eight waves below 512).  9, 8 and 17 scale groups for the waves, rows of one and of several passes.
+@pytest.mark.parametrize("hidden,ffn,counts", [
+    (1152, 1152, [1, 0, 16, 17] + [0, 1] * 14), (1024, 2176, [33, 0, 2, 16] + [1] * 12), (1024, 2176, [0] * 15 + [16]),
+    (2048, 1024, [3] * 31 + [15]),
+])
+def test_w4_decode_blocks_of_two_pairs(hm, hidden, ffn, counts):
+    print("w4 decode two pairs", hidden, ffn, counts, flush=True)
+    E = len(counts)
+    shape = wl.small_shape(dtype=wl.BF16, hidden=hidden, ffn=ffn, n_experts=3, top_k=1)
+    three = wl.make_layer(shape, hidden + ffn, n_tokens=1).experts
+    values = [[w4.dequantize_w4(*w4.quantize_w4(wl.as_f32(m))) for m in e] for e in three]
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    A = int(offsets[-1])
+    d = hm.make_desc(hidden, ffn, E, 1, E, hm.HMOE_BF16_W4)
+    layer = hm.MoELayer(d, [three[e % 3] for e in range(E)], (), None, max_tokens=A, host_copies=False)
+    x = wl.store(np.random.default_rng(7).standard_normal((A, hidden)).astype(np.float32), wl.BF16)
+    o = torch.full((A, hidden), float("nan"), dtype=torch.bfloat16, device=DEV)
+    n_rows = max(A, E)                                    # the launch only knows how many rows there may be
+    ws_bytes = hm.hmoe_ffn_workspace_bytes(d, n_rows)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+    hm.hmoe_expert_ffn_grouped(d, layer.cache, to_device(x), to_device(offsets), n_rows, None, o, ws, ws_bytes, hm.HMOE_FFN_SKINNY)
+    torch.cuda.synchronize()
+    ref = np.zeros((A, hidden))
+    for e, (lo, hi) in enumerate(zip(offsets[:-1], offsets[1:])):
+        if hi > lo:
+            ref[lo:hi] = orc.expert_ffn(wl.as_f64(x[lo:hi]), *values[e % 3])
+    assert max_rel_err(to_host_f32(o), ref) < TOL[wl.BF16]
+    layer.close()
