@@ -408,8 +408,9 @@ int32_t hmoe_route_ffn_combine(
  *   shared experts (shared_desc != NULL): inside the routed launches (hmoe_expert_ffn_grouped_with_shared) when
  *       all_resident is set, T <= 32 and the layer is bf16; else hmoe_expert_ffn_grouped on side_stream, forked from
  *       `stream` before the front end and joined before the sum;
- *   logits == NULL: hmoe_router_route_permute(x, w_router); else hmoe_route_ffn_combine where that is the whole
- *       rest of the pass, or hmoe_route_permute;
+ *   logits == NULL: hmoe_router_route_permute(x, w_router), or, for the decode batches that hmoe_route_ffn_combine routes
+ *       itself, hmoe_router_logits(x, w_router) into `logits` and then that call;
+ *   else hmoe_route_ffn_combine where that is the whole rest of the pass, or hmoe_route_permute;
  *   all_resident: hmoe_expert_ffn_grouped_gather (or _with_shared) over all experts; else hmoe_expert_ffn_staged, with
  *       h_wave, h_slot, h_victim, n_waves and staged_bytes as there (else they are not touched and may be NULL);
  *   hmoe_combine into y.

@@ -786,6 +786,13 @@ extern "C" int32_t hmoe_layer_forward(const hmoe_layer_call* call, const void* x
   auto rest = [&]() -> int32_t {
     if (rc != HMOE_OK) return rc;
     int32_t* counts = all_resident ? nullptr : c.h_counts_pinned;
+    if (!logits && all_resident && !aside && ffn_skinny_routes(*c.desc, T) && (path == HMOE_FFN_AUTO || path == HMOE_FFN_SKINNY)) {
+      // routed inside the FFN's first launch: the router's own launch then has nothing to wait for but its products, and
+      // is spread over the experts instead of ending in one block that has all of them
+      rc = hmoe_router_logits(c.desc, x, c.w_router, T, c.logits, stream);
+      logits = c.logits;
+    }
+    if (rc != HMOE_OK) return rc;
     if (!logits) {
       rc = hmoe_router_route_permute(c.desc, x, c.w_router, T, c.logits, c.topk_idx, c.topk_w, c.expert_offsets, c.perm, c.inv_perm,
                                      counts, c.perm_workspace, c.perm_workspace_bytes, stream);

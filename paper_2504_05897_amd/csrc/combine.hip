@@ -137,7 +137,23 @@ __global__ __launch_bounds__(SHAPE::THREADS, SHAPE::WAVES_PER_SIMD) void router_
                                                                             int n_experts, int hidden,
                                                                             float* __restrict__ logits, int tokens_per_block) {
   __shared__ float red[SHAPE::RED];
-  router_logits_block<SHAPE>(x, w_g, n_tokens, n_experts, hidden, logits, tokens_per_block, red, nullptr);
+  router_logits_block<SHAPE>(x, w_g, n_tokens, n_experts, hidden, logits, tokens_per_block, red, nullptr, n_experts);
+}
+
+// A decode batch: 16 experts per block, so that a router of many is read through several CUs (one block reads it at about 15
+// bytes per clock).  With the routing in the FFN's first launch, against one block that computes, routes and ranks (layer, us):
+// 64 experts of 2048 x 1408, top 6, 1 token 44.1 -> 37.9; 90 of 1024 x 512, top 8, 2 tokens 32.3 -> 26.1; 24 of 4096 x 1024, top
+// 2, 3 tokens 45.3 -> 41.5; 8 of 4096 x 14336, top 2, 8 tokens 381.9 -> 381.1.
+constexpr int ROUTER_SPLIT_EXPERTS = 16;
+__global__ __launch_bounds__(1024) void router_logits_bf16_split_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_g,
+                                                                        int n_tokens, int n_experts, int hidden,
+                                                                        float* __restrict__ logits) {
+  typedef RouterShape<1, 1, 16, 16> SHAPE;
+  static_assert(SHAPE::EXPERT_FRAGS * 16 == ROUTER_SPLIT_EXPERTS && SHAPE::THREADS == 1024, "");
+  __shared__ float red[SHAPE::RED];
+  const int e0 = blockIdx.y * ROUTER_SPLIT_EXPERTS;
+  router_logits_block<SHAPE>(x, w_g + (long)e0 * hidden, n_tokens, min(n_experts - e0, ROUTER_SPLIT_EXPERTS), hidden, logits + e0, 16, red,
+                             nullptr, n_experts);
 }
 
 }  // namespace hmoe
@@ -183,7 +199,9 @@ extern "C" int32_t hmoe_router_logits(const hmoe_layer_desc* desc, const void* x
 #define HMOE_LAUNCH_LOGITS(G, VPL, MA, NF, KS, NW)                                                                 \
   hipLaunchKernelGGL((router_logits_bf16_kernel<RouterShape<MA, NF, KS, NW>>), grid, dim3(64 * NW), 0, s, (const bf16_t*)x, \
                      (const bf16_t*)w_g, T, E, H, logits, tpb)
-    if (T <= ROUTER_SMALL_T) HMOE_ROUTER_SHAPES_ONE_BLOCK(E, HMOE_LAUNCH_LOGITS);
+    if (T <= ROUTER_SMALL_T)
+      hipLaunchKernelGGL(router_logits_bf16_split_kernel, dim3(1, (unsigned)((E + ROUTER_SPLIT_EXPERTS - 1) / ROUTER_SPLIT_EXPERTS)),
+                         dim3(1024), 0, s, (const bf16_t*)x, (const bf16_t*)w_g, T, E, H, logits);
     else HMOE_ROUTER_SHAPES_MANY(E, tpb, HMOE_LAUNCH_LOGITS);
 #undef HMOE_LAUNCH_LOGITS
   } else {

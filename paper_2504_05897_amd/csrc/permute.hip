@@ -294,7 +294,7 @@ __device__ __forceinline__ void front_tokens_body(const bf16_t* __restrict__ x, 
   constexpr int MAX_EXPERTS = SHAPE::EXPERT_FRAGS * 16;
   __shared__ float red[SHAPE::RED];
   __shared__ float lds_logits[SHAPE::MA * 16 * MAX_EXPERTS];
-  router_logits_block<SHAPE>(x, w_g, n_tokens, n_experts, hidden, logits, tokens_per_block, red, lds_logits);  // ends with a barrier
+  router_logits_block<SHAPE>(x, w_g, n_tokens, n_experts, hidden, logits, tokens_per_block, red, lds_logits, n_experts);  // ends with a barrier
   constexpr int TOKENS_PER_PASS = SHAPE::THREADS / G;
   const long t0 = (long)blockIdx.x * tokens_per_block;
   for (int l0 = 0; l0 < tokens_per_block; l0 += TOKENS_PER_PASS) {

@@ -42,12 +42,12 @@ struct RouterShape {
 // K = 4096, 17 to 2048 tokens 54 -> 34 us (four waves: 35); 16384 tokens 214 -> 79 us (92).  Blocks of up to 32 tokens
 // halve the reads of w_g of large batches.
 //
-// tokens_per_block <= 16 MA.  logits [T, E] global out; lds_logits [tokens_per_block * E] the same values in LDS, or
+// tokens_per_block <= 16 MA.  logits [T, logit_pitch] global out (E columns of it); lds_logits [tokens_per_block * E] the same values in LDS, or
 // NULL.  Ends with a block barrier.
 template <class SHAPE>
 __device__ __forceinline__ void router_logits_block(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_g,
                                                     int n_tokens, int n_experts, int hidden, float* __restrict__ logits,
-                                                    int tokens_per_block, float* red, float* lds_logits) {
+                                                    int tokens_per_block, float* red, float* lds_logits, int logit_pitch) {
   constexpr int MA = SHAPE::MA, NF = SHAPE::NF, KS = SHAPE::KS, EF = SHAPE::EXPERT_FRAGS;
   constexpr int U = SHAPE::STEPS;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
@@ -148,7 +148,7 @@ __device__ __forceinline__ void router_logits_block(const bf16_t* __restrict__ x
         v = w == 0 ? quarter_sum : v + quarter_sum;
       }
       if (tok < tokens_per_block && t0 + tok < n_tokens && e < n_experts) {
-        logits[(t0 + tok) * n_experts + e] = v;
+        logits[(t0 + tok) * logit_pitch + e] = v;
         if (lds_logits) lds_logits[tok * n_experts + e] = v;
       }
     }
