@@ -138,7 +138,7 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_kernel(SkinnyCtx c, const 
   // that shares the launch.  Everything below is uniform over the block.
   const bool dense = (int)blockIdx.y < c.shared.grid_rows;
   int row_first, row_end, ffn, block_in_matrix;
-  int token = 0;  // RV > 0: input row of this lane's column of the token operand
+  uint64_t assigned = 0;  // RV > 0: the expert's assignments that no pass has taken yet
   const char* slot;
   const int32_t* row_map = nullptr;
   if (dense) {
@@ -191,13 +191,8 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_kernel(SkinnyCtx c, const 
     }
     if (e < 0) return;  // uniform over the block
     row_first = __popcll(__ballot(mine < e));
-    uint64_t assigned = __ballot(mine == e);  // its assignments in ascending order are its rows
+    assigned = __ballot(mine == e);  // in ascending order its rows
     row_end = row_first + __popcll(assigned);
-    for (int r = 0; assigned; ++r) {
-      const int a = __ffsll((long long)assigned) - 1;
-      assigned &= assigned - 1;
-      if (lane % 32 == r) token = a / rt.top_k;
-    }
     ffn = c.ffn;
     slot = c.slots + (size_t)s * c.slot_bytes;
     block_in_matrix = blockIdx.x;
@@ -226,8 +221,17 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_kernel(SkinnyCtx c, const 
     const int rows = min(MR, row_end - row0);
     const bool has_row = col < rows;
     int in_row = row0 + (has_row ? col : 0);
-    if (RV > 0 && !dense) in_row = token;  // (at most 8 rows: a single pass)
-    else if (GATEUP) in_row = mapped_row(row_map, c.map_div, in_row);
+    if (RV > 0 && !dense) {
+      // (More than one pass: a token whose logits are the lowest NaN names the same expert several times.)
+      in_row = 0;
+      for (int r = 0; r < rows; ++r) {
+        const int a = __ffsll((long long)assigned) - 1;
+        assigned &= assigned - 1;
+        if (col == r) in_row = a / c.route.top_k;
+      }
+    } else if (GATEUP) {
+      in_row = mapped_row(row_map, c.map_div, in_row);
+    }
     const u32x4* xin = (const u32x4*)(in + (size_t)in_row * K) + half;
 
     u32x4 wa[2][U], wb[2][U], xa[2][U];

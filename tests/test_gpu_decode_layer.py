@@ -74,6 +74,41 @@ def test_route_ffn_combine_equals_the_separate_calls(hm, E, K, hidden, ffn, shar
     layer.close()
 
 
+# A logit of bits 0xFFFFFFFF (the lowest NaN) sorts like a retired expert: a token with fewer others than K names one expert
+# several times, and an expert then has more rows than the batch has tokens (15 to 31: up to four passes of the decode kernel).
+@pytest.mark.parametrize("E,K,T,rows_nan", [(16, 8, 8, (3,)), (16, 8, 8, (0, 5, 7)), (72, 9, 7, (0, 1, 6)), (200, 4, 8, tuple(range(7)))])
+def test_route_ffn_combine_of_an_expert_with_more_rows_than_tokens(hm, E, K, T, rows_nan):
+    """The same bits as the separate calls, of the ordinary tokens beside them above all."""
+    print("route_ffn_combine lowest NaN", E, K, T, rows_nan, flush=True)
+    shape = wl.small_shape(dtype=wl.BF16, hidden=128, ffn=192, n_experts=E, top_k=K, x_mode="rmsnorm")
+    lay = wl.make_layer(shape, 5 + E, T)
+    layer = build_layer(hm, lay, max_tokens=T)
+    d, c = layer.desc, layer.cache
+    lg = np.random.default_rng(E).standard_normal((T, E)).astype(np.float32)
+    lg[:, 0] += 9.0                                                   # expert 0: every ordinary token's first choice
+    lg.view(np.uint32)[list(rows_nan)] = 0xFFFFFFFF
+    lg, x = to_device(lg), to_device(lay.x)
+    outs = []
+    for fused in (True, False):
+        layer.ffn_ws.fill_(0xFF)
+        o, y = layer.o_perm.fill_(7.0), layer.y.fill_(7.0)
+        bufs = (layer.topk_idx, layer.topk_w, layer.offsets, layer.perm, layer.inv_perm)
+        if fused:
+            hm.hmoe_route_ffn_combine(d, c, x, lg, T, *bufs, layer.perm_ws, layer.perm_ws_bytes, o, layer.ffn_ws, layer.ffn_ws_bytes,
+                                      None, None, None, None, None, 0, y)
+        else:
+            hm.hmoe_route_permute(d, lg, T, *bufs, None, layer.perm_ws, layer.perm_ws_bytes)
+            hm.hmoe_expert_ffn_grouped_gather(d, c, x, layer.perm, layer.offsets, T * K, None, o, layer.ffn_ws, layer.ffn_ws_bytes)
+            hm.hmoe_combine(d, o, layer.inv_perm, layer.topk_w, None, T, y)
+        torch.cuda.synchronize()
+        outs.append([t.cpu().view(torch.int16) for t in bufs + (o, y)])
+    rows = outs[0][2].view(torch.int32)
+    assert int(rows[1] - rows[0]) == K * len(rows_nan) + T - len(rows_nan) > 8
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    layer.close()
+
+
 @pytest.mark.parametrize("dtype,shared_ffn,n_slots,logits_mode,tokens", [
     ("bf16", (64,), 8, "zipf", (1, 8, 9, 32, 33, 70)),      # shared experts in the routed launches, then beside them
     ("bf16", (64,), 8, "router", (1, 16, 17, 33, 5)),
