@@ -414,7 +414,7 @@ int32_t hmoe_route_ffn_combine(
  *   all_resident: hmoe_expert_ffn_grouped_gather (or _with_shared) over all experts; else hmoe_expert_ffn_staged, with
  *       h_wave, h_slot, h_victim, n_waves and staged_bytes as there (else they are not touched and may be NULL);
  *   hmoe_combine into y.
- * shared_offsets holds {0, T} on the device.  Errors as in those calls.
+ * shared_offsets holds {0, T} on the device; a captured call reads it at every replay.  Errors as in those calls.
  */
 typedef struct {
   const hmoe_layer_desc* desc;

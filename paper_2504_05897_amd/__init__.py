@@ -546,17 +546,19 @@ class MoELayer:
         self.sync = torch.zeros(self.sync_bytes, dtype=torch.uint8, device=dev)   # zeroed once; the calls leave it zero
         if self.shared_desc is not None:
             self.o_shared = torch.empty(T, H, dtype=self.dt, device=dev)
-            self.shared_offsets = torch.zeros(2, dtype=torch.int32, device=dev)
+            self.shared_offsets = torch.tensor([0, T], dtype=torch.int32, device=dev)   # for callers that make the calls themselves
+            # {0, t} for every batch size: a captured graph keeps reading the bounds of its own batch, whatever runs in between
+            self._shared_bounds = torch.zeros(T + 1, 2, dtype=torch.int32, device=dev)
+            self._shared_bounds[:, 1] = torch.arange(T + 1, dtype=torch.int32, device=dev)
             self.shared_ws_bytes = hmoe_ffn_workspace_bytes(self.shared_desc, T)
             self.shared_ws = torch.empty(max(self.shared_ws_bytes, 256), dtype=torch.uint8, device=dev)
-            self._shared_T = -1
         # what a forward pass in one library call needs: the layer's own buffers, which live as long as it does
         has = self.shared_desc is not None
         self._call = LayerCall(
             ctypes.pointer(d), self.cache, ctypes.pointer(self.shared_desc) if has else None, self.shared_cache if has else None,
             _ptr(self.w_router), _ptr(self.logits), _ptr(self.topk_idx), _ptr(self.topk_w), _ptr(self.offsets), _ptr(self.perm),
             _ptr(self.inv_perm), _ptr(self.h_counts), _ptr(self.perm_ws), self.perm_ws_bytes, _ptr(self.o_perm), _ptr(self.ffn_ws),
-            self.ffn_ws_bytes, _ptr(self.y), _ptr(self.shared_offsets) if has else None, _ptr(self.o_shared) if has else None,
+            self.ffn_ws_bytes, _ptr(self.y), None, _ptr(self.o_shared) if has else None,
             _ptr(self.shared_ws) if has else None, self.shared_ws_bytes if has else 0,
             None if self.h_packed_ptrs is None else ctypes.addressof(self.h_packed_ptrs), self.copy_stream.cuda_stream,
             self.side_stream.cuda_stream)
@@ -586,11 +588,10 @@ class MoELayer:
         assert T <= self.max_tokens and x.dtype == self.dt and x.is_contiguous()
         if all_resident is None:
             all_resident = d.n_slots == d.n_experts
-        if self.shared_desc is not None and self._shared_T != T:
-            self.shared_offsets.copy_(torch.tensor([0, T], dtype=torch.int32))
-            self._shared_T = T
+        bounds = None if self.shared_desc is None else self._shared_bounds.data_ptr() + 8 * T
         if self.fused and self.overlap_shared and self.merge_shared and not self.merge_combine:
             # the whole pass in one library call
+            self._call.shared_offsets = bounds
             plan = [None] * 5
             if not all_resident:
                 wave, slot, victim = (np.empty(d.n_experts, np.int32) for _ in range(3))
@@ -621,7 +622,7 @@ class MoELayer:
                 self.ev_fork.record(cur)
                 self.side_stream.wait_event(self.ev_fork)
                 with torch.cuda.stream(self.side_stream):
-                    hmoe_expert_ffn_grouped(self.shared_desc, self.shared_cache, x, self.shared_offsets, T, None,
+                    hmoe_expert_ffn_grouped(self.shared_desc, self.shared_cache, x, bounds, T, None,
                                             self.o_shared, self.shared_ws, self.shared_ws_bytes, path)
                     self.ev_join.record(self.side_stream)
         if logits is None and self.fused:
@@ -657,14 +658,14 @@ class MoELayer:
             sd = self.shared_desc
             hmoe_expert_ffn_combine(d, self.cache, x, self.perm, self.inv_perm, self.topk_w, self.offsets, T, self.o_perm,
                                     self.ffn_ws, self.ffn_ws_bytes, sd, None if sd is None else self.shared_cache,
-                                    None if sd is None else self.shared_offsets, None if sd is None else self.o_shared,
+                                    bounds, None if sd is None else self.o_shared,
                                     None if sd is None else self.shared_ws, 0 if sd is None else self.shared_ws_bytes,
                                     self.y, self.sync, self.sync_bytes, path)
             return self.y[:T]
         if merged:
             hmoe_expert_ffn_grouped_with_shared(d, self.cache, x, self.perm, self.offsets, A, None, self.o_perm,
                                                 self.ffn_ws, self.ffn_ws_bytes, self.shared_desc, self.shared_cache,
-                                                self.shared_offsets, T, self.o_shared, self.shared_ws,
+                                                bounds, T, self.o_shared, self.shared_ws,
                                                 self.shared_ws_bytes, path)
         elif all_resident:
             routed_ffn(None)
@@ -680,7 +681,7 @@ class MoELayer:
             if self.overlap_shared:
                 cur.wait_event(self.ev_join)
             else:
-                hmoe_expert_ffn_grouped(self.shared_desc, self.shared_cache, x, self.shared_offsets, T, None,
+                hmoe_expert_ffn_grouped(self.shared_desc, self.shared_cache, x, bounds, T, None,
                                         self.o_shared, self.shared_ws, self.shared_ws_bytes, path)
         hmoe_combine(d, self.o_perm, self.inv_perm, self.topk_w, o_shared, T, self.y)
         return self.y[:T]

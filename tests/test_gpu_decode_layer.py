@@ -147,3 +147,32 @@ def test_forward_in_one_call_equals_the_calls(hm, dtype, shared_ffn, n_slots, lo
     with pytest.raises(hm.HmoeError):
         one.forward(x, lg)
     calls.close()
+
+
+@pytest.mark.parametrize("dtype,sizes", [("w4", (4, 1)), ("w4", (1, 70)), ("bf16", (40, 33)), ("bf16", (8, 64)), ("f32", (3, 20))])
+def test_graphs_of_several_batch_sizes_on_one_layer(hm, dtype, sizes):
+    """Shared experts beside the routed ones: a replayed graph computes the rows of its own batch, in whatever order graphs and
+    eager calls of other sizes come."""
+    print("graphs of several batch sizes", dtype, sizes, flush=True)
+    shape = wl.small_shape(dtype=wl.F32 if dtype == "f32" else wl.BF16, hidden=128, ffn=256, n_experts=8, top_k=2, shared_ffn=(128,),
+                           x_mode="rmsnorm")
+    base = wl.make_layer(shape, 77, 1)
+    d = hm.make_desc(128, 256, 8, 2, 8, {"bf16": hm.HMOE_BF16, "f32": hm.HMOE_F32, "w4": hm.HMOE_BF16_W4}[dtype])
+    layer, alone = (hm.MoELayer(d, base.experts, base.shared, base.w_router, max_tokens=max(sizes)) for _ in range(2))
+    xs = [to_device(wl.make_layer(shape, 80 + T, T, with_weights=False).x) for T in sizes]
+    want = [alone.forward(x).cpu().clone() for x in xs]
+    graphs = []
+    for x in xs:                                          # (the first call with each size is the one that is captured)
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            layer.forward(x)
+    for i in (0, 1, 1, 0, 0, 1):
+        layer.y.fill_(7.0)
+        layer.o_shared.fill_(7.0)
+        graphs[i].replay()
+        torch.cuda.synchronize()
+        assert torch.equal(layer.y[:sizes[i]].cpu(), want[i]), i
+        eager = layer.forward(xs[1 - i]).cpu()            # an eager call of the other size before the next replay
+        assert torch.equal(eager, want[1 - i]), i
+    layer.close()
+    alone.close()
