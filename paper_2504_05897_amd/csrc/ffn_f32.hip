@@ -2,21 +2,27 @@
 // rest takes the general kernels of ffn_reference.hip, see ffn_f32_takes).  Weights are plain row-major.
 //
 // v_mfma_f64_16x16x4_f64 on operands widened to 64 bits: products are exact, sums are kept in 64 bits and rounded once, so
-// the order of the sums needs no care: error of the layer 1.07e-7 -> 7.3e-8 (2-norm, against 64 bits throughout).  It runs at
-// half the rate of the fp32 instruction, but that one needed 64 partial sums per output to be as exact as one wavefront per
-// output element: eight waves per tile with an eighth of K each, whose 64 KB of partial sums met in LDS, and gate/up of 1000
-// tokens took 8 times what its matrix instructions do.
+// the order of the sums needs no care.  Error of a layer (2-norm, against 64 bits throughout), with the fp32 instruction and 64
+// partial sums per output / here: 256 x 512 1.06e-7 / 7.3e-8, 1024 x 4096 1.9e-7 / 7.4e-8, 4096 x 4096 2.6e-7 / 6.7e-8.  It runs at
+// half the rate of the fp32 instruction, which needed eight waves per tile for those sums, and their 64 KB met in LDS.
 //   * A tile is 16 MR rows of one expert x 32 weight rows (gate and up of 16 features, or 32 columns of the down
-//     projection); every weight row is read once per tile instead of once per token.  The NW waves of the block share K in
-//     pieces of 16, dealt in turn, and their sums meet in LDS: eight waves with few rows, where latency counts, four with
-//     two row fragments (one, two or eight are slower from 64 to 1000 tokens: K is short, and a tile ends sooner).
+//     projection); every weight row is read once per tile instead of once per token.  The four waves of the block share K in
+//     pairs of pieces of 16, dealt in turn, and their sums meet in LDS.  (Pairs next to each other are the 128 bytes of a cache
+//     line; single pieces dealt in turn cost 5 to 12 % from K = 1408 on.  One or two waves, and eight but for one of 50 launches
+//     measured, are slower.)
 //   * Lane (j, kblk) loads four consecutive k of row j; element i of both operands forms the k-step {i, 4 + i, 8 + i,
-//     12 + i} of a piece, so no data moves between lanes.  Loads are unconditional (clamped, and cleared past the end of K),
-//     a set of two pieces ahead, weights first: the rows of gate/up hang on the row map.
-// Layer of 8 experts of 256 x 512, top 2, us in a graph, fp32 instruction -> this: 16 tokens 27.9 -> 27.6, 77 31.4 -> 32.0, 130 37.1
-// -> 36.6, 300 42.7 -> 40.1, 500 60.4 -> 53.6, 1000 89.5 -> 73.8 (gate/up 52.4 -> 37.2).
+//     12 + i} of a piece, so no data moves between lanes.  Loads are unconditional (clamped), a set of two pieces ahead,
+//     weights first: the rows of gate/up hang on the row map.
+//   * What bounds it with many rows is the instruction itself and the vector instructions beside it: 71 % of the time the matrix
+//     pipe was busy when every operand was widened and cleared past the end of K, one vector instruction each.  Only
+//     the last pieces clear now: one expert of 4096 x 4096, 1000 tokens, gate/up 1235 -> 1078 us (fp32 instruction 1168).
+// Layers (us in a graph), fp32 instruction / everything cleared, single pieces / now: 8 experts of 256 x 512, top 2, 16 tokens 20.7 /
+// 20.7 / 17.9, 77 24.5 / 25.5 / 22.7, 300 36.2 / 33.5 / 33.4, 1000 83.4 / 68.1 / 66.9; 8 of 1024 x 4096, top 2, 64 tokens 158 / 166 / 137, 1000
+// 1106 / 1073 / 949; 64 of 2048 x 1408, top 6, 300 tokens 934 / 871 / 764; 4 of 4096 x 4096, top 1, 3 tokens 132 / 127 / 133, 64 276 / 298 /
+// 251, 300 708 / 751 / 645, 1000 1847 / 1964 / 1713; one of 4096 x 4096, 64 tokens 147 / 167 / 139.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 #include "tile_locate.h"
@@ -30,9 +36,10 @@ __device__ __forceinline__ f64x4_t mfma_16x16x4_f64(double a, double b, f64x4_t 
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-template <bool GATEUP, int MR, int NW>
-__global__ __launch_bounds__(64 * NW) void ffn_f32_kernel(TiledCtx c, const float* __restrict__ in, float* __restrict__ out) {
-  constexpr int NU = 2, SET = 2;  // pieces per register set; two sets alternate
+constexpr int F32_WAVES = 4;
+template <bool GATEUP, int MR>
+__global__ __launch_bounds__(64 * F32_WAVES) void ffn_f32_kernel(TiledCtx c, const float* __restrict__ in, float* __restrict__ out) {
+  constexpr int NW = F32_WAVES, NU = 2, SET = 2;  // SET: pieces per register set, next to each other; two sets alternate
   __shared__ double red[NW][MR][NU][4][64];
   TileLoc loc;
   if (!locate_tile<16 * MR>(c, loc)) return;  // uniform over the block
@@ -61,7 +68,7 @@ __global__ __launch_bounds__(64 * NW) void ffn_f32_kernel(TiledCtx c, const floa
   auto load_weights = [&](int s, int p0) {
 #pragma unroll
     for (int d = 0; d < SET; ++d) {
-      const int k = min((p0 + d * NW) * 16 + kblk * 4, K - 4);  // K is a multiple of 4: four k are all inside or all outside
+      const int k = min((p0 + d) * 16 + kblk * 4, K - 4);  // K is a multiple of 4: four k are all inside or all outside
 #pragma unroll
       for (int u = 0; u < NU; ++u) b[s][d][u] = *(const f32x4_t*)(ws[u] + k);
     }
@@ -69,7 +76,7 @@ __global__ __launch_bounds__(64 * NW) void ffn_f32_kernel(TiledCtx c, const floa
   auto load_rows = [&](int s, int p0) {
 #pragma unroll
     for (int d = 0; d < SET; ++d) {
-      const int k = min((p0 + d * NW) * 16 + kblk * 4, K - 4);
+      const int k = min((p0 + d) * 16 + kblk * 4, K - 4);
 #pragma unroll
       for (int i = 0; i < MR; ++i) a[s][d][i] = *(const f32x4_t*)(xs[i] + k);
     }
@@ -79,10 +86,11 @@ __global__ __launch_bounds__(64 * NW) void ffn_f32_kernel(TiledCtx c, const floa
   for (int i = 0; i < MR; ++i)
 #pragma unroll
     for (int u = 0; u < NU; ++u) acc[i][u] = f64x4_t{0, 0, 0, 0};
-  auto multiply = [&](int s, int p0) {
+  auto multiply_set = [&](int s, int p0, auto inside) {
 #pragma unroll
     for (int d = 0; d < SET; ++d) {
-      const bool ok = (p0 + d * NW) * 16 + kblk * 4 < K;  // (both cleared past the end: what was read instead may not be finite)
+      // (both cleared past the end: what was read instead may not be finite)
+      const bool ok = decltype(inside)::value || (p0 + d) * 16 + kblk * 4 < K;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         double bd[NU];
@@ -97,11 +105,15 @@ __global__ __launch_bounds__(64 * NW) void ffn_f32_kernel(TiledCtx c, const floa
       }
     }
   };
-  load_weights(0, wave);
+  auto multiply = [&](int s, int p0) {
+    if ((p0 + SET) * 16 <= K) multiply_set(s, p0, std::true_type{});  // uniform
+    else multiply_set(s, p0, std::false_type{});
+  };
+  load_weights(0, wave * SET);
 #pragma unroll
   for (int i = 0; i < MR; ++i) xs[i] = in + (size_t)(GATEUP && c.row_map ? row[i] / c.map_div : row[i]) * K;
-  load_rows(0, wave);
-  for (int p = wave; p < pieces; p += 2 * SET * NW) {
+  load_rows(0, wave * SET);
+  for (int p = wave * SET; p < pieces; p += 2 * SET * NW) {
     load_weights(1, p + SET * NW);
     load_rows(1, p + SET * NW);
     __builtin_amdgcn_sched_barrier(0);  // (the compiler would move the loads down to their uses)
@@ -145,21 +157,22 @@ __global__ __launch_bounds__(64 * NW) void ffn_f32_kernel(TiledCtx c, const floa
   }
 }
 
-template <bool GATEUP, int MR, int NW>
+template <bool GATEUP, int MR>
 static void launch_stage_f32(TiledCtx c, int n_rows, const float* in, float* out, hipStream_t s) {
   c.n_tiles_n = GATEUP ? (c.ffn + 15) / 16 : (c.hidden + 31) / 32;
   c.grid_padded = (int)((tiles_upper_bound(c, n_rows, 16 * MR) + 7) / 8 * 8);
-  hipLaunchKernelGGL((ffn_f32_kernel<GATEUP, MR, NW>), dim3((unsigned)c.grid_padded), dim3(64 * NW), 0, s, c, in, out);
+  hipLaunchKernelGGL((ffn_f32_kernel<GATEUP, MR>), dim3((unsigned)c.grid_padded), dim3(64 * F32_WAVES), 0, s, c, in, out);
 }
 
 // The general kernels read an expert's weights for every row again, out of the caches (about 6 TB/s); the tiles read them
-// once, but from memory at four fifths of the general kernels' rate, and their two launches start 5 us later (locating a
-// tile, one wave per piece of K, sums in LDS).  So the general kernels have it until the rows that find their expert's
-// weights already read, by uniform routing, re-read more than 30 MB (100 MB where all of the layer's weights stay in an L2)
-// and 15 % of what is read in any case.  Layers, general kernels / tiles, us: 8 experts of 256 x 512, top 2: 8 tokens
-// 15.1 / 19.6, 16 tokens 24.6 / 20.5; 8 of 1024 x 4096, top 2: 2 tokens 56.9 / 63.5, 3 tokens 68.5 / 65.6; 64 of 1024 x 512, top 8: 4
-// tokens 64.3 / 67.0, 6 tokens 85.2 / 81.0; one of 256 x 512: 33 tokens 19.8 / 23.1, 64 tokens 25.0 / 25.0; 4 of 64 x 96, top 2: 64 tokens
-// 15.6 / 19.3.
+// once, and their two launches start later (locating a tile, one wave per piece of K, sums in LDS).  So the general kernels
+// have it until the rows that find their expert's weights already read, by uniform routing, re-read more than 30 MB (100 MB
+// where all of the layer's weights stay in an L2) and 15 % of what is read in any case.  The line was drawn where the tiles on
+// the fp32 instruction began to win; against the present ones it is late by a few tokens.  Layers, general kernels / tiles,
+// us in a graph (* what the rule takes): 8 experts of 256 x 512, top 2: 8 tokens 15.0* / 17.2, 10 tokens 20.3* / 17.2, 16 tokens 24.2 / 17.9*;
+// 8 of 1024 x 4096, top 2: 2 tokens 56.0* / 52.5, 3 tokens 67.0 / 57.8*; 64 of 1024 x 512, top 8: 3 tokens 48.2* / 45.2, 6 tokens
+// 74.0 / 62.5*; one of 256 x 512: 33 tokens 19.6* / 21.8, 64 tokens 24.0* / 23.6, 90 tokens 29.8 / 22.5*; 4 of 64 x 96, top 2: 64 tokens
+// 15.3* / 17.6, 200 tokens 24.2* / 19.0.
 bool ffn_f32_takes(const hmoe_layer_desc& d, int n_rows) {
   if (d.dtype != HMOE_F32 || d.hidden % 4 != 0 || d.ffn % 4 != 0) return false;
   const long n_tiles = std::max((d.ffn + 15) / 16, (d.hidden + 31) / 32);  // the grid has to fit its 32-bit dimension
@@ -178,10 +191,10 @@ int launch_ffn_f32(const FfnArgs& a) {
   // else two, which halve the reads of the weights
   const bool one = a.n_rows < 16 * d.n_experts;
   probe_before(a.stream);
-  (one ? launch_stage_f32<true, 1, 8> : launch_stage_f32<true, 2, 4>)(c, a.n_rows, (const float*)a.x_perm, (float*)a.h, a.stream);
+  (one ? launch_stage_f32<true, 1> : launch_stage_f32<true, 2>)(c, a.n_rows, (const float*)a.x_perm, (float*)a.h, a.stream);
   probe_after(a.stream);
   probe_before(a.stream);
-  (one ? launch_stage_f32<false, 1, 8> : launch_stage_f32<false, 2, 4>)(c, a.n_rows, (const float*)a.h, (float*)a.o_perm, a.stream);
+  (one ? launch_stage_f32<false, 1> : launch_stage_f32<false, 2>)(c, a.n_rows, (const float*)a.h, (float*)a.o_perm, a.stream);
   probe_after(a.stream);
   HMOE_HIP(hipGetLastError());
   return HMOE_OK;
