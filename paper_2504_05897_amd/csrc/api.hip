@@ -670,15 +670,16 @@ extern "C" int32_t hmoe_route_ffn_combine(
   int rc = check_desc(desc);
   if (rc != HMOE_OK) return rc;
   if (T < 0 || T > 0x7fffffff / desc->top_k || !expert_offsets) return HMOE_ERR_INVALID_ARG;
-  if (T == 0) return HMOE_OK;
   const int32_t A = T * desc->top_k;
-  if (!logits || !topk_idx || !topk_w || !perm || !inv_perm || !y || !aligned16(y)) return HMOE_ERR_INVALID_ARG;
-  if (shared_desc && !o_shared) return HMOE_ERR_INVALID_ARG;
-  if ((reinterpret_cast<uintptr_t>(logits) | reinterpret_cast<uintptr_t>(topk_idx) | reinterpret_cast<uintptr_t>(topk_w)) & 3u)
-    return HMOE_ERR_INVALID_ARG;
-  // Decode batches of bf16 layers: routing inside the first launch of the FFN.  Everything else, and whatever these
-  // checks refuse: the calls this one stands for, one after the other.
-  if (ffn_skinny_routes(*desc, T) && (!shared_desc || (shared_desc->n_experts == 1 && shared_desc->n_slots == 1 &&
+  if (T > 0) {
+    if (!logits || !topk_idx || !topk_w || !perm || !inv_perm || !y || !aligned16(y)) return HMOE_ERR_INVALID_ARG;
+    if (shared_desc && !o_shared) return HMOE_ERR_INVALID_ARG;
+    if ((reinterpret_cast<uintptr_t>(logits) | reinterpret_cast<uintptr_t>(topk_idx) | reinterpret_cast<uintptr_t>(topk_w)) & 3u)
+      return HMOE_ERR_INVALID_ARG;
+  }
+  // Decode batches of bf16 layers: routing inside the first launch of the FFN.  Everything else, an empty batch (whose offsets are
+  // written too), and whatever these checks refuse: the calls this one stands for, one after the other.
+  if (T > 0 && ffn_skinny_routes(*desc, T) && (!shared_desc || (shared_desc->n_experts == 1 && shared_desc->n_slots == 1 &&
                                                        shared_desc->top_k == 1 && shared_desc->hidden == desc->hidden &&
                                                        shared_desc->dtype == desc->dtype))) {
     FfnArgs routed, dense;

@@ -176,3 +176,28 @@ def test_graphs_of_several_batch_sizes_on_one_layer(hm, dtype, sizes):
         assert torch.equal(eager, want[1 - i]), i
     layer.close()
     alone.close()
+
+
+@pytest.mark.parametrize("dtype,shared_ffn,n_slots,logits_mode", [("bf16", (), 8, "zipf"), ("bf16", (64,), 8, "router"), ("f32", (), 8, "router"),
+                                                                  ("bf16", (64,), 3, "zipf")])
+def test_an_empty_batch_leaves_zero_offsets(hm, dtype, shared_ffn, n_slots, logits_mode):
+    """forward(x[:0]) says that no expert has rows, as the routing call does, whatever the batch before it was."""
+    print("empty batch", dtype, shared_ffn, n_slots, flush=True)
+    shape = wl.small_shape(dtype=wl.F32 if dtype == "f32" else wl.BF16, hidden=128, ffn=192, n_experts=8, top_k=2, shared_ffn=shared_ffn,
+                           x_mode="rmsnorm", logits_mode=logits_mode)
+    lay = wl.make_layer(shape, 9, 5)
+    layer = build_layer(hm, lay, max_tokens=5, n_slots=n_slots)
+    x, lg = to_device(lay.x), None if logits_mode == "router" else to_device(lay.logits)
+    for T in (5, 0, 3, 0):
+        y = layer.forward(x[:T], None if lg is None else lg[:T])
+        torch.cuda.synchronize()
+        assert y.shape == (T, 128) and int(layer.offsets[-1]) == 2 * T
+        if T == 0:
+            assert not layer.offsets.any()
+    if dtype == "bf16":
+        layer.offsets.fill_(-7)
+        hm.hmoe_route_ffn_combine(layer.desc, layer.cache, x, lg, 0, None, None, layer.offsets, None, None, layer.perm_ws,
+                                  layer.perm_ws_bytes, None, None, 0, None, None, None, None, None, 0, None)
+        torch.cuda.synchronize()
+        assert not layer.offsets.any()
+    layer.close()
