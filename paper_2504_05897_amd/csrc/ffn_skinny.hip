@@ -688,11 +688,14 @@ int launch_ffn_skinny_w4(const FfnArgs& a) {
   if (a.n_rows == 0) return HMOE_OK;
   SkinnyCtx c{a.offsets, a.slot_of, a.slots, a.slot_bytes, a.active, d.n_experts, d.hidden, d.ffn, 1, a.row_map, a.map_div, {}, {}, {}};
   const int busy_max = std::min(d.n_experts, a.n_rows);  // every busy expert has at least one row
-  const size_t in_rows = a.row_map ? (size_t)a.n_rows / a.map_div : a.n_rows;
+  // Offsets of 32 bits: larger inputs take the tiles.  A row map may name any row of x, whatever the number of assignments
+  // (those of some experts only, for instance), so that its descriptor ends where offsets do, not at n_rows / map_div rows.
+  constexpr uint32_t FAR = 0xF0000000u;
+  const size_t in_rows = a.row_map ? ((size_t)a.n_rows + a.map_div - 1) / a.map_div : a.n_rows;
   const size_t in_bytes = in_rows * d.hidden * 2, h_bytes = (size_t)a.n_rows * d.ffn * 2;
-  if (in_bytes > 0xF0000000u || h_bytes > 0xF0000000u) return launch_ffn_tiled_w4(a);
+  if (in_bytes > FAR || h_bytes > FAR) return launch_ffn_tiled_w4(a);
   probe_before(a.stream);
-  launch_stage_w4<true>(c, d.ffn, busy_max, (const bf16_t*)a.x_perm, (uint32_t)in_bytes, (bf16_t*)a.h, a.stream);
+  launch_stage_w4<true>(c, d.ffn, busy_max, (const bf16_t*)a.x_perm, a.row_map ? FAR : (uint32_t)in_bytes, (bf16_t*)a.h, a.stream);
   probe_after(a.stream);
   probe_before(a.stream);
   launch_stage_w4<false>(c, d.hidden, busy_max, (const bf16_t*)a.h, (uint32_t)h_bytes, (bf16_t*)a.o_perm, a.stream);

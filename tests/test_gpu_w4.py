@@ -129,3 +129,24 @@ def test_w4_decode_blocks_of_two_pairs(hm, hidden, ffn, counts):
             ref[lo:hi] = orc.expert_ffn(wl.as_f64(x[lo:hi]), *values[e % 3])
     assert max_rel_err(to_host_f32(o), ref) < TOL[wl.BF16]
     layer.close()
+
+
+@pytest.mark.parametrize("dtype,path", [("w4", 0), ("w4", 1), ("w4", 3), ("bf16", 0), ("bf16", 1), ("bf16", 3), ("f32", 0), ("f32", 1)])
+def test_gather_of_some_assignments(hm, dtype, path):
+    """A call may be given the assignments of some experts only: the rows its permutation names are then not the first A / K
+    of x.  The same bits as the call over the gathered rows."""
+    print("gather of some assignments", dtype, path, flush=True)
+    hidden, ffn, E, K = 256, 128, 4, 2
+    shape = wl.small_shape(dtype=wl.F32 if dtype == "f32" else wl.BF16, hidden=hidden, ffn=ffn, n_experts=E, top_k=K)
+    lay = wl.make_layer(shape, 3, n_tokens=9)
+    d = hm.make_desc(hidden, ffn, E, K, E, {"w4": hm.HMOE_BF16_W4, "bf16": hm.HMOE_BF16, "f32": hm.HMOE_F32}[dtype])
+    layer = hm.MoELayer(d, lay.experts, (), None, max_tokens=9)
+    x = to_device(lay.x)
+    perm = torch.tensor([17, 3, 12, 5, 16], dtype=torch.int32, device=DEV)
+    offsets = torch.tensor([0, 2, 2, 4, 5], dtype=torch.int32, device=DEV)
+    a, b = (torch.full((5, hidden), float("nan"), dtype=layer.dt, device=DEV) for _ in range(2))
+    hm.hmoe_expert_ffn_grouped_gather(d, layer.cache, x, perm, offsets, 5, None, a, layer.ffn_ws, layer.ffn_ws_bytes, path)
+    hm.hmoe_expert_ffn_grouped(d, layer.cache, x[(perm // K).long()].contiguous(), offsets, 5, None, b, layer.ffn_ws, layer.ffn_ws_bytes, path)
+    torch.cuda.synchronize()
+    assert torch.equal(a.cpu(), b.cpu()) and a.float().abs().amin(dim=1).isfinite().all() and (a.float().abs().amax(dim=1) > 0).all()
+    layer.close()
