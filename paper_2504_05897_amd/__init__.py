@@ -552,23 +552,35 @@ class MoELayer:
             self._shared_bounds[:, 1] = torch.arange(T + 1, dtype=torch.int32, device=dev)
             self.shared_ws_bytes = hmoe_ffn_workspace_bytes(self.shared_desc, T)
             self.shared_ws = torch.empty(max(self.shared_ws_bytes, 256), dtype=torch.uint8, device=dev)
-        # what a forward pass in one library call needs: the layer's own buffers, which live as long as it does
-        has = self.shared_desc is not None
-        self._call = LayerCall(
-            ctypes.pointer(d), self.cache, ctypes.pointer(self.shared_desc) if has else None, self.shared_cache if has else None,
-            _ptr(self.w_router), _ptr(self.logits), _ptr(self.topk_idx), _ptr(self.topk_w), _ptr(self.offsets), _ptr(self.perm),
-            _ptr(self.inv_perm), _ptr(self.h_counts), _ptr(self.perm_ws), self.perm_ws_bytes, _ptr(self.o_perm), _ptr(self.ffn_ws),
-            self.ffn_ws_bytes, _ptr(self.y), None, _ptr(self.o_shared) if has else None,
-            _ptr(self.shared_ws) if has else None, self.shared_ws_bytes if has else 0,
-            None if self.h_packed_ptrs is None else ctypes.addressof(self.h_packed_ptrs), self.copy_stream.cuda_stream,
-            self.side_stream.cuda_stream)
-        self._call_ref = ctypes.byref(self._call)
+        self._call_of = None
+        self._layer_call(None)
+
+    def _layer_call(self, bounds) -> LayerCall:
+        """Every buffer of a forward pass in one library call.  The attributes are the caller's to replace (a router loaded
+        later, a larger work buffer), tensors also by setting their `data`: the struct is filled again when any of them lies
+        elsewhere than in the last pass (1.5 us to see)."""
+        s = self.shared_desc is not None
+        of = (self.desc, self.cache, self.shared_desc, self.shared_cache if s else None,
+              None if self.w_router is None else self.w_router.data_ptr(), self.logits.data_ptr(), self.topk_idx.data_ptr(),
+              self.topk_w.data_ptr(), self.offsets.data_ptr(), self.perm.data_ptr(), self.inv_perm.data_ptr(),
+              self.h_counts.data_ptr(), self.perm_ws.data_ptr(), self.perm_ws_bytes, self.o_perm.data_ptr(), self.ffn_ws.data_ptr(),
+              self.ffn_ws_bytes, self.y.data_ptr(), None, self.o_shared.data_ptr() if s else None,
+              self.shared_ws.data_ptr() if s else None, self.shared_ws_bytes if s else 0, self.h_packed_ptrs, self.copy_stream,
+              self.side_stream)
+        if of != self._call_of:
+            desc, cache, shared_desc, *buffers, packed, copy_stream, side_stream = of
+            self._call = LayerCall(ctypes.pointer(desc), cache, ctypes.pointer(shared_desc) if s else None, *buffers,
+                                   None if packed is None else ctypes.addressof(packed), copy_stream.cuda_stream,
+                                   side_stream.cuda_stream)
+            self._call_of = of
+        self._call.shared_offsets = bounds
+        return self._call
 
     def close(self):
         if getattr(self, "cache", None):
             torch.cuda.synchronize(self.dev)
             hmoe_cache_destroy(self.cache)
-            self.cache = self._call.cache = None
+            self.cache = None
             if self.shared_desc is not None:
                 hmoe_cache_destroy(self.shared_cache)
 
@@ -591,13 +603,12 @@ class MoELayer:
         bounds = None if self.shared_desc is None else self._shared_bounds.data_ptr() + 8 * T
         if self.fused and self.overlap_shared and self.merge_shared and not self.merge_combine:
             # the whole pass in one library call
-            self._call.shared_offsets = bounds
             plan = [None] * 5
             if not all_resident:
                 wave, slot, victim = (np.empty(d.n_experts, np.int32) for _ in range(3))
                 n_waves, staged = ctypes.c_int32(), ctypes.c_uint64()
                 plan = [_ptr(wave), _ptr(slot), _ptr(victim), ctypes.addressof(n_waves), ctypes.addressof(staged)]
-            rc = _lib.hmoe_layer_forward(self._call_ref, x.data_ptr(), None if logits is None else logits.data_ptr(), T, path,
+            rc = _lib.hmoe_layer_forward(ctypes.byref(self._layer_call(bounds)), x.data_ptr(), None if logits is None else logits.data_ptr(), T, path,
                                          1 if all_resident else 0, *plan, torch.cuda.current_stream().cuda_stream)
             if rc:
                 _check(rc, "hmoe_layer_forward")

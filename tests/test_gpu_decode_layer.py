@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import workloads as wl
-from hmoe_testlib import build_layer, to_device
+from hmoe_testlib import build_layer, desc_of, to_device
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -200,4 +200,39 @@ def test_an_empty_batch_leaves_zero_offsets(hm, dtype, shared_ffn, n_slots, logi
                                   layer.perm_ws_bytes, None, None, 0, None, None, None, None, None, 0, None)
         torch.cuda.synchronize()
         assert not layer.offsets.any()
+    layer.close()
+
+
+@pytest.mark.parametrize("dtype,shared_ffn,T", [("bf16", (64,), 3), ("bf16", (64,), 40), ("f32", (), 5)])
+def test_replaced_buffers_and_streams_are_used(hm, dtype, shared_ffn, T):
+    """A layer's attributes may be replaced between two passes, a tensor also through its `data`: the next pass reads the new
+    router and writes the new buffers, and the old ones stay as they were."""
+    print("replaced buffers", dtype, shared_ffn, T, flush=True)
+    shape = wl.small_shape(dtype=wl.F32 if dtype == "f32" else wl.BF16, hidden=128, ffn=192, n_experts=8, top_k=2, shared_ffn=shared_ffn,
+                           x_mode="rmsnorm")
+    lay, other = wl.make_layer(shape, 31, T), wl.make_layer(shape, 32, T)
+    x = to_device(lay.x)
+    want = {}
+    for name, router in (("first", lay.w_router), ("second", other.w_router)):
+        fresh = hm.MoELayer(desc_of(hm, shape), lay.experts, lay.shared, router, max_tokens=T)
+        want[name] = fresh.forward(x).cpu().clone()
+        fresh.close()
+    layer = build_layer(hm, lay, max_tokens=T)
+    assert torch.equal(layer.forward(x).cpu(), want["first"])
+    kept = {}
+    for n in ("logits", "topk_idx", "topk_w", "offsets", "perm", "inv_perm", "o_perm", "y", "perm_ws", "ffn_ws") + \
+            (("o_shared", "shared_ws") if shared_ffn else ()):
+        kept[n] = getattr(layer, n)
+        setattr(layer, n, torch.empty_like(kept[n]))
+    before = {n: t.cpu().clone() for n, t in kept.items()}
+    layer.w_router = to_device(other.w_router)
+    layer.side_stream = torch.cuda.Stream()
+    y = layer.forward(x)
+    torch.cuda.synchronize()
+    assert y.data_ptr() == layer.y.data_ptr() and torch.equal(y.cpu(), want["second"])
+    for n, t in kept.items():
+        assert torch.equal(t.cpu().view(torch.uint8), before[n].view(torch.uint8)), n
+    second = layer.w_router.data
+    layer.w_router.data = to_device(lay.w_router)
+    assert torch.equal(layer.forward(x).cpu(), want["first"]) and second.data_ptr() != layer.w_router.data_ptr()
     layer.close()
