@@ -173,9 +173,13 @@ __global__ __launch_bounds__(64 * NW) void ffn_skinny_kernel(SkinnyCtx c, const 
       if (wave == 0) permute_rank_one_wave<RV>(chosen, n_assign, c.n_experts, rt.offsets, nullptr, rt.perm, rt.inv_perm);
       return;
     }
-    // The block's expert: the want-th that is active, resident and named.  (LDS serves a wave's accesses in order.)
+    // The block's expert: the want-th that is active, resident and named.
     const int mine = lane < n_assign ? chosen[lane] : 64 * RV;
     if (lane < n_assign) named[wave][mine] = 1;
+    // (other lanes of the wave read it below: LDS serves a wave's accesses in order, this keeps the compiler to it)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     int want = (int)blockIdx.y - c.shared.grid_rows, e = -1, s = -1;
 #pragma unroll
     for (int i = 0; i < RV; ++i) {
