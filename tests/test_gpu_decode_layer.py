@@ -20,11 +20,13 @@ def hm():
     (8, 2, 128, 192, (64,), (1, 3, 8, 9)),          # 9 tokens: routing in a launch of its own
     (64, 6, 256, 64, (192,), (1, 8)),
     (64, 8, 64, 320, (), (1, 8)),                   # 64 assignments, the most
-    (65, 9, 64, 64, (64,), (1, 7, 8)),              # four experts per lane; 63 and 72 assignments
+    (65, 9, 64, 64, (64,), (1, 7, 8)),              # two experts per lane; 63 and 72 assignments
     (256, 32, 64, 64, (), (1, 2, 3)),               # 64 and 96 assignments
     (200, 3, 128, 64, (448,), (2, 8)),              # more shared groups than routed ones: several grid rows
     (1, 1, 64, 128, (), (1, 8)),
     (16, 4, 64, 8192, (64,), (1, 4)),               # 200 blocks and more: eight waves
+    (96, 8, 128, 512, (64,), (3, 8)),               # the same with two experts per lane
+    (200, 8, 128, 512, (), (8,)),                   # and with four
 ])
 def test_route_ffn_combine_equals_the_separate_calls(hm, E, K, hidden, ffn, shared_ffn, tokens):
     """Every output the same bits as hmoe_route_permute, the FFN call and hmoe_combine; ties and masked logits among them."""
@@ -107,6 +109,39 @@ def test_route_ffn_combine_of_an_expert_with_more_rows_than_tokens(hm, E, K, T, 
     for a, b in zip(*outs):
         assert torch.equal(a, b)
     layer.close()
+
+
+# The router spread over blocks of 16 experts with the routing inside the decode launch, as a layer with a router runs them: one and
+# several blocks, the last one not full, one, two and four experts per lane, both widths of the launch; T = 9 and 17 leave them.
+@pytest.mark.parametrize("E,K,hidden,ffn,shared_ffn,tokens", [
+    (16, 2, 128, 64, (), (1, 8)), (17, 4, 64, 128, (64,), (1, 8, 9)), (64, 6, 128, 640, (128,), (1, 7, 17)), (90, 8, 128, 64, (64,), (1, 8)),
+    (100, 8, 64, 512, (), (2, 8)), (129, 5, 256, 64, (), (1, 8)), (256, 8, 128, 512, (64,), (1, 8, 9)),
+])
+def test_forward_with_a_router_of_many_experts_equals_the_calls(hm, E, K, hidden, ffn, shared_ffn, tokens):
+    """MoELayer.forward against hmoe_router_route_permute, the FFN calls and hmoe_combine: the same bits in every output."""
+    shape = wl.small_shape(dtype=wl.BF16, hidden=hidden, ffn=ffn, n_experts=E, top_k=K, shared_ffn=shared_ffn, x_mode="rmsnorm")
+    lay = wl.make_layer(shape, 40 + E, max(tokens))
+    one, calls = (build_layer(hm, lay, max_tokens=max(tokens)) for _ in range(2))
+    d, c = calls.desc, calls.cache
+    for T in tokens:
+        print("forward with a router", E, K, T, flush=True)
+        x = to_device(lay.x[:T])
+        y = one.forward(x)
+        hm.hmoe_router_route_permute(d, x, calls.w_router, T, calls.logits, calls.topk_idx, calls.topk_w, calls.offsets, calls.perm,
+                                     calls.inv_perm, None, calls.perm_ws, calls.perm_ws_bytes)
+        hm.hmoe_expert_ffn_grouped_gather(d, c, x, calls.perm, calls.offsets, T * K, None, calls.o_perm, calls.ffn_ws, calls.ffn_ws_bytes)
+        if shared_ffn:
+            bounds = torch.tensor([0, T], dtype=torch.int32, device=DEV)
+            hm.hmoe_expert_ffn_grouped(calls.shared_desc, calls.shared_cache, x, bounds, T, None, calls.o_shared, calls.shared_ws,
+                                       calls.shared_ws_bytes)
+        hm.hmoe_combine(d, calls.o_perm, calls.inv_perm, calls.topk_w, calls.o_shared if shared_ffn else None, T, calls.y)
+        torch.cuda.synchronize()
+        assert y.abs().amax() > 1e-3
+        for n, rows in (("logits", T), ("topk_idx", T), ("topk_w", T), ("offsets", E + 1), ("perm", T * K), ("inv_perm", T * K),
+                        ("o_perm", T * K), ("y", T)):
+            assert torch.equal(getattr(one, n)[:rows].cpu(), getattr(calls, n)[:rows].cpu()), (T, n)
+    one.close()
+    calls.close()
 
 
 @pytest.mark.parametrize("dtype,shared_ffn,n_slots,logits_mode,tokens", [
