@@ -50,7 +50,7 @@ PHASES = {
 ALL = ["mixtral", "dsv2lite", "qwen2moe", "stress"]      # the default run, largest last: it is the headline
 SEED0 = {"toy": 0, "mixtral": 1, "dsv2lite": 2, "qwen2moe": 3}
 # sources of the kernels whose HBM traffic profiles/traffic.json records
-TRAFFIC_SOURCES = ["ffn_tiled.hip", "tile_locate.h", "ffn_skinny.hip", "ffn_tiled_w4.hip", "ffn_tiled_w4_wide.hip", "common.h"]
+TRAFFIC_SOURCES = ["ffn_tiled.hip", "tile_locate.h", "ffn_skinny.hip", "route_body.h", "ffn_tiled_w4.hip", "ffn_tiled_w4_wide.hip", "common.h"]
 
 
 def kernel_sources_digest() -> str:
