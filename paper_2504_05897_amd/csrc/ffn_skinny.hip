@@ -506,8 +506,10 @@ int launch_ffn_skinny(const FfnArgs& a, const FfnArgs* dense, const CombineArgs*
 // Everything is loaded through buffer descriptors: a scalar base, a scalar offset per load and one lane offset for all, and
 // lanes without a token get an offset past the end, which fetches nothing.  With 64-bit addresses per lane the kernel held
 // 190 registers, so 8 waves per CU, spent as many vector instructions on addresses as on codes, and every wave fetched the
-// first token 16 times over.  At 124 registers twice the waves are resident, two groups each in flight are enough (more are
-// slower), and there is room for two pairs per block (see launch_stage_w4).  Layers, before -> now, us: 8 experts of 4096 x
+// first token 16 times over.  At 124 registers twice the waves are resident, two groups each in flight are enough (launches
+// with three, us: gate/up of two pairs, 8 experts of 4096 x 14336, 8 tokens 75 -> 83, down 41 -> 43), and there is room for two
+// pairs per block (see launch_stage_w4).  Gate/up of one pair takes three, for the one wave that walks all of K: the same layer, 1
+// token, 28.7 -> 26.2; with few scale groups that is late by as much (64 of 2048 x 1408 10.7 -> 11.6, 8 of 1024 x 2048 6.5 -> 7.0).  Layers, before -> now, us: 8 experts of 4096 x
 // 14336, top 2, 1 / 2 / 4 / 8 / 16 tokens 59.1 -> 50.4, 84.0 -> 77.2, 120.7 -> 110.2, 140.3 -> 127.9, 159.8 -> 143.8; 64 of
 // 2048 x 1408, top 6, 1 / 16 tokens 36.1 -> 33.8, 81.0 -> 76.5; 40 of 3584 x 2560, top 8, one shared, 1 / 8 tokens 72.7 -> 61.4,
 // 109.5 -> 100.2; 8 of 1024 x 2048, top 2, 3 tokens 26.7 -> 22.1.

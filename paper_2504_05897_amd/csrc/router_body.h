@@ -6,8 +6,8 @@
 
 namespace hmoe {
 
-constexpr int ROUTER_SMALL_T = 16;      // tokens up to which a single block computes the logits (and the fused front end
-                                        // routes and permutes in the same launch)
+constexpr int ROUTER_SMALL_T = 16;      // tokens up to which the fused front end is one block, which computes the logits, routes
+                                        // and permutes (hmoe_router_logits: a block per 16 experts, all tokens)
 
 // How a block of NW waves divides its work: MA fragments of 16 tokens; the waves split K KS ways, and NW / KS groups of
 // them own NF fragments of 16 experts each.

@@ -41,7 +41,8 @@ def reference(x, offsets, experts, hidden, to_f64):
     return ref
 
 
-# one 16-row fragment per tile and two; K of one and several rounds of 256 with remainders; widths that are no multiple of 16
+# one 16-row fragment per tile and two; K of one and several rounds of 128 (four waves, two pieces of 16 each) with remainders; widths
+# that are no multiple of 16
 @pytest.mark.parametrize("hidden,ffn,counts", [
     (256, 512, [1, 0, 16, 5]), (4, 8, [3, 1]), (260, 36, [17, 2, 0, 1]), (516, 772, [2, 9]),
     (256, 512, [31, 0, 33, 64, 1]), (100, 44, [40, 15]), (1028, 20, [65, 32]),
@@ -53,8 +54,8 @@ def test_ffn_f32_tiles(hm, hidden, ffn, counts):
     shape, lay, offsets, x = case(wl.F32, hidden, ffn, counts)
     d = desc_of(hm, shape, n_slots=len(counts))
     got = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_AUTO)
-    # sums of K / 64 products each in fp32, then 64 bits: at most 24 roundings of 2^-24 per GEMM at these sizes, and a
-    # handful in silu: 2e-6 of the largest value, and as much again for cancellation
+    # the general kernels' 64 sums of K / 64 products each in fp32: at most 24 roundings of 2^-24 per GEMM at these sizes, and a
+    # handful in silu: 2e-6 of the largest value, and as much again for cancellation (the tiles' 64-bit sums are closer)
     assert max_rel_err(got, reference(x, offsets, lay.experts, hidden, wl.as_f64)) < 4e-6
     general = grouped_ffn(hm, d, lay.experts, x, offsets, hm.HMOE_FFN_REFERENCE)
     # the calls that are too small for the tiles take the general kernels
