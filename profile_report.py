@@ -162,7 +162,7 @@ def main() -> int:
                     os.remove(os.path.join(out_dir, f))
 
     md = ["# rocprofv3 summary: %s" % args.name, "",
-          "Written by `python3 profile_report.py %s%s%s -- %s` (on the GPU box, from the repository root), which runs"
+          "Written by `python3 profile_report.py %s%s%s -- %s` (from the repository root), which runs"
           % (args.name, " --sq" if args.sq else "", "".join(" --traffic " + t for t in args.traffic), " ".join(args.bench_args)),
           "", "```"] + commands + ["```", ""]
     with open(os.path.join(out_dir, "trace.log")) as fh:
