@@ -693,6 +693,7 @@ extern "C" int32_t hmoe_route_ffn_combine(
     if (rc != HMOE_OK) return rc;
     if (path_routed == HMOE_FFN_SKINNY && (!shared_desc || (path_dense == HMOE_FFN_SKINNY && shared_cache->slot_of[0] >= 0))) {
       if (!perm_workspace || perm_workspace_bytes < hmoe_permute_workspace_bytes(desc, T)) return HMOE_ERR_WORKSPACE;
+      if (reinterpret_cast<uintptr_t>(perm_workspace) & 3u) return HMOE_ERR_INVALID_ARG;  // (as hmoe_route_permute)
       if (shared_desc) dense.slots = shared_cache->slots + (size_t)shared_cache->slot_of[0] * shared_cache->slot_bytes;
       RouteArgs route;
       route.logits = logits;

@@ -73,6 +73,10 @@ def test_route_ffn_combine_equals_the_separate_calls(hm, E, K, hidden, ffn, shar
         hm.hmoe_route_ffn_combine(d, c, x, lg, 1, idx, w, offs, perm, inv, layer.perm_ws, 0, o, layer.ffn_ws, layer.ffn_ws_bytes,
                                   *shared, osh, *sws, y)
     assert ei.value.status == hm.HMOE_ERR_WORKSPACE
+    with pytest.raises(hm.HmoeError) as ei:
+        hm.hmoe_route_ffn_combine(d, c, x, lg, 1, idx, w, offs, perm, inv, layer.perm_ws.data_ptr() + 2, layer.perm_ws_bytes, o, layer.ffn_ws,
+                                  layer.ffn_ws_bytes, *shared, osh, *sws, y)
+    assert ei.value.status == hm.HMOE_ERR_INVALID_ARG
     layer.close()
 
 
